@@ -10,10 +10,17 @@
  * outputs (two FP64 or four FP32 samples).  The hybrid quantiles gather
  * their outer elements across the wave exactly as the streaming kernel does
  * (hybrid_eval), so every output is bitwise the one qm_normal_quantile gives
- * for the same uniform.  Outputs before the first block boundary, after the
- * last whole block, or in an output array that is not 16-byte aligned at a
- * block boundary are done one element at a time by the same per-element
- * functions.
+ * for the same uniform.  Outputs before the first block boundary and after
+ * the last whole block (fewer than two blocks' worth) are done one element
+ * at a time by the same per-element functions.
+ *
+ * The 16-byte stores need only the element's alignment (gfx950 takes a
+ * dwordx4 access at any dword), so every sub-range of a stream and every
+ * output address goes through whole blocks.  A stream index and an address
+ * that disagree modulo 16 bytes used to draw each element's block afresh,
+ * twice the Philox work in FP64 and four times in FP32, and to vote instead
+ * of gather: 2^24 FP64 Student t samples from an odd element took 141 us on
+ * MI355X, and 75 here; FP32 quantiles from one 71, and 26 here.
  */
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -40,6 +47,11 @@ struct GenArgs {
     uint64_t n;
 };
 
+/* One block's outputs, 16 bytes at the alignment of an element. */
+template <typename T> struct vec16any;
+template <> struct vec16any<double> { typedef double type __attribute__((ext_vector_type(2), aligned(8))); };
+template <> struct vec16any<float> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
+
 template <typename T> struct OpIdentity { __device__ T operator()(T u) const { return u; } };
 
 /* the NV uniforms of block b */
@@ -56,7 +68,6 @@ __device__ __forceinline__ void block_uniforms(uint64_t b, uint32_t k0, uint32_t
     for (int j = 0; j < 4; ++j) u[j] = open_u23(w.w[j]);
 }
 
-/* H: the per-element map (Op), or with GATHER the hybrid (HybridNQ64/32). */
 /* The first lane's value of x, as a wave-uniform (scalar) value. */
 __device__ __forceinline__ uint64_t gen_wave_uniform(uint64_t x)
 {
@@ -65,103 +76,89 @@ __device__ __forceinline__ uint64_t gen_wave_uniform(uint64_t x)
     return ((uint64_t)hi << 32) | lo;
 }
 
-template <typename T, int UNROLL, class H, bool GATHER, bool VECTOR>
+/* H: the per-element map (Op), or with GATHER the hybrid (HybridNQ64/32). */
+template <typename T, int UNROLL, class H, bool GATHER>
 __global__ __launch_bounds__(256) void k_generate(GenArgs<T> a)
 {
-    typedef typename vec16<T>::type V;
+    typedef typename vec16any<T>::type V;
     constexpr int NV = vec16<T>::n;
     constexpr int K = NV * UNROLL;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (VECTOR) {
-        const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-        __shared__ T outer_buf[GATHER ? 4 : 1][GATHER ? 64 * K : 1];
-        T* buf = outer_buf[GATHER ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0];
-        V* vout = reinterpret_cast<V*>(a.out + a.head);
-        const uint64_t block0 = (a.first + a.head) / NV;
-        /* wave-contiguous tiles of 64 UNROLL vectors, dealt out to the waves
-           in turn; whole waves iterate together, as the gather needs.  Whole
-           tiles store without bound tests; in the one partial last tile the
-           blocks past the end are drawn but not stored. */
-        constexpr uint64_t TILE = 64ull * UNROLL;
-        const uint64_t step = (uint64_t)gridDim.x * 4 * TILE;
-        auto tile = [&](uint64_t t, auto whole) {
-            const uint64_t i = t + lane;
-            T u[K], w[K];
+    const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    __shared__ T outer_buf[GATHER ? 4 : 1][GATHER ? 64 * K : 1];
+    T* buf = outer_buf[GATHER ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0];
+    V* vout = reinterpret_cast<V*>(a.out + a.head);
+    const uint64_t block0 = (a.first + a.head) / NV;
+    /* wave-contiguous tiles of 64 UNROLL vectors, dealt out to the waves
+       in turn; whole waves iterate together, as the gather needs.  Whole
+       tiles store without bound tests; in the one partial last tile the
+       blocks past the end are drawn but not stored. */
+    constexpr uint64_t TILE = 64ull * UNROLL;
+    const uint64_t step = (uint64_t)gridDim.x * 4 * TILE;
+    auto tile = [&](uint64_t t, auto whole) {
+        const uint64_t i = t + lane;
+        T u[K], w[K];
 #pragma unroll
-            for (int k = 0; k < UNROLL; ++k) {
-                T b[NV];
-                block_uniforms(block0 + i + 64 * k, a.k0, a.k1, b);
+        for (int k = 0; k < UNROLL; ++k) {
+            T b[NV];
+            block_uniforms(block0 + i + 64 * k, a.k0, a.k1, b);
 #pragma unroll
-                for (int j = 0; j < NV; ++j) u[NV * k + j] = b[j];
-            }
-            if constexpr (GATHER) {
-                hybrid_eval<T, K, H>(u, w, buf, lane);
-            } else {
-                H op;
-#pragma unroll
-                for (int k = 0; k < K; ++k) w[k] = op(u[k]);
-            }
-#pragma unroll
-            for (int k = 0; k < UNROLL; ++k) {
-                uint64_t idx = i + 64 * k;
-                V y;
-#pragma unroll
-                for (int j = 0; j < NV; ++j) y[j] = w[NV * k + j];
-                if (decltype(whole)::value || idx < a.nvec) __builtin_nontemporal_store(y, vout + idx);
-            }
-        };
-        uint64_t t = gen_wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
-        for (; t + TILE <= a.nvec; t += step) tile(t, std::true_type());
-        if (t < a.nvec) tile(t, std::false_type());
-        if (blockIdx.x == 0) {
-            uint64_t extra = a.head + (a.n - a.tail_begin);
-            for (uint64_t e = threadIdx.x; e < extra; e += blockDim.x) {
-                uint64_t idx = e < a.head ? e : a.tail_begin + (e - a.head);
-                T u = stream_uniform<T>(a.first + idx, a.k0, a.k1);
-                if constexpr (GATHER) a.out[idx] = H::whole(u);
-                else a.out[idx] = H()(u);
-            }
+            for (int j = 0; j < NV; ++j) u[NV * k + j] = b[j];
         }
-    } else {
-        for (uint64_t i = tid; i < a.n; i += stride) {
-            T u = stream_uniform<T>(a.first + i, a.k0, a.k1);
-            if constexpr (GATHER) a.out[i] = H::whole(u);
-            else a.out[i] = H()(u);
+        if constexpr (GATHER) {
+            hybrid_eval<T, K, H>(u, w, buf, lane);
+        } else {
+            H op;
+#pragma unroll
+            for (int k = 0; k < K; ++k) w[k] = op(u[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < UNROLL; ++k) {
+            uint64_t idx = i + 64 * k;
+            V y;
+#pragma unroll
+            for (int j = 0; j < NV; ++j) y[j] = w[NV * k + j];
+            if (decltype(whole)::value || idx < a.nvec) __builtin_nontemporal_store(y, vout + idx);
+        }
+    };
+    uint64_t t = gen_wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
+    for (; t + TILE <= a.nvec; t += step) tile(t, std::true_type());
+    if (t < a.nvec) tile(t, std::false_type());
+    if (blockIdx.x == 0) {
+        uint64_t extra = a.head + (a.n - a.tail_begin);
+        for (uint64_t e = threadIdx.x; e < extra; e += blockDim.x) {
+            uint64_t idx = e < a.head ? e : a.tail_begin + (e - a.head);
+            T u = stream_uniform<T>(a.first + idx, a.k0, a.k1);
+            if constexpr (GATHER) a.out[idx] = H::whole(u);
+            else a.out[idx] = H()(u);
         }
     }
+}
+
+/* The blocks of a generate launch (head, whole blocks, tail) and its grid. */
+template <typename T>
+static uint64_t gen_geometry(GenArgs<T>& a, const KernelShape& shape)
+{
+    constexpr int NV = vec16<T>::n;
+    a.head = (NV - a.first % NV) % NV;
+    if (a.head > a.n) a.head = a.n;
+    a.nvec = (a.n - a.head) / NV;
+    a.tail_begin = a.head + a.nvec * NV;
+    const uint64_t per_block = 256ull * shape.unroll;
+    const uint64_t blocks = (a.nvec + per_block - 1) / per_block;
+    return blocks > shape.max_blocks ? shape.max_blocks : blocks < 1 ? 1 : blocks;
 }
 
 template <typename T, class H, bool GATHER>
 static hipError_t launch_gen(GenArgs<T> a, hipStream_t s, const LaunchShape& shape_all)
 {
     const KernelShape shape = shape_all.generate[sizeof(T) == 8];
-    constexpr int NV = vec16<T>::n;
-    a.head = (NV - a.first % NV) % NV;
-    bool vector = a.head <= a.n && (a.n - a.head) >= (uint64_t)NV &&
-                  (reinterpret_cast<uintptr_t>(a.out + a.head) % 16) == 0;
-    if (vector) {
-        a.nvec = (a.n - a.head) / NV;
-        a.tail_begin = a.head + a.nvec * NV;
-        uint64_t per_block = 256ull * shape.unroll;
-        uint64_t blocks = (a.nvec + per_block - 1) / per_block;
-        if (blocks > shape.max_blocks) blocks = shape.max_blocks;
-        if (blocks < 1) blocks = 1;
-        if (shape.unroll == 4)
-            hipLaunchKernelGGL((k_generate<T, 4, H, GATHER, true>), dim3((unsigned)blocks), dim3(256), 0, s, a);
-        else if (shape.unroll == 1)
-            hipLaunchKernelGGL((k_generate<T, 1, H, GATHER, true>), dim3((unsigned)blocks), dim3(256), 0, s, a);
-        else
-            hipLaunchKernelGGL((k_generate<T, 2, H, GATHER, true>), dim3((unsigned)blocks), dim3(256), 0, s, a);
-    } else {
-        a.head = 0;
-        a.nvec = 0;
-        a.tail_begin = a.n;
-        uint64_t blocks = (a.n + 255) / 256;
-        if (blocks > shape.max_blocks) blocks = shape.max_blocks;
-        if (blocks < 1) blocks = 1;
-        hipLaunchKernelGGL((k_generate<T, 1, H, GATHER, false>), dim3((unsigned)blocks), dim3(256), 0, s, a);
-    }
+    const uint64_t blocks = gen_geometry(a, shape);
+    if (shape.unroll == 4)
+        hipLaunchKernelGGL((k_generate<T, 4, H, GATHER>), dim3((unsigned)blocks), dim3(256), 0, s, a);
+    else if (shape.unroll == 1)
+        hipLaunchKernelGGL((k_generate<T, 1, H, GATHER>), dim3((unsigned)blocks), dim3(256), 0, s, a);
+    else
+        hipLaunchKernelGGL((k_generate<T, 2, H, GATHER>), dim3((unsigned)blocks), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -205,78 +202,66 @@ StudentParams make_params(const TTableHeader& h, const TCells& c, const double* 
 /* Fused uniform -> normal -> Student t.  The quantile stage is the one of
    k_generate (H, gathered per wave with GATHER); each normal then goes
    through student_eval from the LDS table, as in k_student. */
-template <typename T, int UNROLL, class H, bool GATHER, bool VECTOR, int DEG>
+template <typename T, int UNROLL, class H, bool GATHER, int DEG>
 __global__ __launch_bounds__(256) void k_generate_t(GenArgs<T> a, const double* __restrict__ coef, StudentParams P)
 {
     extern __shared__ __attribute__((aligned(16))) double lds_gt[];
     stage_table(lds_gt, coef, P);
     __syncthreads();
-    typedef typename vec16<T>::type V;
+    typedef typename vec16any<T>::type V;
     constexpr int NV = vec16<T>::n;
     constexpr int K = NV * UNROLL;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     auto tmap = [&](T z) { return (T)student_eval<DEG>((double)z, lds_gt, P); };
-    if (VECTOR) {
-        const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-        __shared__ T outer_buf[GATHER ? 4 : 1][GATHER ? 64 * K : 1];
-        T* buf = outer_buf[GATHER ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0];
-        V* vout = reinterpret_cast<V*>(a.out + a.head);
-        const uint64_t block0 = (a.first + a.head) / NV;
-        /* wave-contiguous tiles of 64 UNROLL vectors, as k_generate: whole
-           tiles store without bound tests, the one partial last tile draws
-           its blocks past the end but does not store them */
-        constexpr uint64_t TILE = 64ull * UNROLL;
-        const uint64_t step = (uint64_t)gridDim.x * 4 * TILE;
-        auto tile = [&](uint64_t t, auto whole) {
-            const uint64_t i = t + lane;
-            T u[K], w[K];
+    const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    __shared__ T outer_buf[GATHER ? 4 : 1][GATHER ? 64 * K : 1];
+    T* buf = outer_buf[GATHER ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0];
+    V* vout = reinterpret_cast<V*>(a.out + a.head);
+    const uint64_t block0 = (a.first + a.head) / NV;
+    /* wave-contiguous tiles of 64 UNROLL vectors, as k_generate: whole
+       tiles store without bound tests, the one partial last tile draws
+       its blocks past the end but does not store them */
+    constexpr uint64_t TILE = 64ull * UNROLL;
+    const uint64_t step = (uint64_t)gridDim.x * 4 * TILE;
+    auto tile = [&](uint64_t t, auto whole) {
+        const uint64_t i = t + lane;
+        T u[K], w[K];
 #pragma unroll
-            for (int k = 0; k < UNROLL; ++k) {
-                T b[NV];
-                block_uniforms(block0 + i + 64 * k, a.k0, a.k1, b);
+        for (int k = 0; k < UNROLL; ++k) {
+            T b[NV];
+            block_uniforms(block0 + i + 64 * k, a.k0, a.k1, b);
 #pragma unroll
-                for (int j = 0; j < NV; ++j) u[NV * k + j] = b[j];
-            }
-            if constexpr (GATHER) {
-                hybrid_eval<T, K, H>(u, w, buf, lane);
-            } else {
-                H op;
-#pragma unroll
-                for (int k = 0; k < K; ++k) w[k] = op(u[k]);
-            }
-#pragma unroll
-            for (int k = 0; k < K; ++k) w[k] = tmap(w[k]);
-#pragma unroll
-            for (int k = 0; k < UNROLL; ++k) {
-                uint64_t idx = i + 64 * k;
-                V y;
-#pragma unroll
-                for (int j = 0; j < NV; ++j) y[j] = w[NV * k + j];
-                if (decltype(whole)::value || idx < a.nvec) __builtin_nontemporal_store(y, vout + idx);
-            }
-        };
-        uint64_t t = gen_wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
-        for (; t + TILE <= a.nvec; t += step) tile(t, std::true_type());
-        if (t < a.nvec) tile(t, std::false_type());
-        if (blockIdx.x == 0) {
-            uint64_t extra = a.head + (a.n - a.tail_begin);
-            for (uint64_t e = threadIdx.x; e < extra; e += blockDim.x) {
-                uint64_t idx = e < a.head ? e : a.tail_begin + (e - a.head);
-                T u = stream_uniform<T>(a.first + idx, a.k0, a.k1);
-                T z;
-                if constexpr (GATHER) z = H::whole(u);
-                else z = H()(u);
-                a.out[idx] = tmap(z);
-            }
+            for (int j = 0; j < NV; ++j) u[NV * k + j] = b[j];
         }
-    } else {
-        for (uint64_t i = tid; i < a.n; i += stride) {
-            T u = stream_uniform<T>(a.first + i, a.k0, a.k1);
+        if constexpr (GATHER) {
+            hybrid_eval<T, K, H>(u, w, buf, lane);
+        } else {
+            H op;
+#pragma unroll
+            for (int k = 0; k < K; ++k) w[k] = op(u[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) w[k] = tmap(w[k]);
+#pragma unroll
+        for (int k = 0; k < UNROLL; ++k) {
+            uint64_t idx = i + 64 * k;
+            V y;
+#pragma unroll
+            for (int j = 0; j < NV; ++j) y[j] = w[NV * k + j];
+            if (decltype(whole)::value || idx < a.nvec) __builtin_nontemporal_store(y, vout + idx);
+        }
+    };
+    uint64_t t = gen_wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
+    for (; t + TILE <= a.nvec; t += step) tile(t, std::true_type());
+    if (t < a.nvec) tile(t, std::false_type());
+    if (blockIdx.x == 0) {
+        uint64_t extra = a.head + (a.n - a.tail_begin);
+        for (uint64_t e = threadIdx.x; e < extra; e += blockDim.x) {
+            uint64_t idx = e < a.head ? e : a.tail_begin + (e - a.head);
+            T u = stream_uniform<T>(a.first + idx, a.k0, a.k1);
             T z;
             if constexpr (GATHER) z = H::whole(u);
             else z = H()(u);
-            a.out[i] = tmap(z);
+            a.out[idx] = tmap(z);
         }
     }
 }
@@ -315,121 +300,85 @@ static void hyp_base_constants(const HypTableHeader& h, HypBase* B)
 /* Fused uniform -> base sample -> hyperbolic: all K elements of a lane
    through the LDS cells, then one wave vote for the far ones (as
    k_hyperbolic). */
-template <typename T, int UNROLL, bool VECTOR, int DEG>
+template <typename T, int UNROLL, int DEG>
 __global__ __launch_bounds__(256) void k_generate_h(GenArgs<T> a, HypParams P, HypBase B)
 {
     extern __shared__ __attribute__((aligned(16))) double lds_gh[];
     stage_hyp<DEG>(lds_gh, P);
     __syncthreads();
-    typedef typename vec16<T>::type V;
+    typedef typename vec16any<T>::type V;
     constexpr int NV = vec16<T>::n;
     constexpr int K = NV * UNROLL;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     auto one = [&](T u) {
         const double v = B((double)u);
         return (T)(P.mu + __builtin_copysign(hyp_abs_q<DEG>(v, lds_gh, P), v));
     };
-    if (VECTOR) {
-        V* vout = reinterpret_cast<V*>(a.out + a.head);
-        const uint64_t block0 = (a.first + a.head) / NV;
-        const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-        /* wave-contiguous tiles, as k_generate (whole tiles unchecked, the
-           partial last one checked) */
-        constexpr uint64_t TILE = 64ull * UNROLL;
-        const uint64_t step = (uint64_t)gridDim.x * 4 * TILE;
-        auto tile = [&](uint64_t t, auto whole) {
-            const uint64_t i = t + lane;
-            double v[K], q[K];
-            bool far[K];
-            bool anyfar = false;
+    V* vout = reinterpret_cast<V*>(a.out + a.head);
+    const uint64_t block0 = (a.first + a.head) / NV;
+    const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    /* wave-contiguous tiles, as k_generate (whole tiles unchecked, the
+       partial last one checked) */
+    constexpr uint64_t TILE = 64ull * UNROLL;
+    const uint64_t step = (uint64_t)gridDim.x * 4 * TILE;
+    auto tile = [&](uint64_t t, auto whole) {
+        const uint64_t i = t + lane;
+        double v[K], q[K];
+        bool far[K];
+        bool anyfar = false;
 #pragma unroll
-            for (int k = 0; k < UNROLL; ++k) {
-                T b[NV];
-                /* blocks past the end are drawn but never stored */
-                block_uniforms(block0 + i + 64 * k, a.k0, a.k1, b);
+        for (int k = 0; k < UNROLL; ++k) {
+            T b[NV];
+            /* blocks past the end are drawn but never stored */
+            block_uniforms(block0 + i + 64 * k, a.k0, a.k1, b);
 #pragma unroll
-                for (int j = 0; j < NV; ++j) v[NV * k + j] = B((double)b[j]);
-            }
+            for (int j = 0; j < NV; ++j) v[NV * k + j] = B((double)b[j]);
+        }
+#pragma unroll
+        for (int e = 0; e < K; ++e) {
+            q[e] = hyp_near<DEG>(v[e], lds_gh, P, &far[e]);
+            anyfar |= far[e];
+        }
+        if (wave_any(anyfar)) {
 #pragma unroll
             for (int e = 0; e < K; ++e) {
-                q[e] = hyp_near<DEG>(v[e], lds_gh, P, &far[e]);
-                anyfar |= far[e];
-            }
-            if (wave_any(anyfar)) {
-#pragma unroll
-                for (int e = 0; e < K; ++e) {
-                    if (wave_any(far[e])) {
-                        double qf = hyp_far_of<DEG>(far[e] ? v[e] : 0.0, P);
-                        q[e] = far[e] ? qf : q[e];
-                    }
+                if (wave_any(far[e])) {
+                    double qf = hyp_far_of<DEG>(far[e] ? v[e] : 0.0, P);
+                    q[e] = far[e] ? qf : q[e];
                 }
             }
-#pragma unroll
-            for (int k = 0; k < UNROLL; ++k) {
-                uint64_t idx = i + 64 * k;
-                V y;
-#pragma unroll
-                for (int j = 0; j < NV; ++j) y[j] = (T)(P.mu + __builtin_copysign(q[NV * k + j], v[NV * k + j]));
-                if (decltype(whole)::value || idx < a.nvec) __builtin_nontemporal_store(y, vout + idx);
-            }
-        };
-        uint64_t t = gen_wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
-        for (; t + TILE <= a.nvec; t += step) tile(t, std::true_type());
-        if (t < a.nvec) tile(t, std::false_type());
-        if (blockIdx.x == 0) {
-            uint64_t extra = a.head + (a.n - a.tail_begin);
-            for (uint64_t e = threadIdx.x; e < extra; e += blockDim.x) {
-                uint64_t idx = e < a.head ? e : a.tail_begin + (e - a.head);
-                a.out[idx] = one(stream_uniform<T>(a.first + idx, a.k0, a.k1));
-            }
         }
-    } else {
-        for (uint64_t i = tid; i < a.n; i += stride) a.out[i] = one(stream_uniform<T>(a.first + i, a.k0, a.k1));
+#pragma unroll
+        for (int k = 0; k < UNROLL; ++k) {
+            uint64_t idx = i + 64 * k;
+            V y;
+#pragma unroll
+            for (int j = 0; j < NV; ++j) y[j] = (T)(P.mu + __builtin_copysign(q[NV * k + j], v[NV * k + j]));
+            if (decltype(whole)::value || idx < a.nvec) __builtin_nontemporal_store(y, vout + idx);
+        }
+    };
+    uint64_t t = gen_wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
+    for (; t + TILE <= a.nvec; t += step) tile(t, std::true_type());
+    if (t < a.nvec) tile(t, std::false_type());
+    if (blockIdx.x == 0) {
+        uint64_t extra = a.head + (a.n - a.tail_begin);
+        for (uint64_t e = threadIdx.x; e < extra; e += blockDim.x) {
+            uint64_t idx = e < a.head ? e : a.tail_begin + (e - a.head);
+            a.out[idx] = one(stream_uniform<T>(a.first + idx, a.k0, a.k1));
+        }
     }
-}
-
-/* Vector geometry of a generate launch (head, whole blocks, tail) and its
-   grid; false if the output takes the element-by-element path. */
-template <typename T>
-static bool gen_geometry(GenArgs<T>& a, const KernelShape& shape, uint64_t* blocks)
-{
-    constexpr int NV = vec16<T>::n;
-    a.head = (NV - a.first % NV) % NV;
-    bool vector = a.head <= a.n && (a.n - a.head) >= (uint64_t)NV &&
-                  (reinterpret_cast<uintptr_t>(a.out + a.head) % 16) == 0;
-    uint64_t b;
-    if (vector) {
-        a.nvec = (a.n - a.head) / NV;
-        a.tail_begin = a.head + a.nvec * NV;
-        uint64_t per_block = 256ull * shape.unroll;
-        b = (a.nvec + per_block - 1) / per_block;
-    } else {
-        a.head = 0;
-        a.nvec = 0;
-        a.tail_begin = a.n;
-        b = (a.n + 255) / 256;
-    }
-    if (b > shape.max_blocks) b = shape.max_blocks;
-    *blocks = b < 1 ? 1 : b;
-    return vector;
 }
 
 template <typename T, class H, bool GATHER, int DEG>
 static hipError_t launch_gen_t(GenArgs<T> a, const double* coef, const StudentParams& P, size_t lds, hipStream_t s,
                                const KernelShape& shape)
 {
-    uint64_t blocks;
-    if (gen_geometry(a, shape, &blocks)) {
-        if (shape.unroll == 4)
-            hipLaunchKernelGGL((k_generate_t<T, 4, H, GATHER, true, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, coef, P);
-        else if (shape.unroll == 1)
-            hipLaunchKernelGGL((k_generate_t<T, 1, H, GATHER, true, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, coef, P);
-        else
-            hipLaunchKernelGGL((k_generate_t<T, 2, H, GATHER, true, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, coef, P);
-    } else {
-        hipLaunchKernelGGL((k_generate_t<T, 1, H, GATHER, false, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, coef, P);
-    }
+    const uint64_t blocks = gen_geometry(a, shape);
+    if (shape.unroll == 4)
+        hipLaunchKernelGGL((k_generate_t<T, 4, H, GATHER, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, coef, P);
+    else if (shape.unroll == 1)
+        hipLaunchKernelGGL((k_generate_t<T, 1, H, GATHER, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, coef, P);
+    else
+        hipLaunchKernelGGL((k_generate_t<T, 2, H, GATHER, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, coef, P);
     return hipGetLastError();
 }
 
@@ -487,17 +436,13 @@ template <typename T, int DEG>
 static hipError_t launch_gen_h(GenArgs<T> a, const HypParams& P, const HypBase& B, size_t lds, hipStream_t s,
                                const KernelShape& shape)
 {
-    uint64_t blocks;
-    if (gen_geometry(a, shape, &blocks)) {
-        if (shape.unroll == 4)
-            hipLaunchKernelGGL((k_generate_h<T, 4, true, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, P, B);
-        else if (shape.unroll == 1)
-            hipLaunchKernelGGL((k_generate_h<T, 1, true, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, P, B);
-        else
-            hipLaunchKernelGGL((k_generate_h<T, 2, true, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, P, B);
-    } else {
-        hipLaunchKernelGGL((k_generate_h<T, 1, false, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, P, B);
-    }
+    const uint64_t blocks = gen_geometry(a, shape);
+    if (shape.unroll == 4)
+        hipLaunchKernelGGL((k_generate_h<T, 4, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, P, B);
+    else if (shape.unroll == 1)
+        hipLaunchKernelGGL((k_generate_h<T, 1, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, P, B);
+    else
+        hipLaunchKernelGGL((k_generate_h<T, 2, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, P, B);
     return hipGetLastError();
 }
 

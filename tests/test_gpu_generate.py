@@ -252,3 +252,23 @@ def test_fused_vg(ctx, p):
             assert_close(got[idx], want, RTOL_F64, "fused vg %r" % (p,))
         else:
             assert_close(got[idx], as_f32_output(want), RTOL_F32, "fused vg f32 %r" % (p,))
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("first", [1, 2, 3])
+@pytest.mark.parametrize("n", [2, 63, 511, 514, 1 << 12, (1 << 14) + 5])
+def test_fused_chains_at_any_block_offset_and_alignment(ctx, dtype, first, n):
+    """Ranges that start inside a Philox block, written at every offset from a
+    16-byte boundary, around the sizes of a wave's tile: bitwise the same
+    elements of an aligned run from the stream's start, and nothing outside."""
+    runs = (lambda f, out: qm.qm_generate_student_t(ctx, 21, 6, f, out, 4.0),
+            lambda f, out: qm.qm_generate_hyperbolic(ctx, 21, 6, f, out, 1.0, 0.5, 1.0, mu=0.25))
+    for run in runs:
+        whole = torch.empty(first + n, dtype=dtype, device="cuda")
+        run(0, whole)
+        for offset in range(16 // whole.element_size()):
+            t = torch.zeros(n + offset + 1, dtype=dtype, device="cuda")
+            run(first, t[offset:offset + n])
+            torch.cuda.synchronize()
+            assert torch.equal(t[offset:offset + n], whole[first:]), (first, offset, n)
+            assert torch.all(t[:offset] == 0) and t[offset + n] == 0
