@@ -276,6 +276,7 @@ qm_status qm_init(int hip_device, uint64_t hbm_budget_bytes, qm_ctx** out)
     c->device = hip_device;
     c->budget = hbm_budget_bytes;
     c->cus = cus > 0 ? cus : 256;
+    c->shape.cus = c->cus;
     /* launch shapes per kernel family (workgroups of 256 per CU x vectors
        per lane), the best of measured sweeps over 1..64 x 1..4 on MI355X;
        QM_BLOCKS_PER_CU / QM_UNROLL override every family (tuning) */
@@ -295,6 +296,10 @@ qm_status qm_init(int hip_device, uint64_t hbm_budget_bytes, qm_ctx** out)
         /* fused generation (grid-stride), FP32 and FP64 outputs */
         {&c->shape.generate[0], "QM_SHAPE_GEN32", 32, 2},
         {&c->shape.generate[1], "QM_SHAPE_GEN64", 64, 4},
+        {&c->shape.generate_t[0], "QM_SHAPE_GT32", 32, 2},
+        {&c->shape.generate_t[1], "QM_SHAPE_GT64", 64, 4},
+        {&c->shape.generate_h[0], "QM_SHAPE_GH32", 16, 2},
+        {&c->shape.generate_h[1], "QM_SHAPE_GH64", 16, 4},
         {&c->shape.student[0], "QM_SHAPE_T32", 3, 4},  /* Student t, FP32 outputs */
         {&c->shape.student[1], "QM_SHAPE_T64", 2, 4},  /* Student t, FP64 outputs */
         /* exp -> hyperbolic, FP32, wave-contiguous tiles: 16 x 2 (670 Gs/s on

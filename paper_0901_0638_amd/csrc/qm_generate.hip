@@ -32,6 +32,7 @@
 #include "qm_hyp_device.hpp"
 #include "qm_internal.h"
 #include "qm_philox.hpp"
+#include "qm_stream.hpp"
 #include "qm_student_device.hpp"
 
 namespace qm {
@@ -47,13 +48,6 @@ struct GenArgs {
     uint64_t n;
 };
 
-/* One block's outputs, 16 bytes at the alignment of an element. */
-template <typename T> struct vec16any;
-template <> struct vec16any<double> { typedef double type __attribute__((ext_vector_type(2), aligned(8))); };
-template <> struct vec16any<float> { typedef float type __attribute__((ext_vector_type(4), aligned(4))); };
-
-template <typename T> struct OpIdentity { __device__ T operator()(T u) const { return u; } };
-
 /* the NV uniforms of block b */
 __device__ __forceinline__ void block_uniforms(uint64_t b, uint32_t k0, uint32_t k1, double (&u)[2])
 {
@@ -68,14 +62,6 @@ __device__ __forceinline__ void block_uniforms(uint64_t b, uint32_t k0, uint32_t
     for (int j = 0; j < 4; ++j) u[j] = open_u23(w.w[j]);
 }
 
-/* The first lane's value of x, as a wave-uniform (scalar) value. */
-__device__ __forceinline__ uint64_t gen_wave_uniform(uint64_t x)
-{
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
-
 /* H: the per-element map (Op), or with GATHER the hybrid (HybridNQ64/32). */
 template <typename T, int UNROLL, class H, bool GATHER>
 __global__ __launch_bounds__(256) void k_generate(GenArgs<T> a)
@@ -83,7 +69,7 @@ __global__ __launch_bounds__(256) void k_generate(GenArgs<T> a)
     typedef typename vec16any<T>::type V;
     constexpr int NV = vec16<T>::n;
     constexpr int K = NV * UNROLL;
-    const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const uint32_t lane = wave_lane();
     __shared__ T outer_buf[GATHER ? 4 : 1][GATHER ? 64 * K : 1];
     T* buf = outer_buf[GATHER ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0];
     V* vout = reinterpret_cast<V*>(a.out + a.head);
@@ -120,7 +106,7 @@ __global__ __launch_bounds__(256) void k_generate(GenArgs<T> a)
             if (decltype(whole)::value || idx < a.nvec) __builtin_nontemporal_store(y, vout + idx);
         }
     };
-    uint64_t t = gen_wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
+    uint64_t t = wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
     for (; t + TILE <= a.nvec; t += step) tile(t, std::true_type());
     if (t < a.nvec) tile(t, std::false_type());
     if (blockIdx.x == 0) {
@@ -134,31 +120,27 @@ __global__ __launch_bounds__(256) void k_generate(GenArgs<T> a)
     }
 }
 
-/* The blocks of a generate launch (head, whole blocks, tail) and its grid. */
+/* The blocks of a generate launch: head, whole blocks, tail. */
 template <typename T>
-static uint64_t gen_geometry(GenArgs<T>& a, const KernelShape& shape)
+static void gen_geometry(GenArgs<T>& a)
 {
     constexpr int NV = vec16<T>::n;
     a.head = (NV - a.first % NV) % NV;
     if (a.head > a.n) a.head = a.n;
     a.nvec = (a.n - a.head) / NV;
     a.tail_begin = a.head + a.nvec * NV;
-    const uint64_t per_block = 256ull * shape.unroll;
-    const uint64_t blocks = (a.nvec + per_block - 1) / per_block;
-    return blocks > shape.max_blocks ? shape.max_blocks : blocks < 1 ? 1 : blocks;
 }
 
 template <typename T, class H, bool GATHER>
-static hipError_t launch_gen(GenArgs<T> a, hipStream_t s, const LaunchShape& shape_all)
+static hipError_t launch_gen(GenArgs<T> a, hipStream_t s, const LaunchShape& shape)
 {
-    const KernelShape shape = shape_all.generate[sizeof(T) == 8];
-    const uint64_t blocks = gen_geometry(a, shape);
-    if (shape.unroll == 4)
-        hipLaunchKernelGGL((k_generate<T, 4, H, GATHER>), dim3((unsigned)blocks), dim3(256), 0, s, a);
-    else if (shape.unroll == 1)
-        hipLaunchKernelGGL((k_generate<T, 1, H, GATHER>), dim3((unsigned)blocks), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL((k_generate<T, 2, H, GATHER>), dim3((unsigned)blocks), dim3(256), 0, s, a);
+    const KernelShape ks = shape.generate[sizeof(T) == 8];
+    gen_geometry(a);
+    const int u = launch_unroll(a.nvec, ks, shape.cus);
+    with_unroll(u, [&](auto U) {
+        hipLaunchKernelGGL((k_generate<T, decltype(U)::value, H, GATHER>), dim3(launch_blocks(a.nvec, u, ks)), dim3(256),
+                           0, s, a);
+    });
     return hipGetLastError();
 }
 
@@ -172,7 +154,7 @@ hipError_t launch_generate(int kind, int dtype, int mode, uint32_t seed, uint32_
         a.k1 = stream;
         a.first = first;
         a.n = n;
-        if (kind == QM_UNIFORM && mode == QM_PLAIN) return launch_gen<double, OpIdentity<double>, false>(a, s, shape);
+        if (kind == QM_UNIFORM && mode == QM_PLAIN) return launch_gen<double, OpCopy<double>, false>(a, s, shape);
         if (kind == QM_NORMAL_QUANTILE && mode == QM_PLAIN) {
             if (shape.compact) return launch_gen<double, HybridNQ64, true>(a, s, shape);
             return launch_gen<double, OpNQ64Plain, false>(a, s, shape);
@@ -185,7 +167,7 @@ hipError_t launch_generate(int kind, int dtype, int mode, uint32_t seed, uint32_
         a.k1 = stream;
         a.first = first;
         a.n = n;
-        if (kind == QM_UNIFORM && mode == QM_PLAIN) return launch_gen<float, OpIdentity<float>, false>(a, s, shape);
+        if (kind == QM_UNIFORM && mode == QM_PLAIN) return launch_gen<float, OpCopy<float>, false>(a, s, shape);
         if (kind == QM_NORMAL_QUANTILE && mode == QM_F32_REFINE) {
             if (shape.compact) return launch_gen<float, HybridNQ32, true>(a, s, shape);
             return launch_gen<float, OpNQ32Refine, false>(a, s, shape);
@@ -203,16 +185,16 @@ StudentParams make_params(const TTableHeader& h, const TCells& c, const double* 
    k_generate (H, gathered per wave with GATHER); each normal then goes
    through student_eval from the LDS table, as in k_student. */
 template <typename T, int UNROLL, class H, bool GATHER, int DEG>
-__global__ __launch_bounds__(256) void k_generate_t(GenArgs<T> a, const double* __restrict__ coef, StudentParams P)
+__global__ __launch_bounds__(256) void k_generate_t(GenArgs<T> a, StudentParams P)
 {
     extern __shared__ __attribute__((aligned(16))) double lds_gt[];
-    stage_table(lds_gt, coef, P);
+    stage_table(lds_gt, P.gcoef, P);
     __syncthreads();
     typedef typename vec16any<T>::type V;
     constexpr int NV = vec16<T>::n;
     constexpr int K = NV * UNROLL;
-    auto tmap = [&](T z) { return (T)student_eval<DEG>((double)z, lds_gt, P); };
-    const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const StudentMap<T, DEG> tmap = {lds_gt, P};
+    const uint32_t lane = wave_lane();
     __shared__ T outer_buf[GATHER ? 4 : 1][GATHER ? 64 * K : 1];
     T* buf = outer_buf[GATHER ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0];
     V* vout = reinterpret_cast<V*>(a.out + a.head);
@@ -239,18 +221,17 @@ __global__ __launch_bounds__(256) void k_generate_t(GenArgs<T> a, const double* 
 #pragma unroll
             for (int k = 0; k < K; ++k) w[k] = op(u[k]);
         }
-#pragma unroll
-        for (int k = 0; k < K; ++k) w[k] = tmap(w[k]);
+        tmap.tile(w, u);
 #pragma unroll
         for (int k = 0; k < UNROLL; ++k) {
             uint64_t idx = i + 64 * k;
             V y;
 #pragma unroll
-            for (int j = 0; j < NV; ++j) y[j] = w[NV * k + j];
+            for (int j = 0; j < NV; ++j) y[j] = u[NV * k + j];
             if (decltype(whole)::value || idx < a.nvec) __builtin_nontemporal_store(y, vout + idx);
         }
     };
-    uint64_t t = gen_wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
+    uint64_t t = wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
     for (; t + TILE <= a.nvec; t += step) tile(t, std::true_type());
     if (t < a.nvec) tile(t, std::false_type());
     if (blockIdx.x == 0) {
@@ -261,7 +242,7 @@ __global__ __launch_bounds__(256) void k_generate_t(GenArgs<T> a, const double* 
             T z;
             if constexpr (GATHER) z = H::whole(u);
             else z = H()(u);
-            a.out[idx] = tmap(z);
+            a.out[idx] = tmap.one(z);
         }
     }
 }
@@ -310,12 +291,14 @@ __global__ __launch_bounds__(256) void k_generate_h(GenArgs<T> a, HypParams P, H
     constexpr int NV = vec16<T>::n;
     constexpr int K = NV * UNROLL;
     auto one = [&](T u) {
-        const double v = B((double)u);
-        return (T)(P.mu + __builtin_copysign(hyp_abs_q<DEG>(v, lds_gh, P), v));
+        const double v[1] = {B((double)u)};
+        double q[1];
+        hyp_abs_q<DEG, 1>(v, q, lds_gh, P);
+        return (T)(P.mu + __builtin_copysign(q[0], v[0]));
     };
     V* vout = reinterpret_cast<V*>(a.out + a.head);
     const uint64_t block0 = (a.first + a.head) / NV;
-    const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const uint32_t lane = wave_lane();
     /* wave-contiguous tiles, as k_generate (whole tiles unchecked, the
        partial last one checked) */
     constexpr uint64_t TILE = 64ull * UNROLL;
@@ -323,8 +306,6 @@ __global__ __launch_bounds__(256) void k_generate_h(GenArgs<T> a, HypParams P, H
     auto tile = [&](uint64_t t, auto whole) {
         const uint64_t i = t + lane;
         double v[K], q[K];
-        bool far[K];
-        bool anyfar = false;
 #pragma unroll
         for (int k = 0; k < UNROLL; ++k) {
             T b[NV];
@@ -333,20 +314,7 @@ __global__ __launch_bounds__(256) void k_generate_h(GenArgs<T> a, HypParams P, H
 #pragma unroll
             for (int j = 0; j < NV; ++j) v[NV * k + j] = B((double)b[j]);
         }
-#pragma unroll
-        for (int e = 0; e < K; ++e) {
-            q[e] = hyp_near<DEG>(v[e], lds_gh, P, &far[e]);
-            anyfar |= far[e];
-        }
-        if (wave_any(anyfar)) {
-#pragma unroll
-            for (int e = 0; e < K; ++e) {
-                if (wave_any(far[e])) {
-                    double qf = hyp_far_of<DEG>(far[e] ? v[e] : 0.0, P);
-                    q[e] = far[e] ? qf : q[e];
-                }
-            }
-        }
+        hyp_abs_q<DEG, K>(v, q, lds_gh, P);
 #pragma unroll
         for (int k = 0; k < UNROLL; ++k) {
             uint64_t idx = i + 64 * k;
@@ -356,7 +324,7 @@ __global__ __launch_bounds__(256) void k_generate_h(GenArgs<T> a, HypParams P, H
             if (decltype(whole)::value || idx < a.nvec) __builtin_nontemporal_store(y, vout + idx);
         }
     };
-    uint64_t t = gen_wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
+    uint64_t t = wave_uniform(((uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TILE);
     for (; t + TILE <= a.nvec; t += step) tile(t, std::true_type());
     if (t < a.nvec) tile(t, std::false_type());
     if (blockIdx.x == 0) {
@@ -369,16 +337,13 @@ __global__ __launch_bounds__(256) void k_generate_h(GenArgs<T> a, HypParams P, H
 }
 
 template <typename T, class H, bool GATHER, int DEG>
-static hipError_t launch_gen_t(GenArgs<T> a, const double* coef, const StudentParams& P, size_t lds, hipStream_t s,
-                               const KernelShape& shape)
+static hipError_t launch_gen_t(GenArgs<T> a, const StudentParams& P, size_t lds, hipStream_t s, const KernelShape& ks,
+                               int u)
 {
-    const uint64_t blocks = gen_geometry(a, shape);
-    if (shape.unroll == 4)
-        hipLaunchKernelGGL((k_generate_t<T, 4, H, GATHER, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, coef, P);
-    else if (shape.unroll == 1)
-        hipLaunchKernelGGL((k_generate_t<T, 1, H, GATHER, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, coef, P);
-    else
-        hipLaunchKernelGGL((k_generate_t<T, 2, H, GATHER, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, coef, P);
+    with_unroll(u, [&](auto U) {
+        hipLaunchKernelGGL((k_generate_t<T, decltype(U)::value, H, GATHER, DEG>), dim3(launch_blocks(a.nvec, u, ks)),
+                           dim3(256), lds, s, a, P);
+    });
     return hipGetLastError();
 }
 
@@ -399,50 +364,48 @@ hipError_t launch_generate_student(int dtype, int mode, uint32_t seed, uint32_t 
     const bool f64 = dtype == QM_F64 && mode == QM_PLAIN;
     if (!f64 && !(dtype == QM_F32 && mode == QM_F32_REFINE)) return hipErrorInvalidValue;
     const TCells& c = f64 ? h.f64 : h.f32;
-    const double* coef = table_block(d_table) + c.coef_offset;
-    const StudentParams P = make_params(h, c, coef);
+    const StudentParams P = make_params(h, c, table_block(d_table) + c.coef_offset);
     const size_t lds = (size_t)c.nlds * P.lds_stride * sizeof(double);
-    const KernelShape ks = shape.generate[f64];
-    /* the quantile stage gathers per wave when its buffer fits beside the
-       table (bitwise the same results either way) */
-    const bool gather = shape.compact &&
-                        lds + (f64 ? gather_bytes<double>(ks.unroll) : gather_bytes<float>(ks.unroll)) <= GEN_LDS_MAX;
+    const KernelShape ks = shape.generate_t[f64];
     if (lds > GEN_LDS_MAX) return hipErrorInvalidValue;
-    if (f64) {
-        GenArgs<double> a{};
-        a.out = static_cast<double*>(out);
+    auto launch = [&](auto a) {
+        typedef typename std::remove_pointer<decltype(a.out)>::type T;
+        a.out = static_cast<T*>(out);
         a.k0 = seed;
         a.k1 = stream;
         a.first = first;
         a.n = n;
-        if (c.degree == T_DEGREE_LOW) {
-            if (gather) return launch_gen_t<double, HybridNQ64, true, T_DEGREE_LOW>(a, coef, P, lds, s, ks);
-            return launch_gen_t<double, OpNQ64Plain, false, T_DEGREE_LOW>(a, coef, P, lds, s, ks);
+        gen_geometry(a);
+        const int u = launch_unroll(a.nvec, ks, shape.cus);
+        /* the quantile stage gathers per wave when its buffer fits beside the
+           table (bitwise the same results either way) */
+        const bool gather = shape.compact && lds + gather_bytes<T>(u) <= GEN_LDS_MAX;
+        if constexpr (std::is_same<T, double>::value) {
+            if (c.degree == T_DEGREE_LOW) {
+                if (gather) return launch_gen_t<T, HybridNQ64, true, T_DEGREE_LOW>(a, P, lds, s, ks, u);
+                return launch_gen_t<T, OpNQ64Plain, false, T_DEGREE_LOW>(a, P, lds, s, ks, u);
+            }
+            if (gather) return launch_gen_t<T, HybridNQ64, true, T_DEGREE_HIGH>(a, P, lds, s, ks, u);
+            return launch_gen_t<T, OpNQ64Plain, false, T_DEGREE_HIGH>(a, P, lds, s, ks, u);
+        } else {
+            if (gather) return launch_gen_t<T, HybridNQ32, true, T_DEGREE_F32>(a, P, lds, s, ks, u);
+            return launch_gen_t<T, OpNQ32Refine, false, T_DEGREE_F32>(a, P, lds, s, ks, u);
         }
-        if (gather) return launch_gen_t<double, HybridNQ64, true, T_DEGREE_HIGH>(a, coef, P, lds, s, ks);
-        return launch_gen_t<double, OpNQ64Plain, false, T_DEGREE_HIGH>(a, coef, P, lds, s, ks);
-    }
-    GenArgs<float> a{};
-    a.out = static_cast<float*>(out);
-    a.k0 = seed;
-    a.k1 = stream;
-    a.first = first;
-    a.n = n;
-    if (gather) return launch_gen_t<float, HybridNQ32, true, T_DEGREE_F32>(a, coef, P, lds, s, ks);
-    return launch_gen_t<float, OpNQ32Refine, false, T_DEGREE_F32>(a, coef, P, lds, s, ks);
+    };
+    return f64 ? launch(GenArgs<double>{}) : launch(GenArgs<float>{});
 }
 
 template <typename T, int DEG>
 static hipError_t launch_gen_h(GenArgs<T> a, const HypParams& P, const HypBase& B, size_t lds, hipStream_t s,
-                               const KernelShape& shape)
+                               const LaunchShape& shape)
 {
-    const uint64_t blocks = gen_geometry(a, shape);
-    if (shape.unroll == 4)
-        hipLaunchKernelGGL((k_generate_h<T, 4, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, P, B);
-    else if (shape.unroll == 1)
-        hipLaunchKernelGGL((k_generate_h<T, 1, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, P, B);
-    else
-        hipLaunchKernelGGL((k_generate_h<T, 2, DEG>), dim3((unsigned)blocks), dim3(256), lds, s, a, P, B);
+    const KernelShape ks = shape.generate_h[sizeof(T) == 8];
+    gen_geometry(a);
+    const int u = launch_unroll(a.nvec, ks, shape.cus);
+    with_unroll(u, [&](auto U) {
+        hipLaunchKernelGGL((k_generate_h<T, decltype(U)::value, DEG>), dim3(launch_blocks(a.nvec, u, ks)), dim3(256), lds,
+                           s, a, P, B);
+    });
     return hipGetLastError();
 }
 
@@ -464,7 +427,7 @@ hipError_t launch_generate_hyperbolic(int dtype, int mode, uint32_t seed, uint32
         a.k1 = stream;
         a.first = first;
         a.n = n;
-        return launch_gen_h<float, HYP_DEGREE_F32>(a, P, B, lds, s, shape.hyperbolic[0]);
+        return launch_gen_h<float, HYP_DEGREE_F32>(a, P, B, lds, s, shape);
     }
     GenArgs<double> a{};
     a.out = static_cast<double*>(out);
@@ -472,7 +435,7 @@ hipError_t launch_generate_hyperbolic(int dtype, int mode, uint32_t seed, uint32
     a.k1 = stream;
     a.first = first;
     a.n = n;
-    return launch_gen_h<double, HYP_DEGREE>(a, P, B, lds, s, shape.hyperbolic[1]);
+    return launch_gen_h<double, HYP_DEGREE>(a, P, B, lds, s, shape);
 }
 
 }  // namespace qm

@@ -8,15 +8,9 @@
 #include <stdint.h>
 
 #include "qm_device.hpp"
+#include "qm_stream.hpp"
 
 namespace qm {
-
-typedef double d2 __attribute__((ext_vector_type(2)));
-typedef float f4 __attribute__((ext_vector_type(4)));
-
-template <typename T> struct vec16;
-template <> struct vec16<double> { typedef d2 type; static constexpr int n = 2; };
-template <> struct vec16<float> { typedef f4 type; static constexpr int n = 4; };
 
 struct OpNQ64Plain { __device__ double operator()(double u) const { return normal_quantile_f64<false>(u); } };
 struct OpNQ64Paper { __device__ double operator()(double u) const { return normal_quantile_f64<true>(u); } };
@@ -67,6 +61,8 @@ struct HybridNQ32 {
     static __device__ __forceinline__ float whole(float u) { return normal_quantile_f32_refine(u); }
 };
 
+template <typename T> struct OpCopy { __device__ T operator()(T x) const { return x; } };
+
 template <class Op> struct HybridOf { typedef void type; };
 template <> struct HybridOf<OpNQ64Plain> { typedef HybridNQ64 type; };
 template <> struct HybridOf<OpNQ32Refine> { typedef HybridNQ32 type; };
@@ -115,5 +111,31 @@ __device__ __forceinline__ void hybrid_eval(const T (&u)[K], T (&w)[K], T* buf, 
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
+
+/* A walk's map from a per-element function. */
+template <typename T, class Op>
+struct ElementMap {
+    template <int K>
+    __device__ __forceinline__ void tile(const T (&x)[K], T (&y)[K]) const
+    {
+        Op op;
+#pragma unroll
+        for (int k = 0; k < K; ++k) y[k] = op(x[k]);
+    }
+    __device__ __forceinline__ T one(T x) const { return Op()(x); }
+};
+
+/* A walk's map from a gathered hybrid; buf: the wave's LDS list. */
+template <typename T, class H>
+struct HybridMap {
+    T* buf;
+    uint32_t lane;
+    template <int K>
+    __device__ __forceinline__ void tile(const T (&x)[K], T (&y)[K]) const
+    {
+        hybrid_eval<T, K, H>(x, y, buf, lane);
+    }
+    __device__ __forceinline__ T one(T x) const { return H::whole(x); }
+};
 
 }  // namespace qm

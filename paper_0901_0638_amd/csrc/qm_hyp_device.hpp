@@ -9,27 +9,29 @@
 
 #include "qm_device.hpp"
 #include "qm_hyp_table.h"
+#include "qm_stream.hpp"
 
 namespace qm {
 
 /* Rows of DEG + 1 doubles in global memory.  In LDS every row starts on a
    16-byte boundary and is read in 16-byte pieces (ds_read_b128), so lanes
    on different cells either share a 16-byte bank group or none: never a
-   half overlap.  The FP64-output cells (degree 11) keep their twelve
-   doubles unpadded, six 16-byte reads.  Measured on MI355X (2^26 base
-   samples), this took the FP64 map from 283-329 to 361-363 Gs/s against
-   the earlier rows of 13 doubles read as 8-byte pairs, whose stride only
-   staggered rows over the banks (rows of 12 or 14 doubles read as 8-byte
-   pairs ran at 150-233).  The FP32-output cells (degree 7) are stored
-   mixed: the constant term as a double (dwords 0-1), the seven higher
-   coefficients as floats, highest power first (dwords 2-8), padded to 12
-   dwords: two 16-byte reads and one 4-byte read (36 bytes, against 64 for
-   eight doubles).  lds is the row stride in doubles.  The dynamic LDS the
-   rows live in is declared 16-byte aligned. */
+   half overlap; and a row takes an odd number of such groups, so that the
+   rows start in every one of them.  FP64-output cells (degree 11): twelve
+   doubles padded to fourteen, six reads.  Where the caches feed the map the
+   LDS reads are its limit: 2^22 samples of (1, 0.5, 1) take 13.8 us on
+   MI355X against 14.8 with rows of twelve, whose starts miss half the
+   groups, 2^20 5.6 against 6.2; from 2^26 on both stream at the memory's
+   rate.  FP32-output cells (degree 7) are stored mixed: the constant term as
+   a double (dwords 0-1), the seven higher coefficients as floats, highest
+   power first (dwords 2-8), padded to 12 dwords: two 16-byte reads and one
+   4-byte read (36 bytes, against 64 for eight doubles).  lds is the row
+   stride in doubles.  The dynamic LDS the rows live in is declared 16-byte
+   aligned. */
 template <int DEG> struct HypRow {
     static constexpr int n = DEG + 1;
-    static constexpr int lds = DEG == HYP_DEGREE_F32 ? 6 : DEG + 1;
-    static_assert(lds % 2 == 0, "rows must start on 16-byte boundaries");
+    static constexpr int lds = DEG == HYP_DEGREE_F32 ? 6 : DEG + 3;
+    static_assert(lds % 4 == 2, "rows must take an odd number of 16-byte groups");
 };
 static_assert(HYP_SUB == 8, "the cell index takes the top 3 mantissa bits of t");
 
@@ -130,8 +132,10 @@ __device__ __forceinline__ double hyp_near(double v, const double* __restrict__ 
 
 /* R in the first octave of a side with the origin series (row 0 of its
    cells, layout in qm_hyp_table.h): R = P0(a) + w (P1(a) + w (P2(a) +
-   w P3(a))), w = a^rho; FP32-output cells have no P3.  The terms in w are
-   a small part of R near 0, so the library pow's accuracy is ample. */
+   w P3(a))), w = a^rho = e^(rho log a); FP32-output cells have no P3.  The
+   terms in w are a small part of R near 0 (w <= v0^rho), so the short
+   logarithm and exponential (a few 1e-15 where w matters) are ample; the
+   library pow took three times their instructions. */
 template <int DEG>
 __device__ __forceinline__ double hyp_origin(const double* __restrict__ row, double a)
 {
@@ -139,7 +143,7 @@ __device__ __forceinline__ double hyp_origin(const double* __restrict__ row, dou
        their degrees in v */
     constexpr int NFAM = DEG == HYP_DEGREE ? 4 : 3;
     constexpr int DG64[4] = {0, 1, 2, 4}, DG32[4] = {0, 1, 3, 0};
-    const double w = ::pow(a, row[0]);
+    const double w = exp_refine<12>(-row[0] * neg_log_unit(a));
     double R = 0;
     int k = 1;
 #pragma unroll
@@ -188,39 +192,120 @@ __device__ __forceinline__ double hyp_far_of(double v, const HypParams& P)
 }
 
 /* Both sides' LDS rows: right side rows 0..nlds-1, left side after (for
-   the FP32-output cells in the mixed layout of HypRow). */
+   the FP32-output cells in the mixed layout of HypRow).  16-byte loads (the
+   rows in device memory are 8-byte aligned), four of a thread's in flight
+   together: an FP64 row's twelve doubles are six pieces; an FP32-output row
+   of eight doubles goes to one thread, which writes its three 16-byte
+   groups. */
 template <int DEG>
 __device__ __forceinline__ void stage_hyp(double* lds, const HypParams& P)
 {
-    constexpr int W = HypRow<DEG>::n;
-    const int n = P.nlds * W;
-    for (int i = threadIdx.x; i < 2 * n; i += blockDim.x) {
-        const bool left = i >= n;
-        const int e = left ? i - n : i;
-        const int row = e / W, col = e - row * W;
-        const int r = (left ? P.nlds : 0) + row;
-        const double c = (left ? P.l.gcoef : P.r.gcoef)[e];
-        if constexpr (DEG == HYP_DEGREE_F32) {
-            if (col == DEG) lds[r * HypRow<DEG>::lds] = c;
-            else reinterpret_cast<float*>(lds)[2 * r * HypRow<DEG>::lds + 2 + col] = (float)c;
-        } else {
-            lds[r * HypRow<DEG>::lds + col] = c;
+    typedef double d2any __attribute__((ext_vector_type(2), aligned(8)));
+    typedef double d2v __attribute__((ext_vector_type(2)));
+    constexpr int PIECES = HypRow<DEG>::n / 2;
+    const int step = blockDim.x;
+    if constexpr (DEG == HYP_DEGREE_F32) {
+        typedef float f4v __attribute__((ext_vector_type(4)));
+        for (int r = threadIdx.x; r < 2 * P.nlds; r += step) {
+            const double* src = r < P.nlds ? P.r.gcoef + r * HypRow<DEG>::n : P.l.gcoef + (r - P.nlds) * HypRow<DEG>::n;
+            d2any c[PIECES];
+#pragma unroll
+            for (int k = 0; k < PIECES; ++k) c[k] = reinterpret_cast<const d2any*>(src)[k];
+            double* row = lds + r * HypRow<DEG>::lds;
+            d2v head;
+            head.x = c[3].y;
+            head.y = __hiloint2double(__float_as_int((float)c[0].y), __float_as_int((float)c[0].x));
+            *reinterpret_cast<d2v*>(row) = head;
+            *reinterpret_cast<f4v*>(row + 2) = f4v{(float)c[1].x, (float)c[1].y, (float)c[2].x, (float)c[2].y};
+            reinterpret_cast<float*>(row + 4)[0] = (float)c[3].x;
+        }
+    } else {
+        const int n = P.nlds * PIECES;
+        for (int i = threadIdx.x; i < 2 * n; i += 4 * step) {
+            d2any v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int e = min(i + k * step, 2 * n - 1);
+                v[k] = reinterpret_cast<const d2any*>(e < n ? P.r.gcoef : P.l.gcoef)[e < n ? e : e - n];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int e = i + k * step;
+                if (e < 2 * n)
+                    reinterpret_cast<d2v*>(lds)[e / PIECES * (HypRow<DEG>::lds / 2) + e % PIECES] = v[k];
+            }
         }
     }
 }
 
-/* |Q(v)| of one element, with its own wave vote for the far path. */
-template <int DEG>
-__device__ __forceinline__ double hyp_abs_q(double v, const double* __restrict__ lds, const HypParams& P)
+/*
+ * |Q(v)| of the K elements a lane holds: every element's cell polynomial
+ * first (K independent chains), then, if any lane of the wave has elements
+ * beyond the LDS cells, passes that take one such element of each lane at a
+ * time, whichever of the K it is.  Far elements are rare and scattered: on a
+ * target with the origin series about 0.2% of the base samples are, so that a
+ * wave's tile of 512 holds one on average in one or two lanes, and one
+ * pass serves it.  A vote for each of the K slots entered the far code once
+ * per slot that held any, with a library pow each (2^24 FP64 samples of
+ * variance-gamma (4.25, 1, 0.3): 67.2 us on MI355X, 54.7 with the passes and
+ * the short power of hyp_origin).
+ */
+template <int DEG, int K>
+__device__ __forceinline__ void hyp_abs_q(const double (&v)[K], double (&q)[K], const double* __restrict__ lds,
+                                          const HypParams& P)
 {
-    bool far;
-    double q = hyp_near<DEG>(v, lds, P, &far);
-    if (wave_any(far)) {
-        double qf = hyp_far_of<DEG>(far ? v : 0.0, P);
-        q = far ? qf : q;
+    bool far[K];
+    bool anyfar = false;
+#pragma unroll
+    for (int e = 0; e < K; ++e) {
+        q[e] = hyp_near<DEG>(v[e], lds, P, &far[e]);
+        anyfar |= far[e];
     }
-    return q;
+    if (wave_any(anyfar)) {
+        uint32_t left = 0;
+#pragma unroll
+        for (int e = 0; e < K; ++e) left |= far[e] ? 1u << e : 0u;
+        do {
+            const uint32_t bit = left & -left;
+            double x = 0.0;
+#pragma unroll
+            for (int e = 0; e < K; ++e) x = (bit >> e) & 1u ? v[e] : x;
+            const double f = hyp_far_of<DEG>(x, P);
+#pragma unroll
+            for (int e = 0; e < K; ++e) q[e] = (bit >> e) & 1u ? f : q[e];
+            left ^= bit;
+        } while (wave_any(left != 0));
+    }
 }
+
+/* A walk's map of the hyperbolic and variance-gamma targets:
+   x = mu + sign(v) |Q(v)|, in FP64; FP32 outputs round it once. */
+template <typename T, int DEG>
+struct HypMap {
+    const double* lds;
+    const HypParams& P;
+    template <int K>
+    __device__ __forceinline__ void tile(const T (&x)[K], T (&y)[K]) const
+    {
+        constexpr int C = K > 8 ? 8 : K;    /* eight chains at a time: sixteen cost half the occupancy */
+#pragma unroll
+        for (int c = 0; c < K; c += C) {
+            double v[C], q[C];
+#pragma unroll
+            for (int k = 0; k < C; ++k) v[k] = (double)x[c + k];
+            hyp_abs_q<DEG, C>(v, q, lds, P);
+#pragma unroll
+            for (int k = 0; k < C; ++k) y[c + k] = (T)(P.mu + __builtin_copysign(q[k], v[k]));
+        }
+    }
+    __device__ __forceinline__ T one(T x) const
+    {
+        const T a[1] = {x};
+        T y[1];
+        tile(a, y);
+        return y[0];
+    }
+};
 
 /* Kernel parameters of a table's cell set for FP64 (f32 = false) or FP32
    outputs (qm_hyp.hip): false if the header is not a valid table of ncoef

@@ -28,9 +28,12 @@ struct LaunchShape {
     KernelShape stream;      /* k_map, FP64: exp -> normal, paper mode */
     KernelShape stream32;    /* k_map, FP32: exp -> normal, paper and plain quantiles */
     KernelShape hybrid[2];   /* [0] FP32+refine, [1] FP64 quantile: k_hybrid */
-    KernelShape generate[2]; /* [0] FP32, [1] FP64 outputs: k_generate, k_generate_t */
+    KernelShape generate[2]; /* [0] FP32, [1] FP64 outputs: k_generate */
+    KernelShape generate_t[2]; /* ... k_generate_t */
+    KernelShape generate_h[2]; /* ... k_generate_h */
     KernelShape student[2];  /* [0] FP32, [1] FP64 outputs: k_student */
     KernelShape hyperbolic[2]; /* [0] FP32, [1] FP64: k_hyperbolic */
+    int cus;                 /* compute units of the device */
     int compact;             /* quantiles: gather non-central lanes across the wave */
 };
 

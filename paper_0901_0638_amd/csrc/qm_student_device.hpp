@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include "qm_device.hpp"
+#include "qm_stream.hpp"
 
 namespace qm {
 
@@ -22,13 +23,31 @@ struct StudentParams {
     int lds_stride;   /* doubles between cell rows in LDS: even, >= the row */
 };
 
+/* 16 bytes at the alignment of a double (gfx950 takes a dwordx4 load at any
+   dword): table rows in device memory follow a header of 8-byte multiples. */
+typedef double d2any __attribute__((ext_vector_type(2), aligned(8)));
+
 /* Copy the first nlds cell rows (2^row_shift doubles each) into LDS rows of
-   P.lds_stride doubles. */
+   P.lds_stride doubles, in 16-byte pieces, four in flight per thread before
+   the first is waited for: a workgroup's staging is then one or two trips to
+   the L2 instead of a chain of six to twelve 8-byte ones. */
 __device__ __forceinline__ void stage_table(double* lds, const double* __restrict__ coef, const StudentParams& P)
 {
-    const int ncoef = P.nlds << P.row_shift;
-    const int mask = (1 << P.row_shift) - 1;
-    for (int i = threadIdx.x; i < ncoef; i += blockDim.x) lds[(i >> P.row_shift) * P.lds_stride + (i & mask)] = coef[i];
+    const int shift = P.row_shift - 1;              /* pieces per row */
+    const int n = P.nlds << shift;
+    const int mask = (1 << shift) - 1;
+    const d2any* src = reinterpret_cast<const d2any*>(coef);
+    const int step = blockDim.x;
+    for (int i = threadIdx.x; i < n; i += 4 * step) {
+        d2any v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = src[min(i + k * step, n - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int e = i + k * step;
+            if (e < n) *reinterpret_cast<d2*>(lds + (e >> shift) * P.lds_stride + 2 * (e & mask)) = v[k];
+        }
+    }
 }
 
 /* R(y) of cell j by Horner in d = y - y_c (rows of DEG + 1 doubles). */
@@ -63,13 +82,14 @@ __device__ __forceinline__ double cell_poly_lds(const double* __restrict__ row, 
    clamped to jmax (NaN and inf clamp too), and d = s^2 - y_c with a single
    rounding (|d| <= h/2), so the full input precision reaches the
    polynomial, which matters because log R grows like y/(2 nu). */
-__device__ __forceinline__ int cell_of(double s, double yh, int jmax, const StudentParams& P, double* d)
+__device__ __forceinline__ int cell_of(double s, double yh, int jmax, double h, double inv_h, double centre_offset,
+                                       double* d)
 {
-    double jd = yh * P.inv_h;
+    double jd = yh * inv_h;
     const double jm = (double)jmax;
     jd = (jd < jm) ? jd : jm;
     int j = (int)jd;
-    double yc = __builtin_fma((double)j, P.h, P.centre_offset);   /* exact: h is a power of 2 */
+    double yc = __builtin_fma((double)j, h, centre_offset);   /* exact: h is a power of 2 */
     *d = __builtin_fma(s, s, -yc);
     return j;
 }
@@ -80,9 +100,14 @@ __device__ __forceinline__ int cell_of(double s, double yh, int jmax, const Stud
    (Sections 3.3, 3.5), which the table builder has checked to be as accurate
    as the cells there.  log w is carried as a double-double (s^2/2 exactly,
    the division by nu with its remainder), because an absolute error e in it
-   is a relative error e/nu in t and |log w| reaches several hundred. */
+   is a relative error e/nu in t and |log w| reaches several hundred.  The
+   parameters come one by one: a reference to the block of them put a copy of
+   it in every lane's scratch memory at the head of the kernel, 128 bytes per
+   element of a short launch. */
 template <int DEG>
-static __device__ __noinline__ double student_far(double s, const StudentParams& P)
+static __device__ __noinline__ double student_far(double s, double h, double inv_h, double centre_offset, double y_max,
+                                                  const double* gcoef, int ncell, double log_K, double nu,
+                                                  double sqrt_nu, double tail_a)
 {
 #pragma clang fp contract(off)
     const double INV_SQRT2 = 0.70710678118654752440, LN2 = 0.69314718055994530942;
@@ -91,40 +116,91 @@ static __device__ __noinline__ double student_far(double s, const StudentParams&
     /* s^2 overflows (s above 1.3e154): log t is about s^2/(2 nu) > 700 for
        every nu below 1e300, so t overflows too */
     if (!(yh < __builtin_inf())) return yh;
-    if (yh <= P.y_max) {
+    if (yh <= y_max) {
         double d;
-        int j = cell_of(s, yh, P.ncell - 1, P, &d);
-        return s * cell_poly<DEG>(P.gcoef + j * (DEG + 1), d);
+        int j = cell_of(s, yh, ncell - 1, h, inv_h, centre_offset, &d);
+        return s * cell_poly<DEG>(gcoef + j * (DEG + 1), d);
     }
     double hs = -0.5 * s;                              /* exact */
     double e_hi = hs * s;
     double e_lo = __builtin_fma(hs, s, -e_hi);         /* -s^2/2 = e_hi + e_lo exactly */
-    double r = P.log_K + (::log(::erfcx(s * INV_SQRT2)) - LN2);
+    double r = log_K + (::log(::erfcx(s * INV_SQRT2)) - LN2);
     double a_hi = e_hi + r;                            /* two-sum */
     double bb = a_hi - e_hi;
     double a_lo = (e_hi - (a_hi - bb)) + (r - bb) + e_lo;
-    const double nu = P.nu;
     double q_hi = a_hi / nu;                           /* log w / nu = q_hi + q_lo */
     double q_lo = (__builtin_fma(-q_hi, nu, a_hi) + a_lo) / nu;
-    double t = P.sqrt_nu * ::exp(-q_hi) * (1.0 - q_lo);
-    return t * (1.0 + P.tail_a * ::exp(2.0 * q_hi));
+    double t = sqrt_nu * ::exp(-q_hi) * (1.0 - q_lo);
+    return t * (1.0 + tail_a * ::exp(2.0 * q_hi));
 }
 
-/* t(z) in FP64 from the LDS table, cells of degree DEG. */
-template <int DEG>
-__device__ __forceinline__ double student_eval(double z, const double* __restrict__ tab, const StudentParams& P)
+/* t(z) in FP64, from the LDS table with cells of degree DEG, of the K
+   elements a lane holds: K independent chains, then one wave vote for the
+   elements beyond the LDS cells (also NaN, which propagates either way), of
+   which a pass takes one of each lane. */
+template <int DEG, int K>
+__device__ __forceinline__ void student_eval(const double (&z)[K], double (&t)[K], const double* __restrict__ tab,
+                                             const StudentParams& P)
 {
-    double s = __builtin_fabs(z);
-    double yh = s * s;                      /* only selects the cell */
-    double d;
-    int j = cell_of(s, yh, P.nlds - 1, P, &d);
-    double t = z * cell_poly_lds<DEG>(tab + j * P.lds_stride, d);
-    bool far = !(yh <= P.y_lds);            /* also NaN: NaN propagates either way */
-    if (wave_any(far)) {
-        double tf = __builtin_copysign(student_far<DEG>(far ? s : 1.0, P), z);
-        t = far ? tf : t;
+    bool far[K];
+    bool anyfar = false;
+#pragma unroll
+    for (int e = 0; e < K; ++e) {
+        const double s = __builtin_fabs(z[e]);
+        const double yh = s * s;            /* only selects the cell */
+        double d;
+        const int j = cell_of(s, yh, P.nlds - 1, P.h, P.inv_h, P.centre_offset, &d);
+        t[e] = z[e] * cell_poly_lds<DEG>(tab + j * P.lds_stride, d);
+        far[e] = !(yh <= P.y_lds);
+        anyfar |= far[e];
     }
-    return t;
+    if (wave_any(anyfar)) {
+        uint32_t left = 0;
+#pragma unroll
+        for (int e = 0; e < K; ++e) left |= far[e] ? 1u << e : 0u;
+        do {
+            const uint32_t bit = left & -left;
+            double x = 1.0;
+#pragma unroll
+            for (int e = 0; e < K; ++e) x = (bit >> e) & 1u ? z[e] : x;
+            double f = student_far<DEG>(__builtin_fabs(x), P.h, P.inv_h, P.centre_offset, P.y_max, P.gcoef, P.ncell,
+                                        P.log_K, P.nu, P.sqrt_nu, P.tail_a);
+            f = __builtin_copysign(f, x);
+#pragma unroll
+            for (int e = 0; e < K; ++e) t[e] = (bit >> e) & 1u ? f : t[e];
+            left ^= bit;
+        } while (wave_any(left != 0));
+    }
 }
+
+/* A walk's map of Student t.  FP32 in/out: the FP64 evaluation of the
+   table's FP32 cells (R to 1e-10) rounded once; the input is exact in FP64,
+   so the cell offset carries the input's full precision. */
+template <typename T, int DEG>
+struct StudentMap {
+    const double* tab;
+    const StudentParams& P;
+    template <int K>
+    __device__ __forceinline__ void tile(const T (&x)[K], T (&y)[K]) const
+    {
+        constexpr int C = K > 8 ? 8 : K;    /* eight chains at a time: sixteen cost half the occupancy */
+#pragma unroll
+        for (int c = 0; c < K; c += C) {
+            double z[C], t[C];
+#pragma unroll
+            for (int k = 0; k < C; ++k) z[k] = (double)x[c + k];
+            student_eval<DEG, C>(z, t, tab, P);
+#pragma unroll
+            for (int k = 0; k < C; ++k) y[c + k] = (T)t[k];
+        }
+    }
+    __device__ __forceinline__ T one(T x) const
+    {
+        const T a[1] = {x};
+        T y[1];
+        tile(a, y);
+        return y[0];
+    }
+};
 
 }  // namespace qm
