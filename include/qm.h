@@ -101,16 +101,21 @@ typedef struct qm_ctx qm_ctx;
  * bytes (input + output of admitted requests) that the serving loop keeps in
  * flight; 0 means no serving budget (qm_submit then rejects every request).
  * The context owns the per-nu Student t tables and the serving state.
- * Each kernel family has its own launch shape (workgroups of 256 per compute
- * unit x 16-byte vectors in flight per lane, from measured sweeps: light
- * FP64 maps 2 x 4, the other FP32 maps 32 x 2, FP64 quantile 64 x 4,
- * FP32+refine quantile 16 x 4, fused generation 64 x 4 (FP64) and 32 x 2
- * (FP32), Student t 2 x 4 (FP64) and 3 x 4 (FP32), exp -> hyperbolic or
- * variance-gamma 16 x 4 (FP64) and 16 x 2 (FP32)); the environment
+ * Each kernel family has its own launch shape (most workgroups of 256 per
+ * compute unit x 16-byte vectors in flight per lane, from measured sweeps:
+ * FP64 maps 64 x 4, FP32 maps 32 x 2, FP64 quantile 64 x 4, FP32+refine
+ * quantile 16 x 4, Student t 2 x 4 (FP64) and 4 x 2 (FP32), exp ->
+ * hyperbolic or variance-gamma 3 x 2 and 4 x 2; fused generation of uniforms
+ * 64 x 4, quantiles 8 x 4 (FP64) and 32 x 2 (FP32), Student t 8 x 4,
+ * hyperbolic 8 x 4 and 16 x 2); a launch too small to give every compute
+ * unit two workgroups takes fewer vectors per lane, and one of 2^26 elements
+ * or so and more 64 workgroups per compute unit.  The environment
  * variables QM_BLOCKS_PER_CU (1..64) and QM_UNROLL (1, 2 or 4), read here,
  * override every family, and QM_SHAPE_STREAM, QM_SHAPE_STREAM32,
- * QM_SHAPE_NQ64, QM_SHAPE_NQ32, QM_SHAPE_GEN64, QM_SHAPE_GEN32,
- * QM_SHAPE_T64, QM_SHAPE_T32, QM_SHAPE_H64, QM_SHAPE_H32 ("blocks,unroll")
+ * QM_SHAPE_NQ64, QM_SHAPE_NQ32, QM_SHAPE_GU64, QM_SHAPE_GU32,
+ * QM_SHAPE_GEN64, QM_SHAPE_GEN32, QM_SHAPE_GT64, QM_SHAPE_GT32,
+ * QM_SHAPE_GH64, QM_SHAPE_GH32, QM_SHAPE_T64, QM_SHAPE_T32, QM_SHAPE_H64,
+ * QM_SHAPE_H32 ("blocks,unroll")
  * one family each.  QM_COMPACT=0 turns off the quantiles' gathering of
  * non-central lanes across the wave (the results are bitwise the same
  * either way).

@@ -281,33 +281,44 @@ qm_status qm_init(int hip_device, uint64_t hbm_budget_bytes, qm_ctx** out)
        per lane), the best of measured sweeps over 1..64 x 1..4 on MI355X;
        QM_BLOCKS_PER_CU / QM_UNROLL override every family (tuning) */
     const uint64_t ncu = (uint64_t)(cus > 0 ? cus : 256);
-    struct { qm::KernelShape* ks; const char* env; long bpc, unroll; } fam[] = {
-        {&c->shape.stream, "QM_SHAPE_STREAM", 2, 4},   /* light maps: few workgroups, deep unroll */
+    struct { qm::KernelShape* ks; const char* env; long bpc, unroll, big; } fam[] = {
+        /* light FP64 maps: with no table to stage, many workgroups (2^26
+           exp -> normal: 166 us at 64 x 4, 175 at 2 x 4; 2^22 13.0, 14.0) */
+        {&c->shape.stream, "QM_SHAPE_STREAM", 64, 4, 0},
         /* FP32 maps: four elements per 16-byte vector carry twice the
            arithmetic per byte; exp -> normal FP32 (2^26, scrubbed launches)
            ran 473-478 Gs/s refined and 590-600 plain at 16..32 x 2, against
            393-411 and 498-526 at 2 x 4 */
-        {&c->shape.stream32, "QM_SHAPE_STREAM32", 32, 2},
-        /* quantiles, wave-contiguous tiles: FP32+refine 16 x 4 (8..16 x 4
-           measured 0.504-0.505 ms on the 2^28 FP32 mixture, 32 x 2 0.52-0.54),
-           FP64 64 x 4 */
-        {&c->shape.hybrid[0], "QM_SHAPE_NQ32", 16, 4},
-        {&c->shape.hybrid[1], "QM_SHAPE_NQ64", 64, 4},
-        /* fused generation (grid-stride), FP32 and FP64 outputs */
-        {&c->shape.generate[0], "QM_SHAPE_GEN32", 32, 2},
-        {&c->shape.generate[1], "QM_SHAPE_GEN64", 64, 4},
-        {&c->shape.generate_t[0], "QM_SHAPE_GT32", 32, 2},
-        {&c->shape.generate_t[1], "QM_SHAPE_GT64", 64, 4},
-        {&c->shape.generate_h[0], "QM_SHAPE_GH32", 16, 2},
-        {&c->shape.generate_h[1], "QM_SHAPE_GH64", 16, 4},
-        {&c->shape.student[0], "QM_SHAPE_T32", 3, 4},  /* Student t, FP32 outputs */
-        {&c->shape.student[1], "QM_SHAPE_T64", 2, 4},  /* Student t, FP64 outputs */
-        /* exp -> hyperbolic, FP32, wave-contiguous tiles: 16 x 2 (670 Gs/s on
-           2^26 base samples; 645 at 6 x 2, 658-673 at 8..16 x 2..4) */
-        {&c->shape.hyperbolic[0], "QM_SHAPE_H32", 16, 2},
-        /* exp -> hyperbolic, FP64, wave-contiguous tiles: 16 x 4 (0.185-0.186
-           ms on 2^26 base samples, against 0.189-0.199 at 4..8 x 2..4) */
-        {&c->shape.hyperbolic[1], "QM_SHAPE_H64", 16, 4},
+        {&c->shape.stream32, "QM_SHAPE_STREAM32", 32, 2, 0},
+        /* quantiles: FP32+refine 16 x 4 (8..16 x 4 measured 0.504-0.505 ms on
+           the 2^28 FP32 mixture, 32 x 2 0.52-0.54), FP64 64 x 4 */
+        {&c->shape.hybrid[0], "QM_SHAPE_NQ32", 16, 4, 2},
+        {&c->shape.hybrid[1], "QM_SHAPE_NQ64", 64, 4, 0},
+        /* fused generation, write only.  Uniforms: the stores alone, many
+           workgroups (2^26 FP32: 42 us at 64 x 4, 47 at 32 x 2).  Quantiles:
+           2^26 FP32 96 us at 32 x 2, FP64 155 at 8 x 4, 163 at 64 x 4 */
+        {&c->shape.uniform[0], "QM_SHAPE_GU32", 64, 4, 0},
+        {&c->shape.uniform[1], "QM_SHAPE_GU64", 64, 4, 0},
+        {&c->shape.generate[0], "QM_SHAPE_GEN32", 32, 2, 0},
+        {&c->shape.generate[1], "QM_SHAPE_GEN64", 8, 4, 4},
+        /* kernels that stage a table per workgroup: the grid stays within a
+           few workgroups per unit, so that each stages once for many tiles.
+           Fused Student t, 2^24 FP64: 51 us at 8 x 4, 71 at 64 x 4 (one tile
+           for each staging); FP32 39, 49 at 32 x 2.  Fused hyperbolic, 2^24
+           FP64: 62 us at 8 x 4, 63 at 16 x 4; FP32 44 at 8..16 x 2 */
+        {&c->shape.generate_t[0], "QM_SHAPE_GT32", 8, 4, 4},
+        {&c->shape.generate_t[1], "QM_SHAPE_GT64", 8, 4, 4},
+        {&c->shape.generate_h[0], "QM_SHAPE_GH32", 16, 2, 4},
+        {&c->shape.generate_h[1], "QM_SHAPE_GH64", 8, 4, 4},
+        /* Student t: 2^26 FP64 174 us at 2 x 4, 181-184 at 3..8; FP32 91 at
+           4 x 2, 2^22 8.5 against 10.2 at 2 x 4 */
+        {&c->shape.student[0], "QM_SHAPE_T32", 4, 2, 2},
+        {&c->shape.student[1], "QM_SHAPE_T64", 2, 4, 0},
+        /* exp -> hyperbolic and variance-gamma: 2^22 FP64 14 us at 3 x 2, 17 at
+           16 x 4, 2^24 46 and 54, 2^26 184 and 182; FP32 2^24 25.6 at 4 x 2,
+           26.7 at 16 x 2, 2^26 92 both */
+        {&c->shape.hyperbolic[0], "QM_SHAPE_H32", 4, 2, 2},
+        {&c->shape.hyperbolic[1], "QM_SHAPE_H64", 3, 2, 2},
     };
     long env_bpc = 0, env_unroll = 0;
     if (const char* ev = getenv("QM_BLOCKS_PER_CU")) env_bpc = strtol(ev, nullptr, 10);
@@ -319,7 +330,9 @@ qm_status qm_init(int hip_device, uint64_t hbm_budget_bytes, qm_ctx** out)
             eb = strtol(ev, &end, 10);
             eu = (end && *end == ',') ? strtol(end + 1, nullptr, 10) : 0;
         }
-        if (eb >= 1 && eb <= 64) bpc = eb;
+        f.ks->big_tiles = 64 * ncu * (uint64_t)f.big;
+        f.ks->big_blocks = 64 * ncu;
+        if (eb >= 1 && eb <= 64) { bpc = eb; f.ks->big_tiles = 0; }
         if (eu == 1 || eu == 2 || eu == 4) unroll = eu;
         f.ks->max_blocks = ncu * (uint64_t)bpc;
         f.ks->unroll = (int)unroll;

@@ -134,7 +134,7 @@ static void gen_geometry(GenArgs<T>& a)
 template <typename T, class H, bool GATHER>
 static hipError_t launch_gen(GenArgs<T> a, hipStream_t s, const LaunchShape& shape)
 {
-    const KernelShape ks = shape.generate[sizeof(T) == 8];
+    const KernelShape ks = (std::is_same<H, OpCopy<T>>::value ? shape.uniform : shape.generate)[sizeof(T) == 8];
     gen_geometry(a);
     const int u = launch_unroll(a.nvec, ks, shape.cus);
     with_unroll(u, [&](auto U) {

@@ -12,23 +12,24 @@
 
 namespace qm {
 
-/* Launch geometry of one kernel family: the grid is capped at max_blocks
-   workgroups of 256 (grid-stride beyond), each lane keeps `unroll` 16-byte
-   vectors in flight (1, 2 or 4). */
+/* Launch geometry of one kernel family: at most max_blocks workgroups of
+   256, each lane keeping `unroll` 16-byte vectors in flight (1, 2 or 4); from
+   big_tiles workgroup tiles on (0: never), big_blocks workgroups. */
 struct KernelShape {
     uint64_t max_blocks;
     int unroll;
+    uint64_t big_tiles, big_blocks;
 };
 
 /* Per family, measured on MI355X (launch-shape sweeps over 1..64
-   workgroups per CU x 1..4 vectors): light HBM-bound maps stream best from
-   few workgroups with deep unrolling, the VALU-heavy hybrid quantiles from
-   many. */
+   workgroups per CU x 1..4 vectors, 2^17 to 2^28 elements): kernels that
+   stage a table run best from few workgroups, the others from many. */
 struct LaunchShape {
     KernelShape stream;      /* k_map, FP64: exp -> normal, paper mode */
     KernelShape stream32;    /* k_map, FP32: exp -> normal, paper and plain quantiles */
     KernelShape hybrid[2];   /* [0] FP32+refine, [1] FP64 quantile: k_hybrid */
-    KernelShape generate[2]; /* [0] FP32, [1] FP64 outputs: k_generate */
+    KernelShape uniform[2];  /* [0] FP32, [1] FP64 outputs: k_generate of the uniforms */
+    KernelShape generate[2]; /* ... of quantiles */
     KernelShape generate_t[2]; /* ... k_generate_t */
     KernelShape generate_h[2]; /* ... k_generate_h */
     KernelShape student[2];  /* [0] FP32, [1] FP64 outputs: k_student */

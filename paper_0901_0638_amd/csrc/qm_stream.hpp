@@ -179,10 +179,21 @@ inline int launch_unroll(uint64_t nvec, const KernelShape& ks, int cus)
     return u;
 }
 
+/*
+ * Workgroups of a launch.  Few of them keep each one's set-up (a staged
+ * table) small against its work, and for arrays that the last-level cache
+ * holds that is best; large arrays run at the memory's rate, where a fixed
+ * share per workgroup waits for the slowest channel, and many short
+ * workgroups, handed out as others end, even that out: FP64 hyperbolic
+ * samples took 46 us for 2^24 with 3 workgroups per unit and 55 with 64, but
+ * for 2^26 184 and 175, for 2^27 375 and 358 (MI355X).  The switch lies where
+ * 64 per unit have two tiles each (fused chains with a table: four).
+ */
 inline unsigned launch_blocks(uint64_t nvec, int unroll, const KernelShape& ks)
 {
-    const uint64_t per_block = 256ull * unroll, blocks = (nvec + per_block - 1) / per_block;
-    return (unsigned)(blocks > ks.max_blocks ? ks.max_blocks : blocks < 1 ? 1 : blocks);
+    const uint64_t per_block = 256ull * unroll, tiles = (nvec + per_block - 1) / per_block;
+    const uint64_t cap = ks.big_tiles && tiles >= ks.big_tiles ? ks.big_blocks : ks.max_blocks;
+    return (unsigned)(tiles > cap ? cap : tiles < 1 ? 1 : tiles);
 }
 
 /* f(std::integral_constant<int, u>) for u = 1, 2 or 4. */
