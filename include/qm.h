@@ -20,7 +20,7 @@
  *   qm_generate_student_t, qm_generate_hyperbolic, qm_generate_vg
  *                             Student t / hyperbolic / variance-gamma
  *                             samples drawn the same way, through the maps
- *   qm_run_batch              many such requests in one persistent launch
+ *   qm_run_batch              many such requests in one launch
  *   qm_submit / qm_poll       continuous-batching serving loop
  *
  * Conventions (all entry points):
@@ -324,15 +324,15 @@ typedef struct {
 /*
  * Run `count` requests (host array) of mixed kinds (every kind but
  * QM_UNIFORM), dtypes, modes, nu and hyperbolic parameters as one
- * persistent launch on hip_stream: workgroups claim fixed-size chunks
- * from a device counter; each chunk belongs to one request and is evaluated
+ * launch on hip_stream: workgroups take fixed-size chunks, each its own and
+ * every grid-size-th after it; each chunk belongs to one request and is evaluated
  * by the same device code as the single-request call with that kind, dtype
  * and mode, so each output is bitwise identical to the single call's.
  * Validation covers every request before anything is launched; the first
  * invalid one decides the status.  Student t and hyperbolic tables not yet
  * in the context are built by this call, on the host, before the launch.
- * The call returns after enqueueing; the descriptor upload is ordered on
- * hip_stream.
+ * The call returns after enqueueing; the descriptors travel in the kernel's
+ * arguments (at most 16 requests) or in an upload ordered on hip_stream.
  */
 qm_status qm_run_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count, void* hip_stream);
 
@@ -349,7 +349,7 @@ qm_status qm_run_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count, void
  * (QM_BATCH_NOALLOC_MAX_REQUESTS records, about 768 KiB) that the library
  * holds once per GPU until the process ends, its address looked up by
  * qm_init; they are staged through the context's pinned host buffer, also
- * set up by qm_init.  The claim counter is rewritten to 0 by every call.
+ * set up by qm_init.
  *
  * Ordering: the upload and the launch are ordered on hip_stream.  All calls
  * on one GPU share that device array, so two calls whose work overlaps on
@@ -378,13 +378,13 @@ qm_status qm_run_batch_noalloc(qm_ctx* ctx, const qm_request* reqs, uint64_t cou
  * the context's HBM budget, and launches everything admitted since its
  * previous launch as one batch; batches run on several streams, so requests
  * admitted while others are on the GPU overlap with them.  Per-request state
- * (descriptors, chunk counters) lives on the device for the batch's life.
- * Completion is per request: the workgroup that writes a request's last
- * chunk raises a flag in host-coherent memory once all of the request's
- * stores have reached device memory, and the scheduler reports the request
- * complete as soon as it sees the flag, while the rest of its batch may
- * still run (in a batch of more than 4096 requests with n > 0, at the
- * batch's end).
+ * (descriptors, chunk counts) lives on the device for the batch's life.
+ * Completion is per request for the small requests of a large batch: the
+ * workgroup that writes a request's last chunk raises a flag in host-coherent
+ * memory once all of the request's stores have reached device memory, and the
+ * scheduler reports the request complete as soon as it sees the flag, while
+ * the rest of its batch may still run.  The other requests complete at their
+ * batch's end.
  * Ordering: the serving streams are the library's own and are not ordered
  * after any stream of the caller.  The request's input must therefore be
  * complete in device memory, and its output no longer read or written by

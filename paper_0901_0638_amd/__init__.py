@@ -189,7 +189,7 @@ def make_request(kind, inp, out, mode=None, nu=0.0, user_tag=0, hyperbolic=(0.0,
 
 
 def qm_run_batch(ctx, reqs, stream=None, device_tensor=None):
-    """Run a list of qm_request as one persistent launch."""
+    """Run a list of qm_request as one launch."""
     arr = (qm_request * len(reqs))(*reqs)
     s = ctypes.c_void_p(int(stream)) if stream is not None else _stream(None, device_tensor) if device_tensor is not None else ctypes.c_void_p(0)
     check(load().qm_run_batch(ctx.handle, arr, len(reqs), s))

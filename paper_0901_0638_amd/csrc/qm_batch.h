@@ -1,5 +1,5 @@
 /*
- * qm_batch.h -- descriptors of the persistent batch kernel (internal).
+ * qm_batch.h -- descriptors of the batch kernel (internal).
  */
 #pragma once
 #include <stdint.h>
@@ -10,16 +10,15 @@
 
 namespace qm {
 
-/* Elements per chunk (a workgroup claims one chunk at a time), carried in
-   the batch header: QM_CHUNK_MAX unless tuning lowers the floor, when small
-   batches get chunks of about total / (4 x workgroups), between these
-   bounds (multiples of QM_CHUNK_MIN keep every chunk start 16-byte aligned
-   within an aligned request). */
+/* Elements per chunk (a workgroup takes one chunk at a time), carried in the
+   batch header: a batch is cut into several chunks for each workgroup that
+   the GPU holds at once (batch_chunk), between these bounds (multiples of QM_CHUNK_MIN
+   keep every chunk start 16-byte aligned within an aligned request). */
 constexpr uint64_t QM_CHUNK_MIN = 2048;
-constexpr uint64_t QM_CHUNK_MAX = 32768;
+constexpr uint64_t QM_CHUNK_MAX = 16384;
 
 /* Dynamic LDS (the largest Student t or hyperbolic table of the batch) the batch kernel
-   may ask for: 64 KB less its static 8 KB gather list and claim slot. */
+   may ask for: 64 KB less its static 8 KB gather list. */
 constexpr size_t QM_BATCH_DYNAMIC_LDS_MAX = 65536 - 8192 - 256;
 
 enum BatchOp : uint32_t {
@@ -27,26 +26,24 @@ enum BatchOp : uint32_t {
     BOP_E64_PLAIN, BOP_E64_PAPER, BOP_E32_REFINE, BOP_T64, BOP_T32, BOP_H64, BOP_H32, BOP_E32_PLAIN,
 };
 
-/* Device block: header, then nreq BatchReq (then, with per-request
-   completion, nreq chunk counters). */
+/* Device block: header, then nreq BatchReq. */
 struct BatchHeader {
-    uint64_t counter;       /* next chunk to claim; 0 at launch */
     uint64_t total_chunks;
     uint32_t nreq;
     uint32_t reserved;
     uint64_t chunk;         /* elements per chunk */
     /* per-request completion (the serving loop), or both NULL: for a
-       request marked `flagged`, left[i] holds its unfinished chunks (its
-       chunk count at launch, in device memory) and done[i] is a
-       host-visible word, 0 at launch, that the workgroup finishing its last
-       chunk sets to 1 once every store of the request has reached memory */
-    uint32_t* left;
+       request with `flagged` chunks, count[i] in device memory, 0 at launch,
+       counts its finished ones; the workgroup finishing the last sets the
+       count back to 0 and the host-visible word done[i], 0 at launch, to 1,
+       once every store of the request has reached memory */
+    uint32_t* count;
     uint32_t* done;
 };
 
 struct BatchReq {
     uint32_t op;            /* BatchOp */
-    uint32_t flagged;       /* per-request completion: count this request's chunks and raise its flag */
+    uint32_t flagged;       /* per-request completion: the request's chunks (0: its batch completes it) */
     const void* in;
     void* out;
     uint64_t n;
@@ -57,6 +54,16 @@ struct BatchReq {
         HypParams H;        /* exp -> hyperbolic: table parameters (cells of the request's dtype) */
     };
 };
+
+/* A batch of at most BATCH_ARGS_MAX requests, and of no more chunks than the
+   launch has workgroups, travels in the kernel's arguments (4 KB at most):
+   no upload ordered before the launch. */
+constexpr uint32_t BATCH_ARGS_MAX = 16;
+struct BatchArgs {
+    BatchHeader h;
+    BatchReq r[BATCH_ARGS_MAX];
+};
+static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments");
 
 /* The allocation-free entry point's device array: one header and
    QM_BATCH_NOALLOC_MAX_REQUESTS records (768 KiB) per GPU. */
@@ -69,7 +76,8 @@ constexpr int BATCH_SCRATCH_MAX_DEVICES = 64;
 hipError_t batch_scratch_address(int device, void** out);
 
 StudentParams make_params(const TTableHeader& h, const TCells& c, const double* d_rows);
-hipError_t launch_batch(BatchHeader* d_hdr, const BatchReq* d_reqs, size_t lds_bytes, uint64_t blocks,
+hipError_t launch_batch(const BatchHeader* d_hdr, const BatchReq* d_reqs, size_t lds_bytes, uint64_t blocks,
                         hipStream_t s);
+hipError_t launch_batch_args(const BatchArgs& args, size_t lds_bytes, hipStream_t s);
 
 }  // namespace qm

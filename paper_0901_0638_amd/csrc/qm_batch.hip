@@ -1,18 +1,17 @@
 /*
- * qm_batch.hip -- one persistent launch over many requests of mixed kind,
+ * qm_batch.hip -- one launch over many requests of mixed kind,
  * dtype, mode and nu.
  *
  * Every request is cut into chunks of hdr->chunk elements; chunks are numbered
- * globally in request order (chunk_base = prefix sum).  Each workgroup
- * repeatedly claims the next chunk from a device counter, finds its request
- * by binary search over chunk_base, and evaluates it with the same
- * per-element functions as the single-request kernels, so every output is
- * bitwise identical to the single call's.  A chunk belongs to one request,
- * so the kind switch and the wave votes inside the maps are uniform across
- * the workgroup.  A Student t or hyperbolic chunk stages its table in LDS
- * unless the workgroup's previous chunk already did.  The loop ends when the counter
- * passes the last chunk, which every workgroup reaches without waiting on
- * any other.
+ * globally in request order (chunk_base = prefix sum).  Each workgroup starts
+ * with the chunk of its own index and goes on in steps of the grid, finds
+ * each chunk's request by its chunk_base, and evaluates it with the same walk
+ * and per-element functions as the single-request kernels, so every output is
+ * bitwise identical to the single call's.  A chunk
+ * belongs to one request, so the kind switch and the wave votes inside the
+ * maps are uniform across the workgroup.  A Student t or hyperbolic chunk
+ * stages its table in LDS unless the workgroup's previous chunk already did.
+ * Every workgroup reaches the end of its loop without waiting on another.
  */
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -31,12 +30,24 @@ namespace qm {
    doubles or four floats each), as the streaming kernels read them. */
 constexpr int BATCH_UNROLL = 2;
 
-/* Elements [begin, end) of one request by the whole workgroup, walked by
-   its four waves as the single-request kernels walk an array. */
-template <typename T, class Map>
-__device__ __forceinline__ void chunk_walk(const void* in, void* out, uint64_t begin, uint64_t end, const Map& map)
+/* Descriptors are read through the constant address space: uniform loads
+   into scalar registers, of memory that no launch writes while it runs. */
+typedef const __attribute__((address_space(4))) BatchReq* ReqPtr;
+
+__device__ __forceinline__ ReqPtr uniform_req(uint64_t addr)
 {
-    const Span<T> s = make_span((const T*)in + begin, (T*)out + begin, end - begin);
+    return (ReqPtr)wave_uniform(addr);
+}
+
+/* Elements [begin, end) of the request at `addr` by the whole workgroup,
+   walked by its four waves as the single-request kernels walk an array. */
+template <typename T, class Map>
+__device__ __forceinline__ void chunk_walk(uint64_t addr, uint64_t begin, uint64_t end, const Map& map)
+{
+    const ReqPtr R = uniform_req(addr);
+    begin = wave_uniform(begin);
+    end = wave_uniform(end);
+    const Span<T> s = make_span((const T*)R->in + begin, (T*)R->out + begin, end - begin);
     const uint32_t lane = wave_lane();
     Walk<T, BATCH_UNROLL> w;
     w.begin(s, wave_uniform(threadIdx.x >> 6), blockDim.x >> 6, lane);
@@ -48,129 +59,162 @@ extern __shared__ __attribute__((aligned(16))) double lds_tab[];
 
 /* One chunk per op.  Each is a separate, non-inlined function so that its
    constants and registers are its own: inlined together, the union of all
-   maps' loop-invariant constants would crowd the persistent loop. */
+   maps' loop-invariant constants would crowd the chunk loop.  A request's
+   table parameters are read from its descriptor inside (passed by value they
+   went through every lane's scratch memory). */
 template <typename T, class Op>
-static __device__ __noinline__ void chunk_op(const void* in, void* out, uint64_t begin, uint64_t end)
+static __device__ __noinline__ void chunk_op(uint64_t addr, uint64_t begin, uint64_t end)
 {
-    chunk_walk<T>(in, out, begin, end, ElementMap<T, Op>());
+    chunk_walk<T>(addr, begin, end, ElementMap<T, Op>());
 }
 
 /* LDS list of the hybrid quantiles' gather: 64 K elements per wave (K = 4
    FP64 or 8 FP32 per lane, two 16-byte vectors), 8 KB per workgroup of four
    waves. */
 constexpr int GATHER_DOUBLES_PER_WAVE = 64 * 4;
+__device__ __forceinline__ double* gather_list()
+{
+    static __shared__ double gather[4 * GATHER_DOUBLES_PER_WAVE];
+    return gather + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * GATHER_DOUBLES_PER_WAVE;
+}
 
 /* Hybrid quantile chunk (FP64 plain, FP32+refine): the streaming kernel's
    gather, so that the outer path runs once per 64 outer elements rather than
    on every lane of a wave holding one; bitwise the per-element function. */
 template <typename T, class H>
-static __device__ __noinline__ void chunk_hybrid(const void* in, void* out, uint64_t begin, uint64_t end, double* gather)
+static __device__ __noinline__ void chunk_hybrid(uint64_t addr, uint64_t begin, uint64_t end)
 {
-    T* buf = reinterpret_cast<T*>(gather + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * GATHER_DOUBLES_PER_WAVE);
-    chunk_walk<T>(in, out, begin, end, HybridMap<T, H>{buf, wave_lane()});
+    chunk_walk<T>(addr, begin, end, HybridMap<T, H>{reinterpret_cast<T*>(gather_list()), wave_lane()});
 }
 
 /* Student t from the table in LDS (referenced by symbol, so the loads stay
    LDS loads). */
 template <typename T, int DEG>
-static __device__ __noinline__ void chunk_t(const void* in, void* out, uint64_t begin, uint64_t end,
-                                            const StudentParams P)
+static __device__ __noinline__ void chunk_t(uint64_t addr, uint64_t begin, uint64_t end)
 {
-    chunk_walk<T>(in, out, begin, end, StudentMap<T, DEG>{lds_tab, P});
+    const StudentParams P = *(const StudentParams*)&uniform_req(addr)->P;
+    chunk_walk<T>(addr, begin, end, StudentMap<T, DEG>{lds_tab, P});
 }
 
 /* Exponential -> hyperbolic from the cells in LDS. */
 template <typename T, int DEG>
-static __device__ __noinline__ void chunk_h(const void* in, void* out, uint64_t begin, uint64_t end, const HypParams H)
+static __device__ __noinline__ void chunk_h(uint64_t addr, uint64_t begin, uint64_t end)
 {
-    chunk_walk<T>(in, out, begin, end, HypMap<T, DEG>{lds_tab, H});
+    const HypParams H = *(const HypParams*)&uniform_req(addr)->H;
+    chunk_walk<T>(addr, begin, end, HypMap<T, DEG>{lds_tab, H});
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_batch(BatchHeader* hdr, const BatchReq* __restrict__ reqs)
+/* Elements [begin, end) of the request R; *loaded: the table in LDS. */
+__device__ __forceinline__ void do_chunk(ReqPtr R, uint64_t begin, uint64_t end, const double** loaded)
 {
-    __shared__ uint64_t s_chunk;
-    __shared__ double gather[4 * GATHER_DOUBLES_PER_WAVE];
-    const double* loaded = nullptr;        /* table currently in LDS (uniform) */
-    const uint64_t total = hdr->total_chunks;
-    const uint64_t chunk = hdr->chunk;
-    const uint32_t nreq = hdr->nreq;
-    uint32_t* const left = hdr->left;
-    uint32_t* const done = hdr->done;
-    for (;;) {
-        if (threadIdx.x == 0) s_chunk = atomicAdd(reinterpret_cast<unsigned long long*>(&hdr->counter), 1ull);
-        __syncthreads();
-        const uint64_t c = s_chunk;
-        __syncthreads();
-        if (c >= total) break;
-        /* last request with chunk_base <= c (every listed request has chunks) */
-        uint32_t lo = 0, hi = nreq - 1;
-        while (lo < hi) {
-            uint32_t mid = (lo + hi + 1) >> 1;
-            if (reqs[mid].chunk_base <= c) lo = mid; else hi = mid - 1;
-        }
-        const BatchReq& R = reqs[lo];
-        const uint64_t begin = (c - R.chunk_base) * chunk;
-        const uint64_t end = begin + chunk < R.n ? begin + chunk : R.n;
-        switch (R.op) {
-        case BOP_NQ64_PLAIN: chunk_hybrid<double, HybridNQ64>(R.in, R.out, begin, end, gather); break;
-        case BOP_NQ64_PAPER: chunk_op<double, OpNQ64Paper>(R.in, R.out, begin, end); break;
-        case BOP_NQ32_REFINE: chunk_hybrid<float, HybridNQ32>(R.in, R.out, begin, end, gather); break;
-        case BOP_NQ32_PAPER: chunk_op<float, OpNQ32Paper>(R.in, R.out, begin, end); break;
-        case BOP_NQ32_PLAIN: chunk_op<float, OpNQ32Plain>(R.in, R.out, begin, end); break;
-        case BOP_E64_PLAIN: chunk_op<double, OpE64Plain>(R.in, R.out, begin, end); break;
-        case BOP_E64_PAPER: chunk_op<double, OpE64Paper>(R.in, R.out, begin, end); break;
-        case BOP_E32_REFINE: chunk_op<float, OpE32Refine>(R.in, R.out, begin, end); break;
-        case BOP_E32_PLAIN: chunk_op<float, OpE32Plain>(R.in, R.out, begin, end); break;
-        case BOP_T64:
-        case BOP_T32: {
-            if (R.P.identity) {
-                if (R.op == BOP_T64) chunk_op<double, OpCopy<double>>(R.in, R.out, begin, end);
-                else chunk_op<float, OpCopy<float>>(R.in, R.out, begin, end);
-                break;
-            }
-            if (loaded != R.coef) {
-                __syncthreads();
-                stage_table(lds_tab, R.coef, R.P);
-                __syncthreads();
-                loaded = R.coef;
-            }
-            if (R.op == BOP_T64) {
-                if (R.P.row_shift == 4) chunk_t<double, T_DEGREE_HIGH>(R.in, R.out, begin, end, R.P);
-                else chunk_t<double, T_DEGREE_LOW>(R.in, R.out, begin, end, R.P);
-            }
-            else chunk_t<float, T_DEGREE_F32>(R.in, R.out, begin, end, R.P);
-            break;
-        }
-        case BOP_H64:
-        case BOP_H32: {
-            if (loaded != R.H.r.gcoef) {
-                __syncthreads();
-                if (R.op == BOP_H64) stage_hyp<HYP_DEGREE>(lds_tab, R.H);
-                else stage_hyp<HYP_DEGREE_F32>(lds_tab, R.H);
-                __syncthreads();
-                loaded = R.H.r.gcoef;
-            }
-            if (R.op == BOP_H64) chunk_h<double, HYP_DEGREE>(R.in, R.out, begin, end, R.H);
-            else chunk_h<float, HYP_DEGREE_F32>(R.in, R.out, begin, end, R.H);
-            break;
-        }
-        default:
-            break;
-        }
-        if (done && R.flagged) {
-            /* per-request completion: each thread's stores of the chunk
-               reach device scope before the workgroup counts the chunk;
-               the workgroup that counts a request's last chunk raises its
-               host-visible flag (release at system scope).  Only requests
-               of a few chunks are flagged: the fence writes back the L2,
-               too dear for every chunk of a large batch */
-            __threadfence();
+    const uint64_t addr = (uint64_t)R;
+    const uint32_t op = R->op;
+    if (op == BOP_T64 || op == BOP_T32) {
+        const StudentParams P = *(const StudentParams*)&R->P;
+        if (!P.identity && *loaded != P.gcoef) {
+            stage_table(lds_tab, P.gcoef, P);
             __syncthreads();
-            if (threadIdx.x == 0 &&
-                __hip_atomic_fetch_add(left + lo, ~0u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == 1u)
-                __hip_atomic_store(done + lo, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            *loaded = P.gcoef;
+        }
+    } else if (op == BOP_H64 || op == BOP_H32) {
+        const HypParams H = *(const HypParams*)&R->H;
+        if (*loaded != H.r.gcoef) {
+            if (op == BOP_H64) stage_hyp<HYP_DEGREE>(lds_tab, H);
+            else stage_hyp<HYP_DEGREE_F32>(lds_tab, H);
+            __syncthreads();
+            *loaded = H.r.gcoef;
         }
     }
+    switch (op) {
+    case BOP_NQ64_PLAIN: chunk_hybrid<double, HybridNQ64>(addr, begin, end); break;
+    case BOP_NQ64_PAPER: chunk_op<double, OpNQ64Paper>(addr, begin, end); break;
+    case BOP_NQ32_REFINE: chunk_hybrid<float, HybridNQ32>(addr, begin, end); break;
+    case BOP_NQ32_PAPER: chunk_op<float, OpNQ32Paper>(addr, begin, end); break;
+    case BOP_NQ32_PLAIN: chunk_op<float, OpNQ32Plain>(addr, begin, end); break;
+    case BOP_E64_PLAIN: chunk_op<double, OpE64Plain>(addr, begin, end); break;
+    case BOP_E64_PAPER: chunk_op<double, OpE64Paper>(addr, begin, end); break;
+    case BOP_E32_REFINE: chunk_op<float, OpE32Refine>(addr, begin, end); break;
+    case BOP_E32_PLAIN: chunk_op<float, OpE32Plain>(addr, begin, end); break;
+    case BOP_T64:
+        if (R->P.identity) chunk_op<double, OpCopy<double>>(addr, begin, end);
+        else if (R->P.row_shift == 4) chunk_t<double, T_DEGREE_HIGH>(addr, begin, end);
+        else chunk_t<double, T_DEGREE_LOW>(addr, begin, end);
+        break;
+    case BOP_T32:
+        if (R->P.identity) chunk_op<float, OpCopy<float>>(addr, begin, end);
+        else chunk_t<float, T_DEGREE_F32>(addr, begin, end);
+        break;
+    case BOP_H64: chunk_h<double, HYP_DEGREE>(addr, begin, end); break;
+    case BOP_H32: chunk_h<float, HYP_DEGREE_F32>(addr, begin, end); break;
+    default: break;
+    }
+}
+
+/*
+ * A workgroup's chunks: that of its own index and every gridDim.x-th after
+ * it.  (Claimed from a device counter, the claims are a serial chain through
+ * one memory word: 12 ns each on an idle MI355X and 58 beside the streams, so
+ * that 4600 claims took as long as their chunks' work and smaller chunks only
+ * more; 512 requests of 2^10..2^20 elements: 270 us a pass with claims, 186
+ * without, in smaller chunks.)  The request of a chunk is the last one with chunk_base <= c
+ * (every listed request has chunks), found 64 candidates at a time, one per
+ * lane: two dependent loads for 4096 requests where a binary search took
+ * twelve.
+ */
+__device__ __forceinline__ void batch_chunks(uint64_t total, uint32_t nreq, uint64_t chunk, ReqPtr reqs, uint32_t* count,
+                                             uint32_t* done)
+{
+    const uint32_t lane = wave_lane();
+    const double* loaded = nullptr;        /* table currently in LDS (uniform) */
+    for (uint64_t c = blockIdx.x; c < total; c += gridDim.x) {
+        uint32_t lo = 0, len = nreq;
+        while (len > 1) {
+            const uint32_t stride = (len + 63) >> 6, i = lane * stride;
+            const bool le = i < len && reqs[lo + i].chunk_base <= c;
+            const uint32_t skip = ((uint32_t)__popcll(__ballot(le)) - 1) * stride;
+            lo += skip;
+            len = min(stride, len - skip);
+        }
+        const ReqPtr R = reqs + lo;
+        const uint64_t begin = (c - R->chunk_base) * chunk, n = R->n;
+        const uint64_t end = begin + chunk < n ? begin + chunk : n;
+        if (c != blockIdx.x) __syncthreads();      /* every wave is done with the LDS */
+        do_chunk(R, begin, end, &loaded);
+        if (done && R->flagged) {
+            /* per-request completion: every wave's stores of the chunk have
+               reached the XCD's L2 before the barrier, one thread's release
+               then writes that back and counts the chunk; the workgroup
+               that counts a request's last chunk raises its host-visible
+               flag (release at system scope) */
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                __threadfence();
+                if (__hip_atomic_fetch_add(count + lo, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u ==
+                    R->flagged) {
+                    __hip_atomic_store(count + lo, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(done + lo, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+                }
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_batch(const BatchHeader* hdr, const BatchReq* reqs)
+{
+    typedef const __attribute__((address_space(4))) BatchHeader* HdrPtr;
+    const HdrPtr h = (HdrPtr)(uint64_t)hdr;
+    batch_chunks(h->total_chunks, h->nreq, h->chunk, (ReqPtr)(uint64_t)reqs, h->count, h->done);
+}
+
+/* The batch in the kernel's arguments: read from the argument segment, which
+   starts with them (indexing the parameter would copy it to scratch). */
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_batch_args(BatchArgs)
+{
+    typedef const __attribute__((address_space(4))) BatchArgs* ArgsPtr;
+    const ArgsPtr a = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    batch_chunks(a->h.total_chunks, a->h.nreq, a->h.chunk, a->r, a->h.count, a->h.done);
 }
 
 /*
@@ -204,9 +248,15 @@ hipError_t batch_scratch_address(int device, void** out)
     return hipSuccess;
 }
 
-hipError_t launch_batch(BatchHeader* d_hdr, const BatchReq* d_reqs, size_t lds_bytes, uint64_t blocks, hipStream_t s)
+hipError_t launch_batch(const BatchHeader* d_hdr, const BatchReq* d_reqs, size_t lds_bytes, uint64_t blocks, hipStream_t s)
 {
     hipLaunchKernelGGL(k_batch, dim3((unsigned)blocks), dim3(256), lds_bytes, s, d_hdr, d_reqs);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_args(const BatchArgs& args, size_t lds_bytes, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_batch_args, dim3((unsigned)args.h.total_chunks), dim3(256), lds_bytes, s, args);
     return hipGetLastError();
 }
 

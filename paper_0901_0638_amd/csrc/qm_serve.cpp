@@ -4,7 +4,7 @@
  *
  * Batch: requests are validated, Student t tables fetched (built on first
  * use), descriptors written into a pinned staging buffer, copied to the
- * device on the caller's stream and consumed by one persistent launch
+ * device on the caller's stream and consumed by one launch
  * (qm_batch.hip).  Staging slots are reused once the event recorded after
  * their launch has completed.
  *
@@ -42,26 +42,37 @@ namespace qm {
 /* Batch runner                                                             */
 /* ------------------------------------------------------------------------ */
 
-/* Per-request completion costs the workgroups of a flagged request an L2
-   write-back per chunk, so only requests of at most eight chunks are
-   flagged (measured: flagging every chunk slowed the batch kernel enough
-   that the 50k requests/s trace fell behind its arrivals); larger ones
-   dominate their batch's time anyway and complete with its event. */
+/* Per-request completion costs every chunk of a flagged request an L2
+   write-back and a count, 64 ns each beside the streams and one after the
+   other (MI355X: 1100 flagged chunks took 80 us where the batch's work takes
+   14).  So only requests of at most sixteen chunks are flagged, and as many
+   of a batch's, in order, as add two hundredths to its time at about 350 G
+   elements/s: one chunk for each 2^20 elements (with one for each 2^18 the
+   p99 at 50k requests/s was 0.35 ms, 0.26 with few).  The others complete with the
+   batch's event; so does a whole batch of under 2^24 elements, which is over
+   some tens of microseconds after its first request. */
+constexpr uint64_t FLAG_MIN_ELEMENTS = 1 << 24, FLAG_ELEMENTS_PER_CHUNK = 1 << 20;
 static uint64_t batch_flag_chunks()
 {
     /* tuning: QM_SERVE_FLAG_CHUNKS overrides the limit (0: completion by
        batch only) */
     static const uint64_t v = [] {
         const char* e = getenv("QM_SERVE_FLAG_CHUNKS");
-        return e ? (uint64_t)strtoull(e, nullptr, 10) : (uint64_t)8;
+        return e ? (uint64_t)strtoull(e, nullptr, 10) : (uint64_t)16;
     }();
     return v;
 }
+
+/* Requests per batch that get a completion flag (a batch with more relies
+   on its event alone); one host-coherent array of this many words per
+   serving stream, and one of counts per staging slot. */
+constexpr size_t SERVE_FLAGS = 4096;
 
 struct Staging {
     void* host = nullptr;
     void* dev = nullptr;
     size_t cap = 0;
+    uint32_t* count = nullptr; /* per-request chunk counts: SERVE_FLAGS words, all 0 between launches */
     hipEvent_t ev = nullptr;
     bool busy = false;         /* held by a caller between acquire and event record */
 };
@@ -90,15 +101,16 @@ void runner_free(qm_ctx* ctx)
         }
         if (s->host) (void)hipHostFree(s->host);
         if (s->dev) (void)hipFree(s->dev);
+        if (s->count) (void)hipFree(s->count);
         delete s;
     }
     delete r;
     ctx->runner = nullptr;
 }
 
-/* A staging slot with at least `bytes` of pinned host and device memory
-   whose previous use has completed. */
-static qm_status acquire_slot(BatchRunner* br, size_t bytes, Staging** out)
+/* A staging slot with at least `bytes` of pinned host and device memory, and
+   with zeroed chunk counts if asked for, whose previous use has completed. */
+static qm_status acquire_slot(BatchRunner* br, size_t bytes, bool counts, Staging** out)
 {
     std::unique_lock<std::mutex> lk(br->mu);
     Staging* slot = nullptr;
@@ -152,6 +164,17 @@ static qm_status acquire_slot(BatchRunner* br, size_t bytes, Staging** out)
         }
         slot->cap = cap;
     }
+    if (counts && !slot->count) {
+        static const uint32_t zero[SERVE_FLAGS] = {};
+        if (hipMalloc((void**)&slot->count, sizeof zero) != hipSuccess ||
+            hipMemcpy(slot->count, zero, sizeof zero, hipMemcpyHostToDevice) != hipSuccess) {
+            if (slot->count) (void)hipFree(slot->count);
+            slot->count = nullptr;
+            std::lock_guard<std::mutex> g(br->mu);
+            slot->busy = false;
+            return set_error(QM_E_NOMEM, "staging allocation failed");
+        }
+    }
     *out = slot;
     return QM_OK;
 }
@@ -174,25 +197,38 @@ static uint32_t batch_op(const qm_request& r)
     }
 }
 
-/* Chunk size of a batch of total_n elements: about 4 chunks for each of the
-   cus x 8 workgroups, within [chunk_floor, QM_CHUNK_MAX], a multiple of
-   QM_CHUNK_MIN. */
+/* Chunk size of a batch of total_n elements: about BATCH_ROUNDS chunks for
+   each of the cus x 4 workgroups that the GPU holds at once, within
+   [chunk_floor, QM_CHUNK_MAX], a multiple of QM_CHUNK_MIN.  Fewer, larger
+   chunks leave the last of them running alone, more pay the start of a
+   chunk (descriptor, table, first loads) too often: 512 requests of
+   2^10..2^20 elements take 195 us a pass with 4 rounds, 186 with 8, 201 with
+   16; 4096 requests of 2^10..2^22 elements 5.13 ms in chunks of 16384, 5.39 of
+   32768, 5.29 of 8192.  A lone request is spread over the whole GPU: of 2^15 elements it took
+   30 us in one chunk of that size, and takes 6 in sixteen. */
+constexpr uint64_t BATCH_ROUNDS = 8;
 static uint64_t batch_chunk(uint64_t total_n, int cus)
 {
     static const uint64_t chunk_floor = [] {
-        /* tuning: lower bound of the chunk size.  Default QM_CHUNK_MAX:
-           measured on the serving trace, smaller chunks (2048..8192) cut
-           the p50 latency of lone small requests but raised p99 and the
-           latency under load (per-chunk claim and call overhead) */
+        /* tuning: lower bound of the chunk size */
         const char* e = getenv("QM_BATCH_CHUNK_MIN");
-        uint64_t v = e ? strtoull(e, nullptr, 10) : QM_CHUNK_MAX;
+        uint64_t v = e ? strtoull(e, nullptr, 10) : QM_CHUNK_MIN;
         v = (v / QM_CHUNK_MIN) * QM_CHUNK_MIN;
         return v < QM_CHUNK_MIN ? QM_CHUNK_MIN : (v > QM_CHUNK_MAX ? QM_CHUNK_MAX : v);
     }();
-    const uint64_t blocks_max = (uint64_t)cus * 8;
-    uint64_t chunk = total_n / (blocks_max * 4);
+    uint64_t chunk = total_n / ((uint64_t)cus * 4 * BATCH_ROUNDS);
     chunk = (chunk / QM_CHUNK_MIN) * QM_CHUNK_MIN;
     return chunk < chunk_floor ? chunk_floor : (chunk > QM_CHUNK_MAX ? QM_CHUNK_MAX : chunk);
+}
+
+static uint64_t batch_blocks(const qm_ctx* ctx, uint64_t chunks)
+{
+    /* a workgroup per chunk up to 1024 per compute unit: the hardware hands
+       the next one to whichever unit is free, which evens out chunks of
+       different kinds (512 requests of 2^10..2^20 elements: 186 us a pass,
+       198 with 8 per unit; 4096 of 2^10..2^22: 5.13 ms, 5.28 with 64) */
+    uint64_t blocks = (uint64_t)ctx->cus * 1024;
+    return blocks > chunks ? chunks : blocks;
 }
 
 /*
@@ -249,7 +285,6 @@ static qm_status plan_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count,
     }
     if (lds > QM_BATCH_DYNAMIC_LDS_MAX) return set_error(QM_E_INVAL, "table larger than the LDS a launch may use");
     memset(h, 0, sizeof *h);
-    h->counter = 0;
     h->total_chunks = chunks;
     h->nreq = nreq;
     h->chunk = chunk;
@@ -269,14 +304,22 @@ static qm_status validate_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t co
     return QM_OK;
 }
 
-static uint64_t batch_blocks(const qm_ctx* ctx, uint64_t chunks)
+/* Whether a planned batch travels in the kernel's arguments. */
+static bool fits_args(const qm_ctx* ctx, const BatchHeader& h)
 {
-    uint64_t blocks = (uint64_t)ctx->cus * 8;
-    return blocks > chunks ? chunks : blocks;
+    return h.nreq <= BATCH_ARGS_MAX && h.total_chunks <= (uint64_t)ctx->cus * 8;
+}
+
+static hipError_t launch_in_args(const BatchHeader& h, const BatchReq* reqs, size_t lds, hipStream_t s)
+{
+    BatchArgs a;
+    a.h = h;
+    memcpy(a.r, reqs, h.nreq * sizeof(BatchReq));
+    return launch_batch_args(a, lds, s);
 }
 
 /*
- * Validate and enqueue `count` requests as one persistent launch on s.  If
+ * Validate and enqueue `count` requests as one launch on s.  If
  * done is not NULL, an event that completes with the launch is recorded
  * into it (the caller owns the event).
  */
@@ -298,30 +341,46 @@ qm_status enqueue_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count, hip
         if (done && hipEventRecord(done, s) != hipSuccess) return set_error(QM_E_HIP, "hipEventRecord failed");
         return QM_OK;
     }
-    const size_t reqs_bytes = sizeof(BatchHeader) + d.size() * sizeof(BatchReq);
-    size_t bytes = reqs_bytes + (flags ? d.size() * sizeof(uint32_t) : 0);
+    const bool in_args = fits_args(ctx, h);
+    if (flags) {
+        uint64_t total = 0, budget = 0;
+        for (const BatchReq& r : d) total += r.n;
+        budget = total < FLAG_MIN_ELEMENTS ? 0 : total / FLAG_ELEMENTS_PER_CHUNK;
+        bool any = false;
+        for (BatchReq& r : d) {
+            const uint64_t c = (r.n + h.chunk - 1) / h.chunk;
+            if (c > batch_flag_chunks() || c > budget) continue;
+            budget -= c;
+            r.flagged = (uint32_t)c;
+            any = true;
+        }
+        if (!any) flags = nullptr;
+    }
+    const size_t bytes = sizeof(BatchHeader) + d.size() * sizeof(BatchReq);
+    if (in_args && !flags) {
+        hipError_t e = launch_in_args(h, d.data(), lds, s);
+        if (e != hipSuccess) return set_error(QM_E_HIP, hipGetErrorString(e));
+        if (done && hipEventRecord(done, s) != hipSuccess) return set_error(QM_E_HIP, "hipEventRecord failed");
+        return QM_OK;
+    }
     Staging* slot = nullptr;
-    st = acquire_slot(runner_of(ctx), bytes, &slot);
+    st = acquire_slot(runner_of(ctx), in_args ? 0 : bytes, flags != nullptr, &slot);
     if (st != QM_OK) return st;
     if (flags) {
-        /* the chunk counters follow the descriptors; requests of at most
-           batch_flag_chunks() chunks are flagged, the others complete with
-           the batch */
-        uint32_t* left = reinterpret_cast<uint32_t*>((char*)slot->host + reqs_bytes);
-        for (size_t i = 0; i < d.size(); ++i) {
-            const uint64_t c = (d[i].n + h.chunk - 1) / h.chunk;
-            left[i] = (uint32_t)c;
-            d[i].flagged = c <= batch_flag_chunks();
-        }
-        h.left = reinterpret_cast<uint32_t*>((char*)slot->dev + reqs_bytes);
+        h.count = slot->count;
         h.done = flags;
     }
-    memcpy(slot->host, &h, sizeof h);
-    memcpy((char*)slot->host + sizeof h, d.data(), d.size() * sizeof(BatchReq));
-    hipError_t e = hipMemcpyAsync(slot->dev, slot->host, bytes, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess)
-        e = launch_batch((BatchHeader*)slot->dev, (const BatchReq*)((char*)slot->dev + sizeof h), lds,
-                         batch_blocks(ctx, h.total_chunks), s);
+    hipError_t e;
+    if (in_args) {
+        e = launch_in_args(h, d.data(), lds, s);
+    } else {
+        memcpy(slot->host, &h, sizeof h);
+        memcpy((char*)slot->host + sizeof h, d.data(), d.size() * sizeof(BatchReq));
+        e = hipMemcpyAsync(slot->dev, slot->host, bytes, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess)
+            e = launch_batch((const BatchHeader*)slot->dev, (const BatchReq*)((char*)slot->dev + sizeof h), lds,
+                             batch_blocks(ctx, h.total_chunks), s);
+    }
     hipError_t e2 = hipEventRecord(slot->ev, s);
     {
         std::lock_guard<std::mutex> g(runner_of(ctx)->mu);
@@ -366,12 +425,17 @@ qm_status enqueue_batch_noalloc(qm_ctx* ctx, const qm_request* reqs, uint64_t co
     });
     if (st != QM_OK) return st;
     if (k == 0) return QM_OK;
+    if (fits_args(ctx, h)) {
+        e = launch_in_args(h, staged, lds, s);
+        if (e != hipSuccess) return set_error(QM_E_HIP, hipGetErrorString(e));
+        return QM_OK;
+    }
     memcpy(ctx->noalloc_host, &h, sizeof h);
     const size_t bytes = sizeof(BatchHeader) + k * sizeof(BatchReq);
     e = hipMemcpyAsync(ctx->noalloc_dev, ctx->noalloc_host, bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipEventRecord(ctx->noalloc_ev, s);
     if (e == hipSuccess)
-        e = launch_batch(static_cast<BatchHeader*>(ctx->noalloc_dev),
+        e = launch_batch(static_cast<const BatchHeader*>(ctx->noalloc_dev),
                          reinterpret_cast<const BatchReq*>(static_cast<char*>(ctx->noalloc_dev) + sizeof h), lds,
                          batch_blocks(ctx, h.total_chunks), s);
     if (e != hipSuccess) return set_error(QM_E_HIP, hipGetErrorString(e));
@@ -414,11 +478,6 @@ struct InFlight {
 };
 
 constexpr int SERVE_STREAMS = 4;
-/* Requests per batch that get a completion flag (a batch with more relies
-   on its event alone); one host-coherent array of this many words per
-   stream. */
-constexpr size_t SERVE_FLAGS = 4096;
-
 struct Server {
     qm_ctx* ctx = nullptr;
     std::thread th;

@@ -34,7 +34,7 @@ int ctx_device(const qm_ctx* ctx);
 uint64_t ctx_budget(const qm_ctx* ctx);
 qm_status set_error(qm_status s, const char* msg);
 
-/* Validate and enqueue requests as one persistent launch (done: optional
+/* Validate and enqueue requests as one launch (done: optional
    event recorded after it).  flags, if not NULL, is a host-coherent array
    with a zero word for each request with n > 0, in request order: the
    launch sets a request's word to 1 once its output is complete. */
