@@ -68,10 +68,10 @@ enum qm_dtype { QM_F32 = 0, QM_F64 = 1 };
  *                  2e-15 of Phi^{-1} (absolute 2e-18 where |w| < 1e-3) on the
  *                  whole double range.  F32: the FP64 evaluation rounded to
  *                  float.
- *   QM_F32_REFINE  dtype QM_F32 only: FP32 rational seed plus one FP64
- *                  correction step against an FP64 erf (|u - 1/2| <= 0.45)
- *                  or erfc (beyond); relative error within 2e-7 (absolute
- *                  2e-10 near 0).
+ *   QM_F32_REFINE  dtype QM_F32 only: FP64 rationals of lower degree than
+ *                  QM_PLAIN's, rounded once; relative error within 2e-7
+ *                  (absolute 2e-10 near 0), and within 3.4e-9 of the exact
+ *                  value before the rounding.
  *   QM_PAPER       the paper's constants verbatim, valid only on the paper's
  *                  domain: F64 the (13,13) rational of Section 7.2 / Appendix
  *                  B (v <= 42, u >= 2.875e-19), F32 the (5,6) rational of

@@ -33,6 +33,14 @@ These approximations are fitted here, the rest are the paper's constants:
     (the residual's error divided by phi(z), relative to z) and
     1.1e-3 x 2.6e-6 from G, before its rounding to FP32 (half an ulp,
     6e-8): within the form's 2e-7.
+  * FP32 in and out, evaluated in FP64 and rounded once (QM_F32_REFINE of the
+    quantile and of exponential -> normal).  A rational of lower degree in
+    FP64 is both more accurate and a third to a half of the instructions of
+    the pieces above (an FP32 seed and one FP64 correction step), whose
+    constants remain as the form they describe is still checked.  Central:
+    q P4(r)/Q4(r) for |q| <= 0.45, r = 0.2025 - q^2.  Outer: v = -log 2p with
+    log m a degree-9 polynomial on [1/2, 1], then z = P7(v)/Q6(v) down to the
+    smallest FP32 p.  Exponential -> normal: z = v P10(v)/Q10(v), v <= 103.
   * The FP64 logarithm of the change of variable v = -log(2 min(u,1-u)):
     log m = 2 atanh f = 2f + f s R6(s), f = (m-1)/(m+1), s = f^2, for the
     reduced argument m in [sqrt(1/2), sqrt(2)] (so s <= 0.0294).
@@ -173,6 +181,68 @@ def carr(name, coeffs, comment):
     return "/* %s */\nstatic constexpr double %s[%d] = {\n%s\n};\n" % (comment, name, len(coeffs), body)
 
 
+def fit_log_abs(a, b, deg, nodes=120, rounds=40):
+    """Polynomial in (m - (a + b)/2) minimising max |p - log m| on [a, b]."""
+    mid = (a + b) / 2
+    xs = cheb_nodes(a, b, nodes)
+    fs = [mp.log(x) for x in xs]
+    w = [mp.mpf(1)] * nodes
+    best = None
+    for _ in range(rounds):
+        rows = [[mp.sqrt(w[i]) * (x - mid) ** j for j in range(deg + 1)] for i, x in enumerate(xs)]
+        c = mp.qr_solve(mp.matrix(rows), mp.matrix([mp.sqrt(w[i]) * fs[i] for i in range(nodes)]))[0]
+        coef = [c[j] for j in range(deg + 1)]
+        errs = [mp.polyval(coef[::-1], x - mid) - f for x, f in zip(xs, fs)]
+        mx = max(abs(e) for e in errs)
+        if best is None or mx < best[0]:
+            best = (mx, coef)
+        w = [w[i] * abs(errs[i]) for i in range(nodes)]
+        sw = sum(w)
+        w = [wi / sw * nodes for wi in w]
+    coef = best[1]
+    cr = [mp.mpf(float(x)) for x in coef]
+    dense = [a + (b - a) * k / 1500 for k in range(1501)]
+    return coef, max(abs(mp.polyval(cr[::-1], x - mid) - mp.log(x)) for x in dense)
+
+
+def fit_direct(g, r_lo, X):
+    """The pieces of the FP32 forms that are evaluated in FP64 (g: the central
+    piece's w/q in r, on [r_lo, X])."""
+    out = []
+    xs = cheb_nodes(r_lo, X, 160)
+    _, p, q = fit_rational(xs, [g(x) for x in xs], 4, 4)
+    dense = [r_lo + (X - r_lo) * k / 1500 for k in range(1501)]
+    e = rounded_error(p, q, dense, [g(x) for x in dense])
+    print("FP32 central (4,4): max rel %.3e" % e, file=sys.stderr)
+    out.append(carr("QM_D32_CP", p, "Phi^{-1}(1/2 + q)/q numerator in r = 0.2025 - q^2, FP32 form; rel err %.2e" % e))
+    out.append(carr("QM_D32_CQ", q, "its denominator (constant term 1)"))
+
+    coef, e = fit_log_abs(mp.mpf("0.5"), mp.mpf(1), 9)
+    print("FP32 log (9): max abs %.3e" % e, file=sys.stderr)
+    out.append(carr("QM_D32_LOG", coef, "log m in m - 3/4, 1/2 <= m <= 1; abs err %.2e" % e))
+
+    lo, hi = mp.log(-mp.log(2 * mp.mpf("0.0501"))), mp.log(mp.mpf("103.3"))
+    span = lambda n: [mp.exp(t) for t in cheb_nodes(lo, hi, n)]
+    xs = span(160)
+    _, p, q = fit_rational(xs, [q_exp(v) for v in xs], 7, 6)
+    dense = span(1501)
+    e = rounded_error(p, q, dense, [q_exp(v) for v in dense])
+    print("FP32 outer (7,6): max rel %.3e" % e, file=sys.stderr)
+    out.append(carr("QM_D32_OP", p, "Q(v) numerator in v, 2.3 <= v <= 103.3, FP32 form; rel err %.2e" % e))
+    out.append(carr("QM_D32_OQ", q, "its denominator (constant term 1)"))
+
+    f = lambda v: q_exp(v) / v if v > mp.mpf(10) ** -20 else mp.sqrt(mp.pi / 2)
+    span = lambda n: [mp.exp(t) - 1 for t in cheb_nodes(0, mp.log(mp.mpf("104.2")), n)]
+    xs = span(200)
+    _, p, q = fit_rational(xs, [f(v) for v in xs], 10, 10)
+    dense = span(1501)
+    e = rounded_error(p, q, dense, [f(v) for v in dense])
+    print("FP32 exp -> normal (10,10): max rel %.3e" % e, file=sys.stderr)
+    out.append(carr("QM_E32_P", p, "Q(v)/v numerator in v, v <= 103.2, FP32 exp -> normal; rel err %.2e" % e))
+    out.append(carr("QM_E32_Q", q, "its denominator (constant term 1)"))
+    return out
+
+
 def main():
     mp.mp.dps = 40
     out = []
@@ -266,6 +336,8 @@ def main():
     coef, e_g = fit_poly(lambda y: mp.sqrt(2 * mp.pi) * mp.exp(y / 2), mp.mpf(0), Y, 3)
     print("central 1/phi G3: max rel %.3e" % e_g, file=sys.stderr)
     out.append(carr("QM_C32_G", coef, "1/phi(z) = sqrt(2 pi) e^{y/2} in y = z^2 <= %.4f; rel err %.2e" % (float(Y), e_g)))
+
+    out += fit_direct(g, r_lo, X)
 
     # --- FP64 log kernel: R6(s) ----------------------------------------------
     coef, e_log = fit_log_poly(6)

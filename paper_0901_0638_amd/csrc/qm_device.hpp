@@ -291,20 +291,11 @@ __device__ __forceinline__ float neg_log_f32(float x)
     return __builtin_fmaf(-l2, LN2F, sub ? 32.0f * LN2F : 0.0f);
 }
 
-/* FP32 seed of Q(v) = v P4(v)/Q5(v), relative error ~1.2e-5 on v <= 103.3 */
-__device__ __forceinline__ float expcoord_seed_f32(float v)
-{
-    float num = v * hornerf_d(v, QM_SEED_P);
-    float den = hornerf_d(v, QM_SEED_Q);
-    return num * __builtin_amdgcn_rcpf(den);
-}
-
-/* e^a for |a| <= 700 for the correction steps: a = k ln2 + r,
-   |r| <= ln2/2, the degree-DEG Taylor polynomial in r, then scale by 2^k.
-   Relative error below the remainder (ln2/2)^(DEG+1)/(DEG+1)!: 7e-12 for
-   degree 9, 5.3e-9 for degree 7. */
+/* e^a for a <= 700: a = k ln2 + r, |r| <= ln2/2, the degree-DEG Taylor
+   polynomial in r, then scale by 2^k.  Relative error below the remainder
+   (ln2/2)^(DEG+1)/(DEG+1)!: 2e-16 for degree 12. */
 template <int DEG>
-__device__ __forceinline__ double exp_refine(double a)
+__device__ __forceinline__ double exp_taylor(double a)
 {
     const double LOG2E = 1.4426950408889634074, LN2_HI = 0.69314718055994528623, LN2_LO = 2.3190468138462996154e-17;
     double k = __builtin_rint(a * LOG2E);
@@ -323,8 +314,8 @@ __device__ __forceinline__ double exp_refine(double a)
 }
 
 /* a / b to ~3e-15 for positive b of moderate size: hardware reciprocal and
-   one Newton step, no residual correction (enough for the correction step's
-   1e-11 needs). */
+   one Newton step, no residual correction (enough before a rounding to
+   FP32). */
 __device__ __forceinline__ double div_pos_fast(double a, double b)
 {
     double y = __builtin_amdgcn_rcp(b);
@@ -334,81 +325,44 @@ __device__ __forceinline__ double div_pos_fast(double a, double b)
 }
 
 /*
- * One Halley correction of x0 ~ z >= 0 solving q(z) = p, q(z) = 1 - Phi(z),
- * against an FP64 erfc written as erfc(z/sqrt2) = 2 phi(z) M(z) with the
- * Mills ratio M from a fitted rational (relative 1.1e-12 on [0, 14.5]).
- * With G(x) = q(x) - p = phi(x) t, t = M(x) - p/phi(x), G' = -phi, G'' = x phi:
- *   Halley:  x1 = x0 + t / (1 - x0 t / 2) ~ x0 + t (1 + x0 t / 2)
- * (the expansion drops O(x0^2 t^3), below 1e-10 relative for a 1e-5 seed).
- * The caller supplies p/phi(x0), formed so that it stays in range.
+ * The FP32+refine form: FP32 in and out, every step in FP64, rounded once.
+ * FP64 fused multiply-adds issue at the FP32 rate on gfx950 (4.4-5 cycles a
+ * wave against 4.2, packed FP32 off), so what counts is their number, and a
+ * rational fitted to the accuracy that the rounding leaves room for takes
+ * fewer than an FP32 seed with an FP64 correction step against erf or erfc,
+ * which evaluates two or three functions for one: 21 issue slots against 28
+ * for the central piece, 42 against 71 for the outer one, 33 against 69 for
+ * exponential -> normal.  It is also closer to the exact value before the
+ * rounding: 2.8e-9, 3.2e-9 and 1e-11 relative, against 2.5e-8, 1.5e-8 and
+ * 1e-11 absolute.  MI355X, per pass: 2^24 exponential -> normal 39.4 -> 29.0
+ * us, 2^26 mixture quantiles 106 -> 102, 2^26 fused quantiles 98.3 -> 94.4
+ * (all bound by vector instructions before).
  */
-template <int NP, int NQ>
-__device__ __forceinline__ double halley_upper(double x0, double p_over_phi, const double (&MP)[NP],
-                                               const double (&MQ)[NQ])
-{
-    double M = div_pos_fast(horner(x0, MP), horner(x0, MQ));
-    double t = M - p_over_phi;
-    double h = 0.5 * x0 * t;
-    return __builtin_fma(t, 1.0 + h, x0);
-}
 
-/* One Newton correction of x0 ~ z >= 0 solving q(z) = p (notation as for
- * halley_upper): x1 = x0 + t.  Newton leaves (x0/2) e0^2 of a seed error e0,
- * i.e. x0^2 eps^2 / 2 relative for a relative seed error eps: 1.4e-8 at
- * z = 14 for the 1.2e-5 seed below, so Halley's extra factor is not needed
- * there. */
-template <int NP, int NQ>
-__device__ __forceinline__ double newton_upper(double x0, double p_over_phi, const double (&MP)[NP],
-                                               const double (&MQ)[NQ])
+/* Phi^{-1}(u) for FP32 u outside the centre: p = min(u, 1-u) (exact), v =
+   -log 2p from p = m 2^e (4.5e-9, a third of that in z), Q(v) = P7/Q6. */
+__device__ __forceinline__ float outer_quantile_f32(float u)
 {
-    double t = div_pos_fast(horner(x0, MP), horner(x0, MQ)) - p_over_phi;
-    return x0 + t;
-}
-
-/* Phi^{-1}(u) for FP32 u outside the centre: FP32 seed in the exponential
-   coordinate (1.2e-5) + one FP64 Newton step, rounded to FP32.  Here
-   z > 1.6449, so the step takes the Mills ratio of [1.6, 14.5] (8.5e-9,
-   moving the result by about 8.5e-9 / z^2 relative) and the degree-7
-   exponential (5.3e-9, by about 5.3e-9 / z^2). */
-__device__ __forceinline__ float outer_quantile_f32_refine(float u)
-{
-    const double SQRT2PI = 2.5066282746310005024;
-    float om = 1.0f - u;                       /* exact for u >= 1/2 */
-    float p = (u < om) ? u : om;
-    float v = neg_log_f32(p + p);
-    float z0 = expcoord_seed_f32(v);
-    double x0 = (double)z0;
-    double pd = (double)p;
-    /* x0 has a 24-bit significand, so x0*x0/2 is exact in FP64 */
-    double p_over_phi = pd * SQRT2PI * exp_refine<7>(0.5 * (x0 * x0));
-    double x1 = newton_upper(x0, p_over_phi, QM_MILLS32_P, QM_MILLS32_Q);
-    /* u = 0 and u = 1 both give p = 0: +-inf by the sign of u - 1/2 */
-    float mag = (p == 0.0f) ? __builtin_inff() : (float)x1;
-    /* NaN and out-of-range inputs need no select: p + p is then negative or
-       NaN, the hardware log returns NaN, and NaN propagates to the result */
+    const double LN2 = 0.69314718055994530942;
+    const float om = 1.0f - u;                  /* exact for u >= 1/2 */
+    const float p = (u < om) ? u : om;
+    const double pd = (double)p;                /* FP32 denormals are normal here */
+    const double m = __builtin_amdgcn_frexp_mant(pd);
+    const int e = __builtin_amdgcn_frexp_exp(pd);
+    const double v = __builtin_fma((double)~e, LN2, -horner(m - 0.75, QM_D32_LOG));   /* ~e = -1 - e */
+    float mag = (float)div_pos_fast(horner(v, QM_D32_OP), horner(v, QM_D32_OQ));
+    /* u = 0 and u = 1 both give p = 0: +-inf by the sign of u - 1/2; NaN and
+       u outside [0, 1] give NaN */
+    mag = p > 0.0f ? mag : p == 0.0f ? __builtin_inff() : __builtin_nanf("");
     return __builtin_copysignf(mag, u - 0.5f);
 }
 
-/*
- * Central piece of the FP32+refine form, |q| <= 0.45, q = u - 1/2 (qd, exact
- * in FP64 for FP32 u; qf, its FP32 value, serves the seed only): the FP32
- * seed z0 = q S2(r)/S3(r), r = 0.2025 - q^2 (2.6e-6 relative), then one
- * FP64 Newton step on Phi(z) = u,
- *   z1 = z0 - (erf(z0/sqrt2)/2 - q) / phi(z0),
- * with erf(z/sqrt2)/2 = z E6(z^2) (9.2e-9) and 1/phi(z) = G3(z^2) (1.1e-3).
- * E's error reaches z1 divided by phi(z) (at most 2.7 x 9.2e-9 relative, at
- * |q| = 0.45); G's only scales the step, about 2.6e-6 z, so it costs 2.9e-9
- * z; Newton's own error is (z0/2) e0^2, below 1e-11 z.  About 3e-8 in all,
- * before the rounding to FP32.  No logarithm and no exponential.
- */
-__device__ __forceinline__ float central_quantile_f32_refine(float qf, double qd)
+/* Central piece of the FP32+refine form, |q| <= 0.45, q = u - 1/2 (exact in
+   FP64 for FP32 u): q P4(r)/Q4(r), r = 0.2025 - q^2. */
+__device__ __forceinline__ float central_quantile_f32(double q)
 {
-    float rf = __builtin_fmaf(-qf, qf, (float)QM_CENTRAL_X);
-    float z0 = qf * hornerf_d(rf, QM_C32_SP) * __builtin_amdgcn_rcpf(hornerf_d(rf, QM_C32_SQ));
-    double x0 = (double)z0;
-    double y = x0 * x0;
-    double res = __builtin_fma(x0, horner(y, QM_C32_E), -qd);
-    return (float)__builtin_fma(-res, horner(y, QM_C32_G), x0);
+    const double r = __builtin_fma(-q, q, QM_CENTRAL_X);
+    return (float)div_pos_fast(q * horner(r, QM_D32_CP), horner(r, QM_D32_CQ));
 }
 
 /* Phi^{-1}(u) for FP32 u, FP32+refine form: the hybrid of the FP64 path
@@ -418,9 +372,9 @@ __device__ __forceinline__ float normal_quantile_f32_refine(float u)
 {
     double qd = (double)u - 0.5;
     bool central = is_central(qd);          /* NaN: false */
-    float w = central_quantile_f32_refine(u - 0.5f, qd);
+    float w = central_quantile_f32(qd);
     if (wave_any(!central)) {
-        float wo = outer_quantile_f32_refine(u);
+        float wo = outer_quantile_f32(u);
         w = central ? w : wo;
     }
     return w;
@@ -455,21 +409,14 @@ __device__ __noinline__ float exp_to_normal_f32_big(float v)
     return (v == __builtin_inff()) ? v : mb;
 }
 
-/* Exponential -> normal for FP32 x: FP32 seed Q(|x|) then one FP64 Halley
-   step against q(z) = e^{-|x|}/2, for which
-   p/phi(x0) = sqrt(pi/2) e^{x0^2/2 - |x|}; the exponent is O(log |x|).
-   |x| > 103 (beyond the seed's fit) takes the plain FP64 path, by wave vote. */
+/* Exponential -> normal for FP32 x: Q(v) = v P10(v)/Q10(v), v = |x|.
+   |x| > 103 (beyond its fit) takes the plain FP64 path, by wave vote. */
 __device__ __forceinline__ float exp_to_normal_f32_refine(float x)
 {
-    const double SQRT_HALF_PI = 1.2533141373155002512;
-    float v = __builtin_fabsf(x);
-    bool big = !(v <= 103.0f);                  /* also inf and NaN */
-    float vs = big ? 1.0f : v;
-    double x0 = (double)expcoord_seed_f32(vs);
-    double a = __builtin_fma(0.5 * x0, x0, -(double)vs);
-    double x1 = halley_upper(x0, SQRT_HALF_PI * exp_refine<9>(a), QM_MILLS_P, QM_MILLS_Q);
-    float mag = (float)x1;
-    mag = (vs == 0.0f) ? 0.0f : mag;
+    const float v = __builtin_fabsf(x);
+    const bool big = !(v <= 103.0f);            /* also inf and NaN */
+    const double vd = (double)v;
+    float mag = (float)div_pos_fast(vd * horner(vd, QM_E32_P), horner(vd, QM_E32_Q));
     if (wave_any(big)) {
         float mb = exp_to_normal_f32_big(v);
         mag = big ? mb : mag;

@@ -54,10 +54,10 @@ struct HybridNQ32 {
     static __device__ __forceinline__ bool split(float u, float& w)
     {
         double q = (double)u - 0.5;
-        w = central_quantile_f32_refine(u - 0.5f, q);
+        w = central_quantile_f32(q);
         return !is_central(q);
     }
-    static __device__ __forceinline__ float outer(float u) { return outer_quantile_f32_refine(u); }
+    static __device__ __forceinline__ float outer(float u) { return outer_quantile_f32(u); }
     static __device__ __forceinline__ float whole(float u) { return normal_quantile_f32_refine(u); }
 };
 

@@ -143,7 +143,7 @@ __device__ __forceinline__ double hyp_origin(const double* __restrict__ row, dou
        their degrees in v */
     constexpr int NFAM = DEG == HYP_DEGREE ? 4 : 3;
     constexpr int DG64[4] = {0, 1, 2, 4}, DG32[4] = {0, 1, 3, 0};
-    const double w = exp_refine<12>(-row[0] * neg_log_unit(a));
+    const double w = exp_taylor<12>(-row[0] * neg_log_unit(a));
     double R = 0;
     int k = 1;
 #pragma unroll
