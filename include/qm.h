@@ -103,10 +103,10 @@ typedef struct qm_ctx qm_ctx;
  * The context owns the per-nu Student t tables and the serving state.
  * Each kernel family has its own launch shape (most workgroups of 256 per
  * compute unit x 16-byte vectors in flight per lane, from measured sweeps:
- * FP64 maps 64 x 4, FP32 maps 32 x 2, FP64 quantile 64 x 4, FP32+refine
- * quantile 16 x 4, Student t 2 x 4 (FP64) and 4 x 2 (FP32), exp ->
+ * FP64 maps 64 x 4, FP32 maps 32 x 4, FP64 quantile 64 x 4, FP32+refine
+ * quantile 32 x 4, Student t 2 x 4 (FP64) and 4 x 2 (FP32), exp ->
  * hyperbolic or variance-gamma 3 x 2 and 4 x 2; fused generation of uniforms
- * 64 x 4, quantiles 8 x 4 (FP64) and 32 x 2 (FP32), Student t 8 x 4,
+ * 64 x 4, quantiles 64 x 4 (FP64) and 32 x 4 (FP32), Student t 16 x 4,
  * hyperbolic 8 x 4 and 16 x 2); a launch too small to give every compute
  * unit two workgroups takes fewer vectors per lane, and one of 2^26 elements
  * or so and more 64 workgroups per compute unit.  The environment

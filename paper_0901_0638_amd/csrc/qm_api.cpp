@@ -285,29 +285,28 @@ qm_status qm_init(int hip_device, uint64_t hbm_budget_bytes, qm_ctx** out)
         /* light FP64 maps: with no table to stage, many workgroups (2^26
            exp -> normal: 166 us at 64 x 4, 175 at 2 x 4; 2^22 13.0, 14.0) */
         {&c->shape.stream, "QM_SHAPE_STREAM", 64, 4, 0},
-        /* FP32 maps: four elements per 16-byte vector carry twice the
-           arithmetic per byte; exp -> normal FP32 (2^26, scrubbed launches)
-           ran 473-478 Gs/s refined and 590-600 plain at 16..32 x 2, against
-           393-411 and 498-526 at 2 x 4 */
-        {&c->shape.stream32, "QM_SHAPE_STREAM32", 32, 2, 0},
-        /* quantiles: FP32+refine 16 x 4 (8..16 x 4 measured 0.504-0.505 ms on
-           the 2^28 FP32 mixture, 32 x 2 0.52-0.54), FP64 64 x 4 */
-        {&c->shape.hybrid[0], "QM_SHAPE_NQ32", 16, 4, 2},
+        /* FP32 maps: exp -> normal 2^24 25 us at 32 x 4, 28.6 at 32 x 2; 2^26
+           90 and 100 */
+        {&c->shape.stream32, "QM_SHAPE_STREAM32", 32, 4, 0},
+        /* quantiles: FP32+refine 2^26 93 us at 32 x 4, 98 at 16 x 4, 2^28 372
+           and 386; FP64 2^26 173 at 64 x 4, 187 at 16 x 4 */
+        {&c->shape.hybrid[0], "QM_SHAPE_NQ32", 32, 4, 0},
         {&c->shape.hybrid[1], "QM_SHAPE_NQ64", 64, 4, 0},
         /* fused generation, write only.  Uniforms: the stores alone, many
            workgroups (2^26 FP32: 42 us at 64 x 4, 47 at 32 x 2).  Quantiles:
-           2^26 FP32 96 us at 32 x 2, FP64 155 at 8 x 4, 163 at 64 x 4 */
+           2^26 FP32 89 us at 32 x 4, 92 at 32 x 2, FP64 152 at 64 x 4, 158 at
+           8 x 4 */
         {&c->shape.uniform[0], "QM_SHAPE_GU32", 64, 4, 0},
         {&c->shape.uniform[1], "QM_SHAPE_GU64", 64, 4, 0},
-        {&c->shape.generate[0], "QM_SHAPE_GEN32", 32, 2, 0},
-        {&c->shape.generate[1], "QM_SHAPE_GEN64", 8, 4, 4},
+        {&c->shape.generate[0], "QM_SHAPE_GEN32", 32, 4, 0},
+        {&c->shape.generate[1], "QM_SHAPE_GEN64", 64, 4, 0},
         /* kernels that stage a table per workgroup: the grid stays within a
            few workgroups per unit, so that each stages once for many tiles.
-           Fused Student t, 2^24 FP64: 51 us at 8 x 4, 71 at 64 x 4 (one tile
-           for each staging); FP32 39, 49 at 32 x 2.  Fused hyperbolic, 2^24
+           Fused Student t, 2^24 FP64: 55 us at 16 x 4, 58 at 32 x 4 (one tile
+           for each staging); FP32 2^26 133, 138 at 32 x 4.  Fused hyperbolic, 2^24
            FP64: 62 us at 8 x 4, 63 at 16 x 4; FP32 44 at 8..16 x 2 */
-        {&c->shape.generate_t[0], "QM_SHAPE_GT32", 8, 4, 4},
-        {&c->shape.generate_t[1], "QM_SHAPE_GT64", 8, 4, 4},
+        {&c->shape.generate_t[0], "QM_SHAPE_GT32", 16, 4, 4},
+        {&c->shape.generate_t[1], "QM_SHAPE_GT64", 16, 4, 4},
         {&c->shape.generate_h[0], "QM_SHAPE_GH32", 16, 2, 4},
         {&c->shape.generate_h[1], "QM_SHAPE_GH64", 8, 4, 4},
         /* Student t: 2^26 FP64 174 us at 2 x 4, 181-184 at 3..8; FP32 91 at

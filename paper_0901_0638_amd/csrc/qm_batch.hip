@@ -65,7 +65,7 @@ extern __shared__ __attribute__((aligned(16))) double lds_tab[];
 template <typename T, class Op>
 static __device__ __noinline__ void chunk_op(uint64_t addr, uint64_t begin, uint64_t end)
 {
-    chunk_walk<T>(addr, begin, end, ElementMap<T, Op>());
+    chunk_walk<T>(addr, begin, end, typename MapOf<T, Op>::type());
 }
 
 /* LDS list of the hybrid quantiles' gather: 64 K elements per wave (K = 4

@@ -27,22 +27,67 @@ __device__ __forceinline__ double horner(double x, const double (&c)[N])
     return acc;
 }
 
+/*
+ * The coefficients of the outer quantile pieces, in constant memory.  Their
+ * chains are too long for the scalar registers beside a kernel's loop; held
+ * in vector registers instead, each is first copied into the accumulator of a
+ * two-operand v_fmac_f64, one v_mov_b64 for every step (21 of the 66
+ * instructions of the FP32 piece, of the 111 of the FP64 one).  Loaded where
+ * they are used (scalar loads, from an address the compiler cannot see
+ * through, or it would hoist them out of the loop again) and given to
+ * v_fma_f64 as its scalar operand, which the compiler would not do by itself,
+ * every step is one instruction, and the kernels need 52 to 69 vector
+ * registers where they needed 85 to 107.  MI355X, per pass: 2^26
+ * mixture quantiles 102.2 -> 98.0 us in FP32, 2^28 in FP64 767 -> 751, 2^26
+ * fused FP32 quantiles 94.4 -> 91.7.
+ */
+struct OuterCoeffs {
+    double p13[14], q13[14], tail_p[8], tail_q[8], log_r[7];   /* FP64 */
+    double log32[10], p32[8], q32[7];                          /* FP32 */
+};
+template <int N>
+constexpr void copy_coeffs(double (&to)[N], const double (&from)[N])
+{
+    for (int i = 0; i < N; ++i) to[i] = from[i];
+}
+constexpr OuterCoeffs outer_coeffs()
+{
+    OuterCoeffs c{};
+    copy_coeffs(c.p13, QM_PAPER_P13);
+    copy_coeffs(c.q13, QM_PAPER_Q13);
+    copy_coeffs(c.tail_p, QM_TAIL_P);
+    copy_coeffs(c.tail_q, QM_TAIL_Q);
+    copy_coeffs(c.log_r, QM_LOG_R);
+    copy_coeffs(c.log32, QM_D32_LOG);
+    copy_coeffs(c.p32, QM_D32_OP);
+    copy_coeffs(c.q32, QM_D32_OQ);
+    return c;
+}
+static __constant__ const OuterCoeffs QM_OUTER = outer_coeffs();
+
+typedef const __attribute__((address_space(4))) OuterCoeffs* OuterPtr;
+__device__ __forceinline__ OuterPtr outer_ptr()
+{
+    OuterPtr c = (OuterPtr)&QM_OUTER;
+    asm volatile("" : "+s"(c));
+    return c;
+}
+
+template <int N>
+__device__ __forceinline__ double horner(double x, const __attribute__((address_space(4))) double (&c)[N])
+{
+    double acc = c[0];
+#pragma unroll
+    for (int i = 1; i < N; ++i) asm("v_fma_f64 %0, %1, %2, %3" : "=v"(acc) : "v"(acc), "v"(x), "s"(c[i]));
+    return acc;
+}
+
 template <int N>
 __device__ __forceinline__ float hornerf(float x, const float (&c)[N])
 {
     float acc = c[0];
 #pragma unroll
     for (int i = 1; i < N; ++i) acc = __builtin_fmaf(acc, x, c[i]);
-    return acc;
-}
-
-/* FP32 Horner on FP64-stored coefficients (rounded once at compile time). */
-template <int N>
-__device__ __forceinline__ float hornerf_d(float x, const double (&c)[N])
-{
-    float acc = (float)c[0];
-#pragma unroll
-    for (int i = 1; i < N; ++i) acc = __builtin_fmaf(acc, x, (float)c[i]);
     return acc;
 }
 
@@ -78,7 +123,8 @@ __device__ __forceinline__ double sqrt_pos(double v)
    (exact numerator), s = f^2, R a fitted degree-6 polynomial; log 2 is split
    so that e log2_hi is exact.  Denormal x is handled by frexp.  x = 0,
    negative or NaN x give unspecified values: callers select their results. */
-__device__ __forceinline__ double neg_log_unit(double x)
+template <class R>
+__device__ __forceinline__ double neg_log_unit(double x, const R& coeffs)
 {
     const double SQRT_HALF = 0.70710678118654752440;
     const double LN2_HI = 6.93147180369123816490e-01, LN2_LO = 1.90821492927058770002e-10;
@@ -89,10 +135,12 @@ __device__ __forceinline__ double neg_log_unit(double x)
     e = lo ? e - 1 : e;
     double f = div_pos(m - 1.0, m + 1.0);
     double s = f * f;
-    double lm = __builtin_fma(f * s, horner(s, QM_LOG_R), f + f);
+    double lm = __builtin_fma(f * s, horner(s, coeffs), f + f);
     double de = (double)e;
     return -__builtin_fma(de, LN2_HI, __builtin_fma(de, LN2_LO, lm));
 }
+
+__device__ __forceinline__ double neg_log_unit(double x) { return neg_log_unit(x, QM_LOG_R); }
 
 /* any lane of the wave */
 __device__ __forceinline__ bool wave_any(bool p) { return __any((int)p) != 0; }
@@ -120,33 +168,22 @@ __device__ __noinline__ double expcoord_far(double v)
     return z;
 }
 
-/*
- * Plain FP64 Q(v) for v in [0, inf]: the paper's (13,13) rational on
- * v <= 42 and the fitted Q(v) = s P7(s)/Q7(s), s = sqrt v, beyond.  Both
- * pieces end in a single division.  FAR enables the v > 750 piece.
- */
-template <bool FAR>
-__device__ __forceinline__ double expcoord_q_plain(double v)
+/* Plain FP64 Q(v) for v in [0, 750]: the paper's (13,13) rational on v <= 42
+   and the fitted Q(v) = s P7(s)/Q7(s), s = sqrt v, beyond.  Both pieces end in
+   a single division. */
+__device__ __forceinline__ double expcoord_q_plain(double v, OuterPtr c)
 {
-    double num = v * horner(v, QM_PAPER_P13);
-    double den = horner(v, QM_PAPER_Q13);
+    double num = v * horner(v, c->p13);
+    double den = horner(v, c->q13);
     bool tail = v > QM_TAIL_VMIN;
     if (wave_any(tail)) {
         double s = sqrt_pos(v);
-        double nt = s * horner(s, QM_TAIL_P);
-        double dt = horner(s, QM_TAIL_Q);
+        double nt = s * horner(s, c->tail_p);
+        double dt = horner(s, c->tail_q);
         num = tail ? nt : num;
         den = tail ? dt : den;
     }
-    double q = div_pos(num, den);
-    if (FAR) {
-        bool far = (v > QM_TAIL_VMAX) && (v < __builtin_inf());
-        if (wave_any(far)) {
-            double f = expcoord_far(far ? v : 1000.0);
-            q = far ? f : q;
-        }
-    }
-    return q;
+    return div_pos(num, den);
 }
 
 /* Paper mode: the (13,13) rational verbatim, whatever v (Appendix B). */
@@ -183,7 +220,10 @@ __device__ __forceinline__ double quantile_finish(double u, double mag)
    1-u)), Q(v), sign and specials. */
 __device__ __forceinline__ double outer_quantile_f64(double u)
 {
-    return quantile_finish(u, expcoord_q_plain<false>(quantile_v(u)));
+    const OuterPtr c = outer_ptr();
+    const double om = 1.0 - u;
+    const double p = (u < om) ? u : om;
+    return quantile_finish(u, expcoord_q_plain(neg_log_unit(p + p, c->log_r), c));
 }
 
 /* Central piece, |q| <= 0.45 with q = u - 1/2 (90% of uniform draws):
@@ -266,14 +306,38 @@ __device__ __forceinline__ double normal_quantile_f64_t2(double u)
     return quantile_finish(u, expcoord_q_paper(quantile_v(u)));
 }
 
-/* Exponential -> normal, FP64: v = |x| directly, odd extension. */
-template <bool PAPER>
-__device__ __forceinline__ double exp_to_normal_f64(double x)
+/* Exponential -> normal, FP64: v = |x| directly, odd extension.  Paper mode
+   takes the (13,13) rational whatever v.  Plain mode splits into that
+   rational (_main) and, for v > 42, the deep-tail piece and what lies beyond
+   it (_rare, entered by wave vote), so that a lane's elements can share one
+   vote; NaN and inf are rare too. */
+__device__ __forceinline__ double exp_to_normal_f64_paper(double x)
 {
     double v = __builtin_fabs(x);
-    double mag = PAPER ? expcoord_q_paper(v) : expcoord_q_plain<true>(v);
+    double mag = expcoord_q_paper(v);
     mag = (v == __builtin_inf()) ? v : mag;
     return __builtin_copysign(mag, x);
+}
+
+__device__ __forceinline__ double exp_to_normal_f64_main(double x, bool* rare)
+{
+    const double v = __builtin_fabs(x);
+    *rare = !(v <= QM_TAIL_VMIN);
+    return __builtin_copysign(div_pos(v * horner(v, QM_PAPER_P13), horner(v, QM_PAPER_Q13)), x);
+}
+
+__device__ __forceinline__ double exp_to_normal_f64_rare(double x)
+{
+    const double v = __builtin_fabs(x);
+    const double s = sqrt_pos(v);
+    double q = div_pos(s * horner(s, QM_TAIL_P), horner(s, QM_TAIL_Q));
+    const bool far = v > QM_TAIL_VMAX && v < __builtin_inf();
+    if (wave_any(far)) {
+        const double f = expcoord_far(far ? v : 1000.0);
+        q = far ? f : q;
+    }
+    q = (v == __builtin_inf()) ? v : q;
+    return __builtin_copysign(q, x);
 }
 
 /* ------------------------------------------------------------------------ */
@@ -349,8 +413,9 @@ __device__ __forceinline__ float outer_quantile_f32(float u)
     const double pd = (double)p;                /* FP32 denormals are normal here */
     const double m = __builtin_amdgcn_frexp_mant(pd);
     const int e = __builtin_amdgcn_frexp_exp(pd);
-    const double v = __builtin_fma((double)~e, LN2, -horner(m - 0.75, QM_D32_LOG));   /* ~e = -1 - e */
-    float mag = (float)div_pos_fast(horner(v, QM_D32_OP), horner(v, QM_D32_OQ));
+    const OuterPtr c = outer_ptr();
+    const double v = __builtin_fma((double)~e, LN2, -horner(m - 0.75, c->log32));   /* ~e = -1 - e */
+    float mag = (float)div_pos_fast(horner(v, c->p32), horner(v, c->q32));
     /* u = 0 and u = 1 both give p = 0: +-inf by the sign of u - 1/2; NaN and
        u outside [0, 1] give NaN */
     mag = p > 0.0f ? mag : p == 0.0f ? __builtin_inff() : __builtin_nanf("");
@@ -401,27 +466,28 @@ __device__ __forceinline__ float normal_quantile_f32_plain(float u)
     return (float)normal_quantile_f64<false>((double)u);
 }
 
-/* |x| > 103 for the FP32 form: the plain FP64 map, rounded (kept out of line:
-   it is rare and would otherwise crowd the FP32 loop's registers). */
-__device__ __noinline__ float exp_to_normal_f32_big(float v)
-{
-    float mb = (float)expcoord_q_plain<true>((double)v);
-    return (v == __builtin_inff()) ? v : mb;
-}
-
-/* Exponential -> normal for FP32 x: Q(v) = v P10(v)/Q10(v), v = |x|.
-   |x| > 103 (beyond its fit) takes the plain FP64 path, by wave vote. */
-__device__ __forceinline__ float exp_to_normal_f32_refine(float x)
+/* Exponential -> normal for FP32 x: Q(v) = v P10(v)/Q10(v), v = |x| <= 103;
+   beyond (also inf and NaN) the plain FP64 map, rounded. */
+__device__ __forceinline__ float exp_to_normal_f32_main(float x, bool* rare)
 {
     const float v = __builtin_fabsf(x);
-    const bool big = !(v <= 103.0f);            /* also inf and NaN */
+    *rare = !(v <= 103.0f);
     const double vd = (double)v;
-    float mag = (float)div_pos_fast(vd * horner(vd, QM_E32_P), horner(vd, QM_E32_Q));
-    if (wave_any(big)) {
-        float mb = exp_to_normal_f32_big(v);
-        mag = big ? mb : mag;
-    }
-    return __builtin_copysignf(mag, x);
+    return __builtin_copysignf((float)div_pos_fast(vd * horner(vd, QM_E32_P), horner(vd, QM_E32_Q)), x);
 }
+
+/* The FP64 map of any x, out of line. */
+__device__ __noinline__ double exp_to_normal_f64_whole(double x)
+{
+    bool rare;
+    double z = exp_to_normal_f64_main(x, &rare);
+    if (wave_any(rare)) {
+        const double r = exp_to_normal_f64_rare(x);
+        z = rare ? r : z;
+    }
+    return z;
+}
+
+__device__ __forceinline__ float exp_to_normal_f32_rare(float x) { return (float)exp_to_normal_f64_whole((double)x); }
 
 }  // namespace qm

@@ -15,13 +15,28 @@ namespace qm {
 struct OpNQ64Plain { __device__ double operator()(double u) const { return normal_quantile_f64<false>(u); } };
 struct OpNQ64Paper { __device__ double operator()(double u) const { return normal_quantile_f64<true>(u); } };
 struct OpNQ64PaperT2 { __device__ double operator()(double u) const { return normal_quantile_f64_t2(u); } };
-struct OpE64Plain  { __device__ double operator()(double x) const { return exp_to_normal_f64<false>(x); } };
-struct OpE64Paper  { __device__ double operator()(double x) const { return exp_to_normal_f64<true>(x); } };
+struct OpE64Paper  { __device__ double operator()(double x) const { return exp_to_normal_f64_paper(x); } };
 struct OpNQ32Refine { __device__ float operator()(float u) const { return normal_quantile_f32_refine(u); } };
 struct OpNQ32Paper  { __device__ float operator()(float u) const { return normal_quantile_f32_paper(u); } };
 struct OpNQ32Plain  { __device__ float operator()(float u) const { return normal_quantile_f32_plain(u); } };
-struct OpE32Refine  { __device__ float operator()(float x) const { return exp_to_normal_f32_refine(x); } };
-struct OpE32Plain   { __device__ float operator()(float x) const { return (float)exp_to_normal_f64<false>((double)x); } };
+
+/* Exponential -> normal in two parts: for every element, and for the rare
+   ones beyond its range. */
+struct OpE64Plain {
+    static __device__ __forceinline__ double main(double x, bool* rare) { return exp_to_normal_f64_main(x, rare); }
+    static __device__ __forceinline__ double rare(double x) { return exp_to_normal_f64_rare(x); }
+};
+struct OpE32Refine {
+    static __device__ __forceinline__ float main(float x, bool* rare) { return exp_to_normal_f32_main(x, rare); }
+    static __device__ __forceinline__ float rare(float x) { return exp_to_normal_f32_rare(x); }
+};
+struct OpE32Plain {
+    static __device__ __forceinline__ float main(float x, bool* rare)
+    {
+        return (float)exp_to_normal_f64_main((double)x, rare);
+    }
+    static __device__ __forceinline__ float rare(float x) { return (float)exp_to_normal_f64_rare((double)x); }
+};
 
 /*
  * The hybrid quantiles (FP64 plain, FP32+refine) split each element into
@@ -124,6 +139,44 @@ struct ElementMap {
     }
     __device__ __forceinline__ T one(T x) const { return Op()(x); }
 };
+
+/* A walk's map from a function in two parts: all of a lane's elements first
+   (K independent chains; a vote between them would end each before the next
+   begins), then one wave vote for the rare ones. */
+template <typename T, class Op>
+struct VotedMap {
+    template <int K>
+    __device__ __forceinline__ void tile(const T (&x)[K], T (&y)[K]) const
+    {
+        bool rare[K];
+        bool any = false;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            y[k] = Op::main(x[k], &rare[k]);
+            any |= rare[k];
+        }
+        if (wave_any(any)) {
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (wave_any(rare[k])) {
+                    const T r = Op::rare(x[k]);
+                    y[k] = rare[k] ? r : y[k];
+                }
+        }
+    }
+    __device__ __forceinline__ T one(T x) const
+    {
+        const T a[1] = {x};
+        T y[1];
+        tile(a, y);
+        return y[0];
+    }
+};
+
+template <typename T, class Op> struct MapOf { typedef ElementMap<T, Op> type; };
+template <typename T> struct MapOf<T, OpE64Plain> { typedef VotedMap<T, OpE64Plain> type; };
+template <typename T> struct MapOf<T, OpE32Refine> { typedef VotedMap<T, OpE32Refine> type; };
+template <typename T> struct MapOf<T, OpE32Plain> { typedef VotedMap<T, OpE32Plain> type; };
 
 /* A walk's map from a gathered hybrid; buf: the wave's LDS list. */
 template <typename T, class H>

@@ -22,7 +22,7 @@ template <typename T, int UNROLL, class Op>
 __global__ __launch_bounds__(256) void k_map(Span<T> s)
 {
     const uint32_t lane = wave_lane();
-    const ElementMap<T, Op> map;
+    const typename MapOf<T, Op>::type map{};
     Walk<T, UNROLL> w;
     w.begin(s, wave_uniform(blockIdx.x * 4ull + (threadIdx.x >> 6)), gridDim.x * 4ull, lane);
     w.run(s, lane, map);
