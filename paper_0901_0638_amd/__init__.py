@@ -20,7 +20,17 @@ from ._lib import (  # noqa: F401
     check, load, qm_request, qm_serving_counters,
 )
 
-_DTYPES = {"torch.float64": QM_F64, "torch.float32": QM_F32}
+_dtypes = None          # torch dtype -> qm_dtype, filled on the first call (torch is imported by then)
+_raw_stream = None      # device index -> the current stream's handle
+
+
+def _bind_torch():
+    global _dtypes, _raw_stream
+    import torch
+    # the raw handle without a Stream object around it, which costs 2 us a call
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+        lambda i: torch.cuda.current_stream(i).cuda_stream)
+    _dtypes = {torch.float64: QM_F64, torch.float32: QM_F32}
 
 
 class Context:
@@ -58,27 +68,35 @@ class Context:
 
 
 def _dtype_of(t):
+    if _dtypes is None:
+        _bind_torch()
     try:
-        return _DTYPES[str(t.dtype)]
+        return _dtypes[t.dtype]
     except KeyError:
         raise TypeError("expected a float32 or float64 tensor, got %s" % t.dtype)
 
 
 def _stream(stream, t):
+    """`stream`, or the current one of t's device."""
     if stream is not None:
-        return ctypes.c_void_p(int(stream))
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+        return int(stream)
+    if not t.is_cuda:
+        raise ValueError("tensors must be on a HIP device")
+    if _raw_stream is None:
+        _bind_torch()
+    return _raw_stream(t.get_device())
 
 
 def _io(inp, out):
-    if inp.device.type != "cuda" or out.device.type != "cuda":
+    """(input address, output address, elements, qm_dtype) of a tensor pair."""
+    if not (inp.is_cuda and out.is_cuda):
         raise ValueError("tensors must be on a HIP device")
     if not (inp.is_contiguous() and out.is_contiguous()):
         raise ValueError("tensors must be contiguous")
-    if inp.numel() != out.numel() or inp.dtype != out.dtype:
+    n = inp.numel()
+    if n != out.numel() or inp.dtype != out.dtype:
         raise ValueError("input and output must have the same size and dtype")
-    return ctypes.c_void_p(inp.data_ptr()), ctypes.c_void_p(out.data_ptr()), inp.numel(), _dtype_of(inp)
+    return inp.data_ptr(), out.data_ptr(), n, _dtype_of(inp)
 
 
 def qm_normal_quantile(ctx, u, w, mode=QM_PLAIN, stream=None):
@@ -91,12 +109,12 @@ def qm_generate(ctx, seed, stream_id, first, out, kind=QM_NORMAL_QUANTILE, mode=
     """out[i] = map of the open uniform of element first + i of the Philox4x32-10
     stream with key (seed, stream_id): kind QM_UNIFORM (u itself) or
     QM_NORMAL_QUANTILE (Phi^{-1}(u); FP64 PLAIN/PAPER, FP32 F32_REFINE/PLAIN/PAPER)."""
-    if out.device.type != "cuda" or not out.is_contiguous():
+    if not out.is_cuda or not out.is_contiguous():
         raise ValueError("output must be a contiguous tensor on a HIP device")
     dt = _dtype_of(out)
     if mode is None:
         mode = QM_F32_REFINE if (dt == QM_F32 and kind == QM_NORMAL_QUANTILE) else QM_PLAIN
-    check(load().qm_generate(ctx.handle, int(seed), int(stream_id), int(first), ctypes.c_void_p(out.data_ptr()),
+    check(load().qm_generate(ctx.handle, int(seed), int(stream_id), int(first), out.data_ptr(),
                              out.numel(), int(kind), dt, int(mode), _stream(stream, out)))
 
 
@@ -105,7 +123,7 @@ def qm_generate_student_t(ctx, seed, stream_id, first, out, nu, mode=None, strea
     dt = _dtype_of(out)
     if mode is None:
         mode = QM_PLAIN if dt == QM_F64 else QM_F32_REFINE
-    check(load().qm_generate_student_t(ctx.handle, int(seed), int(stream_id), int(first), ctypes.c_void_p(out.data_ptr()),
+    check(load().qm_generate_student_t(ctx.handle, int(seed), int(stream_id), int(first), out.data_ptr(),
                                        out.numel(), dt, int(mode), float(nu), _stream(stream, out)))
 
 
@@ -115,7 +133,7 @@ def qm_generate_hyperbolic(ctx, seed, stream_id, first, out, alpha, beta, delta,
     if mode is None:
         mode = QM_PLAIN if dt == QM_F64 else QM_F32_REFINE
     check(load().qm_generate_hyperbolic(ctx.handle, int(seed), int(stream_id), int(first),
-                                        ctypes.c_void_p(out.data_ptr()), out.numel(), dt, int(mode), float(alpha),
+                                        out.data_ptr(), out.numel(), dt, int(mode), float(alpha),
                                         float(beta), float(delta), float(mu), _stream(stream, out)))
 
 
@@ -124,7 +142,7 @@ def qm_generate_vg(ctx, seed, stream_id, first, out, lam, alpha, beta, mu=0.0, m
     dt = _dtype_of(out)
     if mode is None:
         mode = QM_PLAIN if dt == QM_F64 else QM_F32_REFINE
-    check(load().qm_generate_vg(ctx.handle, int(seed), int(stream_id), int(first), ctypes.c_void_p(out.data_ptr()),
+    check(load().qm_generate_vg(ctx.handle, int(seed), int(stream_id), int(first), out.data_ptr(),
                                 out.numel(), dt, int(mode), float(lam), float(alpha), float(beta), float(mu),
                                 _stream(stream, out)))
 
@@ -185,22 +203,28 @@ def make_request(kind, inp, out, mode=None, nu=0.0, user_tag=0, hyperbolic=(0.0,
     if mode is None:
         mode = QM_PLAIN if dt == QM_F64 else QM_F32_REFINE
     a, b, d = (float(x) for x in hyperbolic)
-    return qm_request(kind, dt, mode, 0, float(nu), pi.value, po.value, n, user_tag, a, b, d, float(mu))
+    return qm_request(kind, dt, mode, 0, float(nu), pi, po, n, user_tag, a, b, d, float(mu))
+
+
+def _request_array(reqs):
+    """The C array of a list of qm_request, copied through the buffer protocol
+    (item by item it takes 100 ns each, as long as a small batch's kernel)."""
+    if not set(map(type, reqs)) <= {qm_request}:
+        return (qm_request * len(reqs))(*reqs)      # raises what ctypes raises
+    return (qm_request * len(reqs)).from_buffer_copy(b"".join(reqs))
 
 
 def qm_run_batch(ctx, reqs, stream=None, device_tensor=None):
     """Run a list of qm_request as one launch."""
-    arr = (qm_request * len(reqs))(*reqs)
-    s = ctypes.c_void_p(int(stream)) if stream is not None else _stream(None, device_tensor) if device_tensor is not None else ctypes.c_void_p(0)
-    check(load().qm_run_batch(ctx.handle, arr, len(reqs), s))
+    s = _stream(stream, device_tensor) if stream is not None or device_tensor is not None else None
+    check(load().qm_run_batch(ctx.handle, _request_array(reqs), len(reqs), s))
 
 
 def qm_run_batch_noalloc(ctx, reqs, stream=None, device_tensor=None):
     """qm_run_batch through the allocation-free entry point (tables must
     already be in the context)."""
-    arr = (qm_request * len(reqs))(*reqs)
-    s = ctypes.c_void_p(int(stream)) if stream is not None else _stream(None, device_tensor) if device_tensor is not None else ctypes.c_void_p(0)
-    check(load().qm_run_batch_noalloc(ctx.handle, arr, len(reqs), s))
+    s = _stream(stream, device_tensor) if stream is not None or device_tensor is not None else None
+    check(load().qm_run_batch_noalloc(ctx.handle, _request_array(reqs), len(reqs), s))
 
 
 def qm_submit(ctx, req):

@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <condition_variable>
 #include <cstdio>
@@ -474,30 +475,39 @@ struct InFlight {
        flag array, or -1 (n = 0, or no flags: the batch's event completes it) */
     std::vector<int32_t> flag;
     uint32_t* flags;
-    size_t open;                /* tickets not yet observed complete */
+    bool ended;                 /* its event has fired */
 };
 
 constexpr int SERVE_STREAMS = 4;
+/* How long the scheduler stays awake after its last batch. */
+constexpr std::chrono::microseconds SERVE_IDLE_SPIN(50);
+
 struct Server {
     qm_ctx* ctx = nullptr;
     std::thread th;
+    /* mu guards the queue, the tickets and the counters: what submitters,
+       pollers and the scheduler share, each for a few hundred nanoseconds.
+       Streams, batches in flight and events are the scheduler's own, so that
+       its device queries hold up nobody. */
     std::mutex mu;
     std::condition_variable cv;
     std::deque<uint64_t> queue;
+    std::atomic<uint64_t> queued{0};      /* queue.size(), readable without mu */
+    std::atomic<bool> stop{false};        /* set under mu */
+    bool waiting = false;                 /* the scheduler sleeps on cv */
     std::unordered_map<uint64_t, Ticket> tickets;
     uint64_t next_ticket = 1;
     uint64_t in_flight_bytes = 0;
-    bool stop = false;
-    hipStream_t streams[SERVE_STREAMS] = {};
-    bool stream_busy[SERVE_STREAMS] = {};
-    uint32_t* flags[SERVE_STREAMS] = {};  /* host-coherent, device-visible; NULL: events only */
-    std::vector<InFlight> inflight;
-    std::vector<hipEvent_t> free_events;
     std::deque<uint64_t> finished;        /* terminal tickets, oldest first */
     std::vector<uint64_t> latencies_ns;   /* ring of SERVE_KEEP_LATENCIES */
     uint64_t completed = 0, failed = 0, submitted = 0;
     uint64_t in_flight_bytes_hwm = 0;
     uint64_t in_flight_requests = 0;
+    hipStream_t streams[SERVE_STREAMS] = {};
+    bool stream_busy[SERVE_STREAMS] = {};
+    uint32_t* flags[SERVE_STREAMS] = {};  /* host-coherent, device-visible; NULL: events only */
+    std::vector<InFlight> inflight;
+    std::vector<hipEvent_t> free_events;
 };
 
 /* A ticket reached a terminal state: keep it among the recent ones. */
@@ -527,7 +537,6 @@ static void complete_ticket(Server* S, InFlight& f, size_t k, clk::time_point no
     --S->in_flight_requests;
     S->in_flight_bytes -= tk.bytes;
     f.bytes -= tk.bytes;
-    --f.open;
     finish_ticket(S, t);
 }
 
@@ -545,72 +554,98 @@ static void server_loop(Server* S)
     }();
     std::vector<uint64_t> admit;
     std::vector<qm_request> reqs;
+    std::vector<std::pair<size_t, size_t>> seen;   /* (batch, ticket of it) observed complete */
+    clk::time_point last_work = clk::now();
     for (;;) {
-        std::unique_lock<std::mutex> lk(S->mu);
         /* complete requests whose flag is up, and retire finished batches
            (their event completes whatever the flags have not) */
-        clk::time_point now = clk::now();
-        for (size_t i = 0; i < S->inflight.size();) {
+        seen.clear();
+        bool ended = false;
+        for (size_t i = 0; i < S->inflight.size(); ++i) {
             InFlight& f = S->inflight[i];
-            if (hipEventQuery(f.ev) == hipSuccess) {
-                for (size_t k = 0; k < f.tickets.size(); ++k) complete_ticket(S, f, k, now);
+            f.ended = hipEventQuery(f.ev) == hipSuccess;
+            ended |= f.ended;
+            if (!f.ended && !f.flags) continue;
+            for (size_t k = 0; k < f.tickets.size(); ++k)
+                if (f.ended || (f.flag[k] >= 0 && __atomic_load_n(f.flags + f.flag[k], __ATOMIC_ACQUIRE) != 0)) {
+                    seen.emplace_back(i, k);
+                    f.flag[k] = -1;
+                }
+        }
+        if (!seen.empty()) {
+            std::lock_guard<std::mutex> lk(S->mu);
+            const clk::time_point now = clk::now();
+            for (const auto& c : seen) complete_ticket(S, S->inflight[c.first], c.second, now);
+        }
+        for (size_t i = 0; ended && i < S->inflight.size();) {
+            InFlight& f = S->inflight[i];
+            if (f.ended) {
                 S->stream_busy[f.stream] = false;
                 S->free_events.push_back(f.ev);
                 S->inflight.erase(S->inflight.begin() + i);
-                continue;
+            } else {
+                ++i;
             }
-            if (f.flags && f.open) {
-                for (size_t k = 0; k < f.tickets.size(); ++k)
-                    if (f.flag[k] >= 0 && __atomic_load_n(f.flags + f.flag[k], __ATOMIC_ACQUIRE) != 0) {
-                        complete_ticket(S, f, k, now);
-                        f.flag[k] = -1;
-                    }
-            }
-            ++i;
         }
         /* continuous batching: a batch is formed only when a stream is idle,
            from everything queued by then (in arrival order, within the
            budget); while all streams are busy, arrivals accumulate into the
            next, larger batch rather than queueing behind small ones */
         admit.clear();
+        reqs.clear();
         uint64_t bytes = 0;
         int idle = -1;
         for (int k = 0; k < SERVE_STREAMS; ++k)
             if (!S->stream_busy[k]) { idle = k; break; }
-        if (!S->stop && idle >= 0) {
+        const bool stop = S->stop;
+        if (!stop && idle >= 0 && S->queued > 0) {
+            std::lock_guard<std::mutex> lk(S->mu);
             while (!S->queue.empty()) {
                 Ticket& tk = S->tickets[S->queue.front()];
                 if (S->in_flight_bytes + bytes + tk.bytes > S->ctx->budget) break;
                 bytes += tk.bytes;
                 tk.state = T_RUNNING;
                 admit.push_back(S->queue.front());
+                reqs.push_back(tk.req);
                 S->queue.pop_front();
+                --S->queued;
             }
-        }
-        if (S->stop && S->inflight.empty() && admit.empty()) {
-            for (uint64_t t : S->queue) {
-                S->tickets[t].state = T_CLOSED;
-                finish_ticket(S, t);
-            }
-            S->queue.clear();
-            return;
+            S->in_flight_bytes += bytes;
+            S->in_flight_requests += admit.size();
+            if (S->in_flight_bytes > S->in_flight_bytes_hwm) S->in_flight_bytes_hwm = S->in_flight_bytes;
         }
         if (admit.empty()) {
-            if (S->inflight.empty()) {
-                S->cv.wait(lk);
-            } else if (poll_us == 0) {
+            const clk::time_point now = clk::now();
+            if (!S->inflight.empty()) last_work = now;
+            if (S->inflight.empty() && (stop || now - last_work > SERVE_IDLE_SPIN)) {
+                std::unique_lock<std::mutex> lk(S->mu);
+                if (S->stop) {
+                    for (uint64_t t : S->queue) {
+                        S->tickets[t].state = T_CLOSED;
+                        finish_ticket(S, t);
+                    }
+                    S->queue.clear();
+                    S->queued = 0;
+                    return;
+                }
+                S->waiting = true;
+                S->cv.wait(lk, [S] { return S->stop || !S->queue.empty(); });
+                S->waiting = false;
+                last_work = clk::now();
+            } else if (poll_us == 0 || S->inflight.empty()) {
                 /* work on the device: poll again at once (a timed wait
                    oversleeps by tens of microseconds, which every request
-                   would pay); yield so submitters can take the lock */
-                lk.unlock();
+                   would pay), as for a moment after the last of it (a
+                   sleeping scheduler costs the next submitter a wake-up) */
                 std::this_thread::yield();
             } else {
+                std::unique_lock<std::mutex> lk(S->mu);
+                S->waiting = true;
                 S->cv.wait_for(lk, std::chrono::microseconds(poll_us));
+                S->waiting = false;
             }
             continue;
         }
-        reqs.clear();
-        for (uint64_t t : admit) reqs.push_back(S->tickets[t].req);
         /* completion flags: one word per request with n > 0, in order */
         std::vector<int32_t> flag(admit.size(), -1);
         uint32_t* flags = S->flags[idle];
@@ -623,18 +658,14 @@ static void server_loop(Server* S)
             flags = nullptr;
             std::fill(flag.begin(), flag.end(), -1);
         }
-        S->in_flight_bytes += bytes;
-        S->in_flight_requests += admit.size();
-        if (S->in_flight_bytes > S->in_flight_bytes_hwm) S->in_flight_bytes_hwm = S->in_flight_bytes;
         hipEvent_t ev = nullptr;
         if (!S->free_events.empty()) { ev = S->free_events.back(); S->free_events.pop_back(); }
         hipStream_t st = S->streams[idle];
         S->stream_busy[idle] = true;
-        lk.unlock();
         if (!ev) (void)hipEventCreateWithFlags(&ev, hipEventDisableTiming);
         qm_status rc = enqueue_batch(S->ctx, reqs.data(), reqs.size(), st, ev, flags);
-        lk.lock();
         if (rc != QM_OK) {
+            std::lock_guard<std::mutex> lk(S->mu);
             for (uint64_t t : admit) {
                 S->tickets[t].state = T_FAILED;
                 finish_ticket(S, t);
@@ -646,7 +677,7 @@ static void server_loop(Server* S)
             S->free_events.push_back(ev);
             continue;
         }
-        S->inflight.push_back(InFlight{ev, admit, bytes, idle, std::move(flag), flags, admit.size()});
+        S->inflight.push_back(InFlight{ev, admit, bytes, idle, std::move(flag), flags, false});
     }
 }
 
@@ -745,6 +776,7 @@ qm_status qm_submit(qm_ctx* ctx, const qm_request* req, uint64_t* ticket)
     st = QM_OK;
     qm::Server* S = qm::server_of(ctx, &st);
     if (!S) return st;
+    bool wake;
     {
         std::lock_guard<std::mutex> lk(S->mu);
         if (S->stop) return qm::set_error(QM_E_CLOSED, "serving loop is shutting down");
@@ -756,10 +788,12 @@ qm_status qm_submit(qm_ctx* ctx, const qm_request* req, uint64_t* ticket)
         tk.t_submit = qm::clk::now();
         S->tickets.emplace(t, tk);
         S->queue.push_back(t);
+        ++S->queued;
         ++S->submitted;
         *ticket = t;
+        wake = S->waiting;
     }
-    S->cv.notify_one();
+    if (wake) S->cv.notify_one();
     return QM_OK;
 }
 
