@@ -261,7 +261,8 @@ struct HypBase {
         const double ratio = (neg ? u : 1.0 - u) * (neg ? inv_p_minus : inv_p_plus);
         /* u = 1 (an FP64 uniform of the top 53-bit value rounds to 1) is the
            base's right end, v = +inf (mapped to +inf) */
-        const double l = ratio > 0.0 ? neg_log_unit(ratio) : __builtin_inf();
+        double l = neg_log_unit(ratio);      /* finite for 0: a select, not a branch that would part the lane's elements */
+        l = ratio > 0.0 ? l : __builtin_inf();
         return l * (neg ? -inv_rate_minus : inv_rate_plus);
     }
 };
@@ -365,7 +366,7 @@ hipError_t launch_generate_student(int dtype, int mode, uint32_t seed, uint32_t 
     if (!f64 && !(dtype == QM_F32 && mode == QM_F32_REFINE)) return hipErrorInvalidValue;
     const TCells& c = f64 ? h.f64 : h.f32;
     const StudentParams P = make_params(h, c, table_block(d_table) + c.coef_offset);
-    const size_t lds = (size_t)c.nlds * P.lds_stride * sizeof(double);
+    const size_t lds = student_lds_bytes(P);
     const KernelShape ks = shape.generate_t[f64];
     if (lds > GEN_LDS_MAX) return hipErrorInvalidValue;
     auto launch = [&](auto a) {

@@ -86,7 +86,7 @@ __device__ __forceinline__ double hyp_cell(const double* __restrict__ lds, int r
     if constexpr (DEG == HYP_DEGREE_F32) {
         typedef float f4v __attribute__((ext_vector_type(4)));
         typedef double d2v __attribute__((ext_vector_type(2)));
-        const double* r = lds + row * HypRow<DEG>::lds;
+        const double* r = lds + __umul24((uint32_t)row, (uint32_t)HypRow<DEG>::lds);
         const d2v a = *reinterpret_cast<const d2v*>(r);            /* c0, then the top two floats */
         const f4v b = *reinterpret_cast<const f4v*>(r + 2);
         const float last = reinterpret_cast<const float*>(r + 4)[0];
@@ -102,7 +102,7 @@ __device__ __forceinline__ double hyp_cell(const double* __restrict__ lds, int r
         return __builtin_fma(d, (double)S, c0);
     } else {
         typedef double d2v __attribute__((ext_vector_type(2)));
-        const double* r = lds + row * HypRow<DEG>::lds;
+        const double* r = lds + __umul24((uint32_t)row, (uint32_t)HypRow<DEG>::lds);
         double c[DEG + 1];
 #pragma unroll
         for (int k = 0; k < (DEG + 1) / 2; ++k) {

@@ -266,7 +266,7 @@ static qm_status plan_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count,
             const TCells& c = r.dtype == QM_F64 ? t->hdr.f64 : t->hdr.f32;
             b.coef = table_block(t->d_table) + c.coef_offset;
             b.P = make_params(t->hdr, c, b.coef);
-            if (!t->hdr.identity) lds = std::max(lds, (size_t)c.nlds * b.P.lds_stride * sizeof(double));
+            if (!t->hdr.identity) lds = std::max(lds, student_lds_bytes(b.P));
         } else if (r.kind == QM_EXP_TO_HYPERBOLIC || r.kind == QM_EXP_TO_VG) {
             const bool vg = r.kind == QM_EXP_TO_VG;
             const DeviceHypTable* t = nullptr;

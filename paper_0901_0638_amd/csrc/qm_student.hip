@@ -17,6 +17,9 @@
 #include <stdint.h>
 #include <stdlib.h>
 
+#include <algorithm>
+#include <cmath>
+
 #include "qm_device.hpp"
 #include "qm_internal.h"
 #include "qm_stream.hpp"
@@ -75,13 +78,18 @@ static bool cells_valid(const TCells& c, int degree)
     return c.degree == degree && c.stride == degree + 1 && c.nlds >= 1 && c.ncell >= c.nlds;
 }
 
+/* The staged cells reach |z| = 7, which a normal draw passes with probability
+   2.6e-12 (the table's LDS range goes to 10, for twice the rows to stage and
+   to keep); the cells beyond are read from device memory by the far path, to
+   the same bits. */
+constexpr double T_Y_STAGED = 49.0;
+
 StudentParams make_params(const TTableHeader& h, const TCells& c, const double* d_rows)
 {
     StudentParams P;
     P.h = c.h;
     P.inv_h = c.inv_h;
     P.centre_offset = c.centre_offset;
-    P.y_lds = c.y_lds;
     P.y_max = c.y_max;
     P.gcoef = d_rows;
     P.log_K = h.log_K;
@@ -90,10 +98,11 @@ StudentParams make_params(const TTableHeader& h, const TCells& c, const double* 
     P.inv_nu = 1.0 / h.nu;
     P.nu = h.nu;
     P.ncell = c.ncell;
-    P.nlds = c.nlds;
+    P.nlds = std::min(c.nlds, (int)std::ceil(T_Y_STAGED / c.h));
+    P.y_lds = P.nlds * c.h;
     P.identity = h.identity;
     P.row_shift = c.stride == 16 ? 4 : 3;
-    P.lds_stride = student_lds_stride(c.stride, c.nlds);
+    P.lds_stride = student_lds_stride(c.stride, P.nlds);
     return P;
 }
 
@@ -111,7 +120,7 @@ static hipError_t launch_t(const void* in, void* out, uint64_t n, const double* 
     }
     const TCells& c = sizeof(T) == 8 ? h.f64 : h.f32;
     const StudentParams P = make_params(h, c, d_block + c.coef_offset);
-    const size_t lds = (size_t)c.nlds * P.lds_stride * sizeof(double);
+    const size_t lds = student_lds_bytes(P);
     if (lds > 65536) return hipErrorInvalidValue;   /* beyond the dynamic LDS a launch may ask for */
     const Span<T> a = make_span(static_cast<const T*>(in), static_cast<T*>(out), n);
     const int u = launch_unroll(a.nvec, shape, shape_all.cus);

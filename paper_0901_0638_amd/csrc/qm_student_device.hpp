@@ -27,6 +27,8 @@ struct StudentParams {
    dword): table rows in device memory follow a header of 8-byte multiples. */
 typedef double d2any __attribute__((ext_vector_type(2), aligned(8)));
 
+inline size_t student_lds_bytes(const StudentParams& P) { return (size_t)P.nlds * P.lds_stride * sizeof(double); }
+
 /* Copy the first nlds cell rows (2^row_shift doubles each) into LDS rows of
    P.lds_stride doubles, in 16-byte pieces, four in flight per thread before
    the first is waited for: a workgroup's staging is then one or two trips to
@@ -150,7 +152,7 @@ __device__ __forceinline__ void student_eval(const double (&z)[K], double (&t)[K
         const double yh = s * s;            /* only selects the cell */
         double d;
         const int j = cell_of(s, yh, P.nlds - 1, P.h, P.inv_h, P.centre_offset, &d);
-        t[e] = z[e] * cell_poly_lds<DEG>(tab + j * P.lds_stride, d);
+        t[e] = z[e] * cell_poly_lds<DEG>(tab + __umul24((uint32_t)j, (uint32_t)P.lds_stride), d);
         far[e] = !(yh <= P.y_lds);
         anyfar |= far[e];
     }
