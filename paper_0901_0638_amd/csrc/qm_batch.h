@@ -64,6 +64,7 @@ struct BatchArgs {
     BatchReq r[BATCH_ARGS_MAX];
 };
 static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments");
+static_assert(sizeof(BatchHeader) % 8 == 0 && sizeof(BatchReq) % 8 == 0, "uploaded in 8-byte words");
 
 /* The allocation-free entry point's device array: one header and
    QM_BATCH_NOALLOC_MAX_REQUESTS records (768 KiB) per GPU. */
@@ -78,6 +79,8 @@ hipError_t batch_scratch_address(int device, void** out);
 StudentParams make_params(const TTableHeader& h, const TCells& c, const double* d_rows);
 hipError_t launch_batch(const BatchHeader* d_hdr, const BatchReq* d_reqs, size_t lds_bytes, uint64_t blocks,
                         hipStream_t s);
+/* Copy `bytes` (a multiple of 8) of pinned host memory to the device, on s. */
+hipError_t launch_upload(const void* host, void* dev, size_t bytes, hipStream_t s);
 hipError_t launch_batch_args(const BatchArgs& args, size_t lds_bytes, hipStream_t s);
 
 }  // namespace qm

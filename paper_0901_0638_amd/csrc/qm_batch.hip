@@ -254,6 +254,24 @@ hipError_t launch_batch(const BatchHeader* d_hdr, const BatchReq* d_reqs, size_t
     return hipGetLastError();
 }
 
+/* The descriptors' upload as a kernel that reads the pinned staging memory: a
+   copy command goes through another queue, whose hand-over and back cost more
+   than the copy (512 requests, 98 KB, MI355X: 180.9 us a pass with the copy
+   command, 169.5 with this). */
+__global__ __launch_bounds__(256) void k_upload(const uint64_t* host, uint64_t* dev, uint32_t n)
+{
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) dev[i] = host[i];
+}
+
+hipError_t launch_upload(const void* host, void* dev, size_t bytes, hipStream_t s)
+{
+    const uint32_t n = (uint32_t)(bytes / 8);
+    hipLaunchKernelGGL(k_upload, dim3((n + 255) / 256), dim3(256), 0, s, static_cast<const uint64_t*>(host),
+                       static_cast<uint64_t*>(dev), n);
+    return hipGetLastError();
+}
+
 hipError_t launch_batch_args(const BatchArgs& args, size_t lds_bytes, hipStream_t s)
 {
     hipLaunchKernelGGL(k_batch_args, dim3((unsigned)args.h.total_chunks), dim3(256), lds_bytes, s, args);

@@ -377,7 +377,7 @@ qm_status enqueue_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count, hip
     } else {
         memcpy(slot->host, &h, sizeof h);
         memcpy((char*)slot->host + sizeof h, d.data(), d.size() * sizeof(BatchReq));
-        e = hipMemcpyAsync(slot->dev, slot->host, bytes, hipMemcpyHostToDevice, s);
+        e = launch_upload(slot->host, slot->dev, bytes, s);
         if (e == hipSuccess)
             e = launch_batch((const BatchHeader*)slot->dev, (const BatchReq*)((char*)slot->dev + sizeof h), lds,
                              batch_blocks(ctx, h.total_chunks), s);
@@ -433,7 +433,7 @@ qm_status enqueue_batch_noalloc(qm_ctx* ctx, const qm_request* reqs, uint64_t co
     }
     memcpy(ctx->noalloc_host, &h, sizeof h);
     const size_t bytes = sizeof(BatchHeader) + k * sizeof(BatchReq);
-    e = hipMemcpyAsync(ctx->noalloc_dev, ctx->noalloc_host, bytes, hipMemcpyHostToDevice, s);
+    e = launch_upload(ctx->noalloc_host, ctx->noalloc_dev, bytes, s);
     if (e == hipSuccess) e = hipEventRecord(ctx->noalloc_ev, s);
     if (e == hipSuccess)
         e = launch_batch(static_cast<const BatchHeader*>(ctx->noalloc_dev),
