@@ -71,7 +71,6 @@ static void side_far(const HypSide& s, const double* d_block, HypSideFar* f)
     f->clog = s.far_clog;
     f->gcoef = d_block + s.coef_offset;
     f->ncell = s.ncell;
-    f->origin = s.origin;
 }
 
 bool make_hyp_params(const HypTableHeader& h, bool f32, const HypTableHeader* d_table, uint64_t ncoef, double mu,
@@ -80,7 +79,8 @@ bool make_hyp_params(const HypTableHeader& h, bool f32, const HypTableHeader* d_
     const HypSide& R = f32 ? h.right32 : h.right;
     const HypSide& L = f32 ? h.left32 : h.left;
     const int deg = f32 ? HYP_DEGREE_F32 : HYP_DEGREE;
-    if (!side_valid(R, deg, ncoef) || !side_valid(L, deg, ncoef) || R.v0 != L.v0 || R.inv_v0 != L.inv_v0)
+    if (!side_valid(R, deg, ncoef) || !side_valid(L, deg, ncoef) || R.v0 != L.v0 || R.inv_v0 != L.inv_v0 ||
+        R.origin != L.origin)
         return false;
     const double* d_block = reinterpret_cast<const double*>(reinterpret_cast<const char*>(d_table) + sizeof(HypTableHeader));
     const int stride = f32 ? HypRow<HYP_DEGREE_F32>::lds : HypRow<HYP_DEGREE>::lds;
@@ -95,8 +95,9 @@ bool make_hyp_params(const HypTableHeader& h, bool f32, const HypTableHeader* d_
     side_far(R, d_block, &P->r);
     side_far(L, d_block, &P->l);
     P->nlds = HYP_SUB * noct;
-    P->jlo = (R.origin || L.origin) ? HYP_SUB : 0;
-    *lds_bytes = (size_t)2 * P->nlds * stride * sizeof(double);
+    P->jlo = R.origin ? HYP_SUB : 0;
+    /* the cells, and both sides' origin series */
+    *lds_bytes = (size_t)2 * (P->nlds * stride + (R.origin ? deg + 1 : 0)) * sizeof(double);
     return true;
 }
 

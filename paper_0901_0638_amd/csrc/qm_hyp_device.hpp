@@ -40,7 +40,6 @@ struct HypSideFar {
     double v_top, c0, c1, c2, clog;
     const double* gcoef;          /* the side's rows in global memory */
     int ncell;
-    int origin;                   /* 1: v < v0 is the origin series of row 0 */
 };
 
 struct HypParams {
@@ -48,7 +47,8 @@ struct HypParams {
     HypSideFar r, l;              /* v >= 0, v < 0 */
     int nlds;                     /* cells per side in LDS, right side's first */
     int jlo;                      /* first cell the LDS path takes: 0, or HYP_SUB when the sides
-                                     hold the origin series (their first octave goes the far way) */
+                                     hold the origin series in their first octave; both sides'
+                                     series then follow the cells in LDS, as the doubles of row 0 */
 };
 
 
@@ -130,14 +130,16 @@ __device__ __forceinline__ double hyp_near(double v, const double* __restrict__ 
     return a * hyp_cell<DEG>(lds, row, d);
 }
 
-/* R in the first octave of a side with the origin series (row 0 of its
-   cells, layout in qm_hyp_table.h): R = P0(a) + w (P1(a) + w (P2(a) +
-   w P3(a))), w = a^rho = e^(rho log a); FP32-output cells have no P3.  The
-   terms in w are a small part of R near 0 (w <= v0^rho), so the short
-   logarithm and exponential (a few 1e-15 where w matters) are ample; the
-   library pow took three times their instructions. */
+/* |Q(a)| in the first octave of a side with the origin series (row 0 of its
+   cells, layout in qm_hyp_table.h; here in LDS): a R, R = P0(a) + w (P1(a) +
+   w (P2(a) + w P3(a))), w = a^rho = e^(rho log a); FP32-output cells have no
+   P3.  The terms in w are a small part of R near 0 (w <= v0^rho), so the
+   short logarithm and exponential (a few 1e-15 where w matters) are ample;
+   the library pow took three times their instructions.  Out of line: a
+   kernel's loop would hold its constants otherwise. */
+typedef const __attribute__((address_space(3))) double* LdsRow;
 template <int DEG>
-__device__ __forceinline__ double hyp_origin(const double* __restrict__ row, double a)
+static __device__ __noinline__ double hyp_origin(LdsRow row, double a)
 {
     /* the families in row order, from the highest power of w down, and
        their degrees in v */
@@ -154,19 +156,17 @@ __device__ __forceinline__ double hyp_origin(const double* __restrict__ row, dou
         for (int m = 0; m <= dg; ++m, ++k) p = __builtin_fma(p, a, row[k]);
         R = __builtin_fma(R, w, p);
     }
-    return R;
+    return a * R;
 }
 
 /* |Q(v)| beyond the LDS cells: the side's global-memory cells up to v_top,
-   then the large-v form; inf -> inf, NaN -> NaN; below v0 on a side with the
-   origin series, that series.  The side's parameters come as plain values
+   then the large-v form; inf -> inf, NaN -> NaN.  The side's parameters come as plain values
    selected per lane (a reference to a lane-dependent side, or a struct
    passed by value, would put them in scratch memory). */
 template <int DEG>
 static __device__ __noinline__ double hyp_far(double a, double v0, double inv_v0, double v_top, double c0, double c1,
-                                              double c2, double clog, const double* gcoef, int ncell, int origin)
+                                              double c2, double clog, const double* gcoef, int ncell)
 {
-    if (origin && a < v0) return a * hyp_origin<DEG>(gcoef, a);
     if (!(a < v_top)) {
         if (!(a < __builtin_inf())) return a;
         if (clog == 0.0) return a + (c0 + (c1 + c2 / a) / a);
@@ -188,7 +188,7 @@ __device__ __forceinline__ double hyp_far_of(double v, const HypParams& P)
     const bool neg = v < 0.0;
     return hyp_far<DEG>(__builtin_fabs(v), P.v0, P.inv_v0, neg ? P.l.v_top : P.r.v_top, neg ? P.l.c0 : P.r.c0,
                    neg ? P.l.c1 : P.r.c1, neg ? P.l.c2 : P.r.c2, neg ? P.l.clog : P.r.clog,
-                   neg ? P.l.gcoef : P.r.gcoef, neg ? P.l.ncell : P.r.ncell, neg ? P.l.origin : P.r.origin);
+                   neg ? P.l.gcoef : P.r.gcoef, neg ? P.l.ncell : P.r.ncell);
 }
 
 /* Both sides' LDS rows: right side rows 0..nlds-1, left side after (for
@@ -204,6 +204,10 @@ __device__ __forceinline__ void stage_hyp(double* lds, const HypParams& P)
     typedef double d2v __attribute__((ext_vector_type(2)));
     constexpr int PIECES = HypRow<DEG>::n / 2;
     const int step = blockDim.x;
+    if (P.jlo && threadIdx.x < 2 * HypRow<DEG>::n) {
+        const int left = threadIdx.x >= HypRow<DEG>::n, k = threadIdx.x - left * HypRow<DEG>::n;
+        lds[2 * P.nlds * HypRow<DEG>::lds + threadIdx.x] = (left ? P.l.gcoef : P.r.gcoef)[k];
+    }
     if constexpr (DEG == HYP_DEGREE_F32) {
         typedef float f4v __attribute__((ext_vector_type(4)));
         for (int r = threadIdx.x; r < 2 * P.nlds; r += step) {
@@ -238,17 +242,33 @@ __device__ __forceinline__ void stage_hyp(double* lds, const HypParams& P)
     }
 }
 
+/* One pass over a lane's flagged elements: f of the first of them (bit `bit`
+   of the K), and its result in its place. */
+template <int K, class F>
+__device__ __forceinline__ void one_per_lane(const double (&v)[K], double (&q)[K], uint32_t& left, F f)
+{
+    const uint32_t bit = left & -left;
+    double x = 0.0;
+#pragma unroll
+    for (int e = 0; e < K; ++e) x = (bit >> e) & 1u ? v[e] : x;
+    const double r = f(x);
+#pragma unroll
+    for (int e = 0; e < K; ++e) q[e] = (bit >> e) & 1u ? r : q[e];
+    left ^= bit;
+}
+
 /*
  * |Q(v)| of the K elements a lane holds: every element's cell polynomial
  * first (K independent chains), then, if any lane of the wave has elements
  * beyond the LDS cells, passes that take one such element of each lane at a
- * time, whichever of the K it is.  Far elements are rare and scattered: on a
+ * time, whichever of the K it is.  Such elements are rare and scattered: on a
  * target with the origin series about 0.2% of the base samples are, so that a
  * wave's tile of 512 holds one on average in one or two lanes, and one
  * pass serves it.  A vote for each of the K slots entered the far code once
- * per slot that held any, with a library pow each (2^24 FP64 samples of
- * variance-gamma (4.25, 1, 0.3): 67.2 us on MI355X, 54.7 with the passes and
- * the short power of hyp_origin).
+ * per slot that held any, with the series' row from device memory and a
+ * library pow each (2^24 FP64 samples of variance-gamma (4.25, 1, 0.3): 67.2
+ * us on MI355X; 52.5 with the passes and the short power, 49.7 with the rows
+ * in LDS).
  */
 template <int DEG, int K>
 __device__ __forceinline__ void hyp_abs_q(const double (&v)[K], double (&q)[K], const double* __restrict__ lds,
@@ -265,16 +285,18 @@ __device__ __forceinline__ void hyp_abs_q(const double (&v)[K], double (&q)[K], 
         uint32_t left = 0;
 #pragma unroll
         for (int e = 0; e < K; ++e) left |= far[e] ? 1u << e : 0u;
-        do {
-            const uint32_t bit = left & -left;
-            double x = 0.0;
+        if (P.jlo) {
+            uint32_t first = 0;
 #pragma unroll
-            for (int e = 0; e < K; ++e) x = (bit >> e) & 1u ? v[e] : x;
-            const double f = hyp_far_of<DEG>(x, P);
-#pragma unroll
-            for (int e = 0; e < K; ++e) q[e] = (bit >> e) & 1u ? f : q[e];
-            left ^= bit;
-        } while (wave_any(left != 0));
+            for (int e = 0; e < K; ++e) first |= far[e] && __builtin_fabs(v[e]) < P.v0 ? 1u << e : 0u;
+            left ^= first;
+            const LdsRow series = (LdsRow)(lds + 2 * P.nlds * HypRow<DEG>::lds);
+            while (wave_any(first != 0))
+                one_per_lane(v, q, first, [&](double x) {
+                    return hyp_origin<DEG>(series + (x < 0.0 ? HypRow<DEG>::n : 0), __builtin_fabs(x));
+                });
+        }
+        while (wave_any(left != 0)) one_per_lane(v, q, left, [&](double x) { return hyp_far_of<DEG>(x, P); });
     }
 }
 
