@@ -304,7 +304,8 @@ qm_status qm_init(int hip_device, uint64_t hbm_budget_bytes, qm_ctx** out)
            few workgroups per unit, so that each stages once for many tiles.
            Fused Student t, 2^24 FP64: 55 us at 16 x 4, 58 at 32 x 4 (one tile
            for each staging); FP32 2^26 133, 138 at 32 x 4.  Fused hyperbolic, 2^24
-           FP64: 62 us at 8 x 4, 63 at 16 x 4; FP32 44 at 8..16 x 2 */
+           FP64: 61 us at 8..16 x 4, 63 at 32 x 4; FP32 47 at 8..16 x 2, 48 at
+           32 x 2 */
         {&c->shape.generate_t[0], "QM_SHAPE_GT32", 16, 4, 4},
         {&c->shape.generate_t[1], "QM_SHAPE_GT64", 16, 4, 4},
         {&c->shape.generate_h[0], "QM_SHAPE_GH32", 16, 2, 4},

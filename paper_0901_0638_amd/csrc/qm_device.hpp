@@ -118,6 +118,20 @@ __device__ __forceinline__ double sqrt_pos(double v)
     return __builtin_fma(d, h, s);
 }
 
+/* c ? a : b with the lane mask in a scalar register pair.  The compiler keeps
+   a select's mask in VCC, where a second v_cndmask_b32 straight after the
+   first takes 23 cycles a wave on gfx950; a 64-bit select is two of them (25
+   cycles with its comparison, 11 through a scalar pair).  In the FP64 paths a
+   minimum, a ldexp by the comparison's 0 or 1, or an added special takes the
+   place of a select where one can: 2^24 fused samples, hyperbolic FP64 63.6 ->
+   61.1 us and FP32 49.2 -> 46.8, Student t FP64 57.8 -> 56.4. */
+__device__ __forceinline__ double select_f64(bool c, double a, double b)
+{
+    uint64_t m = __builtin_amdgcn_ballot_w64(c);
+    asm("" : "+s"(m));
+    return __builtin_amdgcn_inverse_ballot_w64(m) ? a : b;
+}
+
 /* -log(x) for x in (0, 1], relative error about an ulp.  x = m 2^e with m in
    [sqrt(1/2), sqrt(2)); log m = 2 atanh f = 2f + f s R(s), f = (m-1)/(m+1)
    (exact numerator), s = f^2, R a fitted degree-6 polynomial; log 2 is split
@@ -130,9 +144,9 @@ __device__ __forceinline__ double neg_log_unit(double x, const R& coeffs)
     const double LN2_HI = 6.93147180369123816490e-01, LN2_LO = 1.90821492927058770002e-10;
     double m = __builtin_amdgcn_frexp_mant(x);
     int e = __builtin_amdgcn_frexp_exp(x);
-    bool lo = m < SQRT_HALF;
-    m = lo ? m + m : m;
-    e = lo ? e - 1 : e;
+    const int lo = m < SQRT_HALF;            /* a scaling by 2^lo: cheaper than 64-bit selects */
+    m = __builtin_amdgcn_ldexp(m, lo);
+    e -= lo;
     double f = div_pos(m - 1.0, m + 1.0);
     double s = f * f;
     double lm = __builtin_fma(f * s, horner(s, coeffs), f + f);
@@ -180,8 +194,8 @@ __device__ __forceinline__ double expcoord_q_plain(double v, OuterPtr c)
         double s = sqrt_pos(v);
         double nt = s * horner(s, c->tail_p);
         double dt = horner(s, c->tail_q);
-        num = tail ? nt : num;
-        den = tail ? dt : den;
+        num = select_f64(tail, nt, num);
+        den = select_f64(tail, dt, den);
     }
     return div_pos(num, den);
 }
@@ -198,22 +212,25 @@ __device__ __forceinline__ double expcoord_q_paper(double v)
 
 /* Reflection x = 2 min(u, 1-u) is exact (1-u exact for u >= 1/2, Sterbenz);
    v = -log x; sign by u - 1/2 (+0 at u = 1/2).  u = 0 -> -inf, u = 1 -> +inf,
-   u outside [0,1] or NaN -> NaN, all by select (Section 7.2 reflection; the
-   paper's kernels leave u in {0,1} to NaN). */
+   u outside [0,1] or NaN -> NaN (Section 7.2 reflection; the paper's kernels
+   leave u in {0,1} to NaN). */
+__device__ __forceinline__ double reflect(double u) { return __builtin_fmin(u, 1.0 - u); }
+
 __device__ __forceinline__ double quantile_v(double u)
 {
-    double om = 1.0 - u;
-    double p = (u < om) ? u : om;
+    const double p = reflect(u);
     return neg_log_unit(p + p);
 }
 
+/* mag is finite where p = min(u, 1-u) = 0; p < 0 outside [0,1].  The specials
+   are added, with one 32-bit select each: an inf or NaN for p = 0, p < 0 or
+   NaN, 0 otherwise. */
 __device__ __forceinline__ double quantile_finish(double u, double mag)
 {
-    double w = __builtin_copysign(mag, u - 0.5);
-    w = (u == 0.0) ? -__builtin_inf() : w;
-    w = (u == 1.0) ? __builtin_inf() : w;
-    w = (u >= 0.0 && u <= 1.0) ? w : __builtin_nan("");
-    return w;
+    const double p = reflect(u);
+    int special = p == 0.0 ? 0x7ff00000 : 0x7ff80000;
+    special = p > 0.0 ? 0 : special;
+    return __builtin_copysign(mag + __hiloint2double(special, 0), u - 0.5);
 }
 
 /* The exponential-coordinate path for any u (plain mode): v = -log(2 min(u,
@@ -221,8 +238,7 @@ __device__ __forceinline__ double quantile_finish(double u, double mag)
 __device__ __forceinline__ double outer_quantile_f64(double u)
 {
     const OuterPtr c = outer_ptr();
-    const double om = 1.0 - u;
-    const double p = (u < om) ? u : om;
+    const double p = reflect(u);
     return quantile_finish(u, expcoord_q_plain(neg_log_unit(p + p, c->log_r), c));
 }
 
@@ -259,7 +275,7 @@ __device__ __forceinline__ double normal_quantile_f64(double u)
     double w = central_quantile(q);
     if (wave_any(!central)) {
         double wo = outer_quantile_f64(u);
-        w = central ? w : wo;
+        w = select_f64(central, w, wo);
     }
     return w;
 }

@@ -257,13 +257,14 @@ struct HypBase {
     double p_minus, inv_p_minus, inv_p_plus, inv_rate_minus, inv_rate_plus;
     __device__ __forceinline__ double operator()(double u) const
     {
-        const bool neg = u < p_minus;
-        const double ratio = (neg ? u : 1.0 - u) * (neg ? inv_p_minus : inv_p_plus);
+        /* u / p_minus < 1 < (1 - u) / p_plus on the left of the mode, the other
+           way round on its right */
+        const double ratio = __builtin_fmin(u * inv_p_minus, (1.0 - u) * inv_p_plus);
         /* u = 1 (an FP64 uniform of the top 53-bit value rounds to 1) is the
-           base's right end, v = +inf (mapped to +inf) */
-        double l = neg_log_unit(ratio);      /* finite for 0: a select, not a branch that would part the lane's elements */
-        l = ratio > 0.0 ? l : __builtin_inf();
-        return l * (neg ? -inv_rate_minus : inv_rate_plus);
+           base's right end, v = +inf (mapped to +inf): the logarithm of 0 is
+           finite, and the infinity is added */
+        const double l = neg_log_unit(ratio) + __hiloint2double(ratio > 0.0 ? 0 : 0x7ff00000, 0);
+        return l * select_f64(u < p_minus, -inv_rate_minus, inv_rate_plus);
     }
 };
 

@@ -87,10 +87,7 @@ __device__ __forceinline__ double cell_poly_lds(const double* __restrict__ row, 
 __device__ __forceinline__ int cell_of(double s, double yh, int jmax, double h, double inv_h, double centre_offset,
                                        double* d)
 {
-    double jd = yh * inv_h;
-    const double jm = (double)jmax;
-    jd = (jd < jm) ? jd : jm;
-    int j = (int)jd;
+    int j = (int)__builtin_fmin(yh * inv_h, (double)jmax);
     double yc = __builtin_fma((double)j, h, centre_offset);   /* exact: h is a power of 2 */
     *d = __builtin_fma(s, s, -yc);
     return j;
