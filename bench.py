@@ -37,8 +37,8 @@ HBM_PEAK_GBS = 8000.0
 T_NUS = (1, 2, 3, 4, 5, 10, 30)
 
 
-QUANTILE_SOURCES = ("qm_kernels.hip", "qm_hybrid.hpp", "qm_device.hpp", "qm_coeffs.h", "qm_paper_coeffs.h")
-HYPERBOLIC_SOURCES = ("qm_hyp.hip", "qm_hyp_device.hpp", "qm_hyp_table.h", "qm_device.hpp")
+QUANTILE_SOURCES = ("qm_kernels.hip", "qm_hybrid.hpp", "qm_stream.hpp", "qm_device.hpp", "qm_coeffs.h", "qm_paper_coeffs.h")
+HYPERBOLIC_SOURCES = ("qm_hyp.hip", "qm_hyp_device.hpp", "qm_hyp_table.h", "qm_stream.hpp", "qm_device.hpp")
 
 
 def kernel_source_hash(files=QUANTILE_SOURCES):
@@ -764,7 +764,7 @@ def run_hyperbolic(args, torch, qm, qi):
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": counted_traffic("hyperbolic_exp_2e26_hbm_counters.md", "k_hyperbolic<double>",
                                                 HYPERBOLIC_SOURCES),
-                     "kernel": "qm::k_hyperbolic<double, true, 4, 11> (16 workgroups/CU x 4 vectors, wave-contiguous tiles)",
+                     "kernel": "qm::k_hyperbolic<double, 2, 11> (64 workgroups per CU, tiles of 2 vectors a lane)",
                      "algorithmic_bytes_per_launch": 16.0 * n, "avg_launch_ms": round(avg64, 4),
                      "profiler_avg_launch_ms": profiler_avg_ms("hyperbolic_exp_2e26_kernel_stats.md",
                                                                "k_hyperbolic<double>", HYPERBOLIC_SOURCES)},
