@@ -106,10 +106,11 @@ typedef struct qm_ctx qm_ctx;
  * FP64 maps 64 x 4, FP32 maps 32 x 4, FP64 quantile 64 x 4, FP32+refine
  * quantile 32 x 4, Student t 2 x 4 (FP64) and 4 x 2 (FP32), exp ->
  * hyperbolic or variance-gamma 3 x 2 and 4 x 2; fused generation of uniforms
- * 64 x 4, quantiles 64 x 4 (FP64) and 32 x 4 (FP32), Student t 16 x 4,
- * hyperbolic 8 x 4 and 16 x 2); a launch too small to give every compute
- * unit two workgroups takes fewer vectors per lane, and one of 2^26 elements
- * or so and more 64 workgroups per compute unit.  The environment
+ * one vector per lane and workgroup, quantiles 64 x 4 (FP64) and 32 x 4 (FP32),
+ * Student t 16 x 4, hyperbolic 16 x 4 and 16 x 2); a launch too small to give
+ * every compute unit two workgroups takes fewer vectors per lane, and a map
+ * of 2^25 elements or so and more one workgroup for every tile or two.
+ * The environment
  * variables QM_BLOCKS_PER_CU (1..64) and QM_UNROLL (1, 2 or 4), read here,
  * override every family, and QM_SHAPE_STREAM, QM_SHAPE_STREAM32,
  * QM_SHAPE_NQ64, QM_SHAPE_NQ32, QM_SHAPE_GU64, QM_SHAPE_GU32,

@@ -103,9 +103,14 @@ bool make_hyp_params(const HypTableHeader& h, bool f32, const HypTableHeader* d_
 
 template <typename T, int DEG>
 static hipError_t launch_h(const void* in, void* out, uint64_t n, const HypParams& P, size_t lds, hipStream_t s,
-                           const KernelShape& shape, int cus)
+                           KernelShape shape, int cus)
 {
     const Span<T> a = make_span(static_cast<const T*>(in), static_cast<T*>(out), n);
+    /* targets with the origin series: a tile's passes over it are a latency
+       that two tiles do not hide and more do (variance-gamma 4.25, 2^26 FP64:
+       196 us at 64 workgroups per unit, 219 with two tiles each; 2^28 763 and
+       853) */
+    if (P.jlo) shape.big_blocks = 64 * (uint64_t)cus;
     const int u = launch_unroll(a.nvec, shape, cus);
     const dim3 grid(launch_blocks(a.nvec, u, shape)), block(256);
     with_unroll(u, [&](auto U) {

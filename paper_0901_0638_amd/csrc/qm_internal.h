@@ -13,17 +13,20 @@
 namespace qm {
 
 /* Launch geometry of one kernel family: at most max_blocks workgroups of
-   256, each lane keeping `unroll` 16-byte vectors in flight (1, 2 or 4); from
-   big_tiles workgroup tiles on (0: never), big_blocks workgroups. */
+   256, each lane keeping `unroll` 16-byte vectors in flight (1, 2 or 4).
+   Launches of big_vecs vectors and more keep big_unroll in flight, with two
+   tiles to a workgroup, those of huge_vecs and more four, with one tile (0:
+   never); both have at most big_blocks workgroups. */
 struct KernelShape {
     uint64_t max_blocks;
-    int unroll;
-    uint64_t big_tiles, big_blocks;
+    int unroll, big_unroll;
+    uint64_t big_vecs, huge_vecs, big_blocks;
 };
 
-/* Per family, measured on MI355X (launch-shape sweeps over 1..64
-   workgroups per CU x 1..4 vectors, 2^17 to 2^28 elements): kernels that
-   stage a table run best from few workgroups, the others from many. */
+/* Per family, measured on MI355X (launch-shape sweeps over 1..1024
+   workgroups per CU x 1..4 vectors, 2^17 to 2^29 elements): kernels that
+   stage a table run best from few workgroups, the others from many; arrays
+   beyond the last-level cache from one for every tile or two. */
 struct LaunchShape {
     KernelShape stream;      /* k_map, FP64: exp -> normal, paper mode */
     KernelShape stream32;    /* k_map, FP32: exp -> normal, paper and plain quantiles */

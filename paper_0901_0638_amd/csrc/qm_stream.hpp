@@ -163,17 +163,22 @@ __device__ __forceinline__ void run_edges(const Span<T>& s, const Map& map)
     }
 }
 
+inline bool launch_big(uint64_t nvec, const KernelShape& ks) { return ks.big_vecs && nvec >= ks.big_vecs; }
+inline bool launch_huge(uint64_t nvec, const KernelShape& ks) { return ks.huge_vecs && nvec >= ks.huge_vecs; }
+
 /*
  * Vectors per lane for a launch of nvec vectors: the family's own, halved
  * while the grid would have fewer than two workgroups of 256 for each
- * compute unit.  A short launch is bound by the latency of one tile, which
- * grows with the elements a lane holds, and by the compute units left idle:
- * on MI355X 2^17 FP64 hyperbolic samples took 4.3 us with four vectors per
+ * compute unit; a big launch's own.  A short launch is bound by the latency of
+ * one tile, which grows with the elements a lane holds, and by the compute
+ * units left idle: on MI355X 2^17 FP64 hyperbolic samples took 4.3 us with four vectors per
  * lane and 3.3 with one, fused FP32 ones 7.5 and 3.7; at 2^20 (two
  * workgroups per unit with four vectors) the three are within 5%.
  */
 inline int launch_unroll(uint64_t nvec, const KernelShape& ks, int cus)
 {
+    if (launch_huge(nvec, ks)) return 4;
+    if (launch_big(nvec, ks)) return ks.big_unroll;
     int u = ks.unroll;
     while (u > 1 && nvec < 512ull * u * (uint64_t)cus) u /= 2;
     return u;
@@ -182,18 +187,31 @@ inline int launch_unroll(uint64_t nvec, const KernelShape& ks, int cus)
 /*
  * Workgroups of a launch.  Few of them keep each one's set-up (a staged
  * table) small against its work, and for arrays that the last-level cache
- * holds that is best; large arrays run at the memory's rate, where a fixed
- * share per workgroup waits for the slowest channel, and many short
- * workgroups, handed out as others end, even that out: FP64 hyperbolic
- * samples took 46 us for 2^24 with 3 workgroups per unit and 55 with 64, but
- * for 2^26 184 and 175, for 2^27 375 and 358 (MI355X).  The switch lies where
- * 64 per unit have two tiles each (fused chains with a table: four).
+ * holds that is best (FP64 hyperbolic samples, 2^24: 46 us with 3 workgroups
+ * per compute unit, 55 with 64).  Large arrays run at the memory's rate, and
+ * there a workgroup takes two tiles, one from each half of the array: the
+ * resident workgroups, handed out in order, then write two windows that
+ * advance together, where a fixed grid's strides spread them over the array
+ * more and more, and the second tile's loads are in flight while the first is
+ * mapped.  MI355X, us, fixed grid -> two tiles: FP64 quantiles 2^28 752 ->
+ * 705, 2^29 1620 -> 1430 (both faster than a copy kernel on a fixed grid:
+ * 732 for 2^28); FP64 Student t 2^26 174.5 -> 167.5, 2^27 354 -> 340; FP64
+ * hyperbolic 2^27 363 -> 346; FP32 Student t 2^28 362 -> 340.  One tile each
+ * is slower there (Student t 2^26 187, quantiles 182 against 172), and two
+ * neighbouring tiles are too at some sizes (quantiles 2^28 741).  From two
+ * tiles for each of 64 workgroups per unit on (FP32 maps, which are closer to
+ * their arithmetic: 128).  From eight times 256 MB on one tile of four vectors
+ * each does as well or better: FP64 2^28, Student t 687 (nu = 4), 708 (nu = 1)
+ * and 743 (nu = 30) with two tiles, 696..702 with one, exp -> normal 690 and
+ * 675, hyperbolic 705 and 710, quantiles 705 and 701.
  */
 inline unsigned launch_blocks(uint64_t nvec, int unroll, const KernelShape& ks)
 {
     const uint64_t per_block = 256ull * unroll, tiles = (nvec + per_block - 1) / per_block;
-    const uint64_t cap = ks.big_tiles && tiles >= ks.big_tiles ? ks.big_blocks : ks.max_blocks;
-    return (unsigned)(tiles > cap ? cap : tiles < 1 ? 1 : tiles);
+    const bool big = launch_big(nvec, ks);
+    const uint64_t blocks = big && !launch_huge(nvec, ks) ? (tiles + 1) / 2 : tiles;
+    const uint64_t cap = big ? ks.big_blocks : ks.max_blocks;
+    return (unsigned)(blocks > cap ? cap : blocks < 1 ? 1 : blocks);
 }
 
 /* f(std::integral_constant<int, u>) for u = 1, 2 or 4. */

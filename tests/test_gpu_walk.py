@@ -89,3 +89,36 @@ def test_far_elements_anywhere_equal_a_launch_of_their_own(ctx, name, dtype):
     run(ctx, near, y[:near.numel()])
     base[at] = alone[at % 8]
     assert torch.equal(y[:near.numel()], base)
+
+
+BIG = {"quantile": (25, 26), "exp_normal": (25, 26), "student": (24, 24), "student_1": (24, 24), "hyperbolic": (24, 24),
+       "vg_origin": (24, 24)}      # log2 of the vectors (FP64, FP32) from which a workgroup takes two tiles
+
+
+@pytest.mark.parametrize("huge", [False, True])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("name", sorted(BIG))
+def test_large_launches_equal_small_ones(ctx, name, dtype, huge):
+    """From the first size on with two tiles to a workgroup, and from that
+    with one of four vectors: an even and an odd number of tiles, whole and
+    with a partial last one, element by element the values of a small launch."""
+    x = inputs(name, dtype, TOP)
+    want = torch.empty_like(x)
+    MAPS[name](ctx, x, want)
+    per = 16 // x.element_size()
+    first = per << (27 if huge else BIG[name][dtype == torch.float32])
+    n = first + 1024 * per + 5
+    reps = -(-n // TOP)
+    xs = x.repeat(reps)[:n]
+    as_int = torch.int64 if dtype == torch.float64 else torch.int32
+    want = torch.where(torch.isnan(want), torch.full_like(want, float("nan")), want).view(as_int)
+    for m in (first, first + 1024 * per, n):
+        y = torch.full((n,), 7.0, dtype=dtype, device="cuda")
+        MAPS[name](ctx, xs[:m], y[:m])
+        assert bool((y[m:] == 7.0).all())
+        whole = m // TOP * TOP
+        y.masked_fill_(torch.isnan(y), float("nan"))
+        got = y.view(as_int)
+        assert bool((got[:whole].view(-1, TOP) == want).all()), (name, m)
+        assert bool((got[whole:m] == want[:m - whole]).all()), (name, m)
+        del y, got
