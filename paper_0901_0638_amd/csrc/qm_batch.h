@@ -10,10 +10,10 @@
 
 namespace qm {
 
-/* Elements per chunk (a workgroup takes one chunk at a time), carried in the
-   batch header: a batch is cut into several chunks for each workgroup that
-   the GPU holds at once (batch_chunk), between these bounds (multiples of QM_CHUNK_MIN
-   keep every chunk start 16-byte aligned within an aligned request). */
+/* Elements of a request per chunk (a workgroup takes one chunk at a time; a
+   request's chunks share its tiles in turn): a batch is cut into several
+   chunks for each workgroup that the GPU holds at once (batch_chunk), between
+   these bounds, in multiples of QM_CHUNK_MIN. */
 constexpr uint64_t QM_CHUNK_MIN = 2048;
 constexpr uint64_t QM_CHUNK_MAX = 16384;
 
@@ -31,7 +31,7 @@ struct BatchHeader {
     uint64_t total_chunks;
     uint32_t nreq;
     uint32_t reserved;
-    uint64_t chunk;         /* elements per chunk */
+    uint64_t chunk;         /* elements of a request per chunk: a request of n has ceil(n / chunk) */
     /* per-request completion (the serving loop), or both NULL: for a
        request with `flagged` chunks, count[i] in device memory, 0 at launch,
        counts its finished ones; the workgroup finishing the last sets the

@@ -39,20 +39,24 @@ __device__ __forceinline__ ReqPtr uniform_req(uint64_t addr)
     return (ReqPtr)wave_uniform(addr);
 }
 
-/* Elements [begin, end) of the request at `addr` by the whole workgroup,
-   walked by its four waves as the single-request kernels walk an array. */
+/* Part `part` of the `parts` of the request at `addr`, by the whole workgroup.
+   The parts' waves take the request's tiles in turn, as the workgroups of a
+   single-request launch do; the first part has the edge elements.  Parts that
+   were runs of neighbouring tiles read and wrote as many windows as there are
+   workgroups, each far from the next (512 requests of 2^10..2^20 elements:
+   169.7 us a pass, 166.0 in turn; 4096 of 2^10..2^22: 5.09 ms and 4.97). */
 template <typename T, class Map>
-__device__ __forceinline__ void chunk_walk(uint64_t addr, uint64_t begin, uint64_t end, const Map& map)
+__device__ __forceinline__ void chunk_walk(uint64_t addr, uint64_t part, uint64_t parts, const Map& map)
 {
     const ReqPtr R = uniform_req(addr);
-    begin = wave_uniform(begin);
-    end = wave_uniform(end);
-    const Span<T> s = make_span((const T*)R->in + begin, (T*)R->out + begin, end - begin);
+    part = wave_uniform(part);
+    parts = wave_uniform(parts);
+    const Span<T> s = make_span((const T*)R->in, (T*)R->out, R->n);
     const uint32_t lane = wave_lane();
     Walk<T, BATCH_UNROLL> w;
-    w.begin(s, wave_uniform(threadIdx.x >> 6), blockDim.x >> 6, lane);
+    w.begin(s, part * 4 + wave_uniform(threadIdx.x >> 6), parts * 4, lane);
     w.run(s, lane, map);
-    run_edges(s, map);
+    if (part == 0) run_edges(s, map);
 }
 
 extern __shared__ __attribute__((aligned(16))) double lds_tab[];
@@ -63,9 +67,9 @@ extern __shared__ __attribute__((aligned(16))) double lds_tab[];
    table parameters are read from its descriptor inside (passed by value they
    went through every lane's scratch memory). */
 template <typename T, class Op>
-static __device__ __noinline__ void chunk_op(uint64_t addr, uint64_t begin, uint64_t end)
+static __device__ __noinline__ void chunk_op(uint64_t addr, uint64_t part, uint64_t parts)
 {
-    chunk_walk<T>(addr, begin, end, typename MapOf<T, Op>::type());
+    chunk_walk<T>(addr, part, parts, typename MapOf<T, Op>::type());
 }
 
 /* LDS list of the hybrid quantiles' gather: 64 K elements per wave (K = 4
@@ -82,30 +86,30 @@ __device__ __forceinline__ double* gather_list()
    gather, so that the outer path runs once per 64 outer elements rather than
    on every lane of a wave holding one; bitwise the per-element function. */
 template <typename T, class H>
-static __device__ __noinline__ void chunk_hybrid(uint64_t addr, uint64_t begin, uint64_t end)
+static __device__ __noinline__ void chunk_hybrid(uint64_t addr, uint64_t part, uint64_t parts)
 {
-    chunk_walk<T>(addr, begin, end, HybridMap<T, H>{reinterpret_cast<T*>(gather_list()), wave_lane()});
+    chunk_walk<T>(addr, part, parts, HybridMap<T, H>{reinterpret_cast<T*>(gather_list()), wave_lane()});
 }
 
 /* Student t from the table in LDS (referenced by symbol, so the loads stay
    LDS loads). */
 template <typename T, int DEG>
-static __device__ __noinline__ void chunk_t(uint64_t addr, uint64_t begin, uint64_t end)
+static __device__ __noinline__ void chunk_t(uint64_t addr, uint64_t part, uint64_t parts)
 {
     const StudentParams P = *(const StudentParams*)&uniform_req(addr)->P;
-    chunk_walk<T>(addr, begin, end, StudentMap<T, DEG>{lds_tab, P});
+    chunk_walk<T>(addr, part, parts, StudentMap<T, DEG>{lds_tab, P});
 }
 
 /* Exponential -> hyperbolic from the cells in LDS. */
 template <typename T, int DEG>
-static __device__ __noinline__ void chunk_h(uint64_t addr, uint64_t begin, uint64_t end)
+static __device__ __noinline__ void chunk_h(uint64_t addr, uint64_t part, uint64_t parts)
 {
     const HypParams H = *(const HypParams*)&uniform_req(addr)->H;
-    chunk_walk<T>(addr, begin, end, HypMap<T, DEG>{lds_tab, H});
+    chunk_walk<T>(addr, part, parts, HypMap<T, DEG>{lds_tab, H});
 }
 
-/* Elements [begin, end) of the request R; *loaded: the table in LDS. */
-__device__ __forceinline__ void do_chunk(ReqPtr R, uint64_t begin, uint64_t end, const double** loaded)
+/* Part `part` of the `parts` of the request R; *loaded: the table in LDS. */
+__device__ __forceinline__ void do_chunk(ReqPtr R, uint64_t part, uint64_t parts, const double** loaded)
 {
     const uint64_t addr = (uint64_t)R;
     const uint32_t op = R->op;
@@ -126,26 +130,26 @@ __device__ __forceinline__ void do_chunk(ReqPtr R, uint64_t begin, uint64_t end,
         }
     }
     switch (op) {
-    case BOP_NQ64_PLAIN: chunk_hybrid<double, HybridNQ64>(addr, begin, end); break;
-    case BOP_NQ64_PAPER: chunk_op<double, OpNQ64Paper>(addr, begin, end); break;
-    case BOP_NQ32_REFINE: chunk_hybrid<float, HybridNQ32>(addr, begin, end); break;
-    case BOP_NQ32_PAPER: chunk_op<float, OpNQ32Paper>(addr, begin, end); break;
-    case BOP_NQ32_PLAIN: chunk_op<float, OpNQ32Plain>(addr, begin, end); break;
-    case BOP_E64_PLAIN: chunk_op<double, OpE64Plain>(addr, begin, end); break;
-    case BOP_E64_PAPER: chunk_op<double, OpE64Paper>(addr, begin, end); break;
-    case BOP_E32_REFINE: chunk_op<float, OpE32Refine>(addr, begin, end); break;
-    case BOP_E32_PLAIN: chunk_op<float, OpE32Plain>(addr, begin, end); break;
+    case BOP_NQ64_PLAIN: chunk_hybrid<double, HybridNQ64>(addr, part, parts); break;
+    case BOP_NQ64_PAPER: chunk_op<double, OpNQ64Paper>(addr, part, parts); break;
+    case BOP_NQ32_REFINE: chunk_hybrid<float, HybridNQ32>(addr, part, parts); break;
+    case BOP_NQ32_PAPER: chunk_op<float, OpNQ32Paper>(addr, part, parts); break;
+    case BOP_NQ32_PLAIN: chunk_op<float, OpNQ32Plain>(addr, part, parts); break;
+    case BOP_E64_PLAIN: chunk_op<double, OpE64Plain>(addr, part, parts); break;
+    case BOP_E64_PAPER: chunk_op<double, OpE64Paper>(addr, part, parts); break;
+    case BOP_E32_REFINE: chunk_op<float, OpE32Refine>(addr, part, parts); break;
+    case BOP_E32_PLAIN: chunk_op<float, OpE32Plain>(addr, part, parts); break;
     case BOP_T64:
-        if (R->P.identity) chunk_op<double, OpCopy<double>>(addr, begin, end);
-        else if (R->P.row_shift == 4) chunk_t<double, T_DEGREE_HIGH>(addr, begin, end);
-        else chunk_t<double, T_DEGREE_LOW>(addr, begin, end);
+        if (R->P.identity) chunk_op<double, OpCopy<double>>(addr, part, parts);
+        else if (R->P.row_shift == 4) chunk_t<double, T_DEGREE_HIGH>(addr, part, parts);
+        else chunk_t<double, T_DEGREE_LOW>(addr, part, parts);
         break;
     case BOP_T32:
-        if (R->P.identity) chunk_op<float, OpCopy<float>>(addr, begin, end);
-        else chunk_t<float, T_DEGREE_F32>(addr, begin, end);
+        if (R->P.identity) chunk_op<float, OpCopy<float>>(addr, part, parts);
+        else chunk_t<float, T_DEGREE_F32>(addr, part, parts);
         break;
-    case BOP_H64: chunk_h<double, HYP_DEGREE>(addr, begin, end); break;
-    case BOP_H32: chunk_h<float, HYP_DEGREE_F32>(addr, begin, end); break;
+    case BOP_H64: chunk_h<double, HYP_DEGREE>(addr, part, parts); break;
+    case BOP_H32: chunk_h<float, HYP_DEGREE_F32>(addr, part, parts); break;
     default: break;
     }
 }
@@ -161,8 +165,7 @@ __device__ __forceinline__ void do_chunk(ReqPtr R, uint64_t begin, uint64_t end,
  * lane: two dependent loads for 4096 requests where a binary search took
  * twelve.
  */
-__device__ __forceinline__ void batch_chunks(uint64_t total, uint32_t nreq, uint64_t chunk, ReqPtr reqs, uint32_t* count,
-                                             uint32_t* done)
+__device__ __forceinline__ void batch_chunks(uint64_t total, uint32_t nreq, ReqPtr reqs, uint32_t* count, uint32_t* done)
 {
     const uint32_t lane = wave_lane();
     const double* loaded = nullptr;        /* table currently in LDS (uniform) */
@@ -176,10 +179,9 @@ __device__ __forceinline__ void batch_chunks(uint64_t total, uint32_t nreq, uint
             len = min(stride, len - skip);
         }
         const ReqPtr R = reqs + lo;
-        const uint64_t begin = (c - R->chunk_base) * chunk, n = R->n;
-        const uint64_t end = begin + chunk < n ? begin + chunk : n;
+        const uint64_t first = R->chunk_base, next = lo + 1 < nreq ? reqs[lo + 1].chunk_base : total;
         if (c != blockIdx.x) __syncthreads();      /* every wave is done with the LDS */
-        do_chunk(R, begin, end, &loaded);
+        do_chunk(R, c - first, next - first, &loaded);
         if (done && R->flagged) {
             /* per-request completion: every wave's stores of the chunk have
                reached the XCD's L2 before the barrier, one thread's release
@@ -205,7 +207,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 {
     typedef const __attribute__((address_space(4))) BatchHeader* HdrPtr;
     const HdrPtr h = (HdrPtr)(uint64_t)hdr;
-    batch_chunks(h->total_chunks, h->nreq, h->chunk, (ReqPtr)(uint64_t)reqs, h->count, h->done);
+    batch_chunks(h->total_chunks, h->nreq, (ReqPtr)(uint64_t)reqs, h->count, h->done);
 }
 
 /* The batch in the kernel's arguments: read from the argument segment, which
@@ -214,7 +216,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 {
     typedef const __attribute__((address_space(4))) BatchArgs* ArgsPtr;
     const ArgsPtr a = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
-    batch_chunks(a->h.total_chunks, a->h.nreq, a->h.chunk, a->r, a->h.count, a->h.done);
+    batch_chunks(a->h.total_chunks, a->h.nreq, a->r, a->h.count, a->h.done);
 }
 
 /*

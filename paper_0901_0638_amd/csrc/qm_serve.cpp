@@ -203,9 +203,9 @@ static uint32_t batch_op(const qm_request& r)
    [chunk_floor, QM_CHUNK_MAX], a multiple of QM_CHUNK_MIN.  Fewer, larger
    chunks leave the last of them running alone, more pay the start of a
    chunk (descriptor, table, first loads) too often: 512 requests of
-   2^10..2^20 elements take 195 us a pass with 4 rounds, 186 with 8, 201 with
-   16; 4096 requests of 2^10..2^22 elements 5.13 ms in chunks of 16384, 5.39 of
-   32768, 5.29 of 8192.  A lone request is spread over the whole GPU: of 2^15 elements it took
+   2^10..2^20 elements take 177 us a pass with 4 rounds, 166 with 8, 172 with
+   12; 4096 requests of 2^10..2^22 elements 4.97 ms in chunks of 16384, 5.30 of
+   32768, 5.06 of 8192.  A lone request is spread over the whole GPU: of 2^15 elements it took
    30 us in one chunk of that size, and takes 6 in sixteen. */
 constexpr uint64_t BATCH_ROUNDS = 8;
 static uint64_t batch_chunk(uint64_t total_n, int cus)
