@@ -16,7 +16,7 @@ sample.
     --workload batch   4096 mixed requests (sizes log-uniform 2^10..2^22,
                        40% quantile FP32+refine, 20% quantile FP64, 30%
                        Student t nu in 1..50, 10% exp -> normal), seed 3:
-                       one persistent launch vs one launch per request.
+                       one batched launch vs one launch per request.
     --workload serve   Poisson arrivals at swept rates, sizes 2^12..2^24,
                        same mix, HBM budget 64 GB: p50/p99 latency and
                        Gsamples/s, vs the same trace as sequential launches.
@@ -764,7 +764,7 @@ def run_hyperbolic(args, torch, qm, qi):
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": counted_traffic("hyperbolic_exp_2e26_hbm_counters.md", "k_hyperbolic<double>",
                                                 HYPERBOLIC_SOURCES),
-                     "kernel": "qm::k_hyperbolic<double, 2, 11> (64 workgroups per CU, tiles of 2 vectors a lane)",
+                     "kernel": "qm::k_hyperbolic<double, 2, 11> (a workgroup for every two tiles of 2 vectors a lane)",
                      "algorithmic_bytes_per_launch": 16.0 * n, "avg_launch_ms": round(avg64, 4),
                      "profiler_avg_launch_ms": profiler_avg_ms("hyperbolic_exp_2e26_kernel_stats.md",
                                                                "k_hyperbolic<double>", HYPERBOLIC_SOURCES)},

@@ -163,6 +163,7 @@ __device__ __forceinline__ void run_edges(const Span<T>& s, const Map& map)
     }
 }
 
+/* launches of the last two kinds of KernelShape */
 inline bool launch_big(uint64_t nvec, const KernelShape& ks) { return ks.big_vecs && nvec >= ks.big_vecs; }
 inline bool launch_huge(uint64_t nvec, const KernelShape& ks) { return ks.huge_vecs && nvec >= ks.huge_vecs; }
 
@@ -171,9 +172,9 @@ inline bool launch_huge(uint64_t nvec, const KernelShape& ks) { return ks.huge_v
  * while the grid would have fewer than two workgroups of 256 for each
  * compute unit; a big launch's own.  A short launch is bound by the latency of
  * one tile, which grows with the elements a lane holds, and by the compute
- * units left idle: on MI355X 2^17 FP64 hyperbolic samples took 4.3 us with four vectors per
- * lane and 3.3 with one, fused FP32 ones 7.5 and 3.7; at 2^20 (two
- * workgroups per unit with four vectors) the three are within 5%.
+ * units left idle: on MI355X 2^17 FP64 hyperbolic samples took 4.3 us with
+ * four vectors per lane and 3.3 with one, fused FP32 ones 7.5 and 3.7; at 2^20
+ * (two workgroups per unit with four vectors) the three are within 5%.
  */
 inline int launch_unroll(uint64_t nvec, const KernelShape& ks, int cus)
 {
@@ -200,7 +201,7 @@ inline int launch_unroll(uint64_t nvec, const KernelShape& ks, int cus)
  * is slower there (Student t 2^26 187, quantiles 182 against 172), and two
  * neighbouring tiles are too at some sizes (quantiles 2^28 741).  From two
  * tiles for each of 64 workgroups per unit on (FP32 maps, which are closer to
- * their arithmetic: 128).  From eight times 256 MB on one tile of four vectors
+ * their arithmetic: 128), 256 MB or so.  From 2 GB on one tile of four vectors
  * each does as well or better: FP64 2^28, Student t 687 (nu = 4), 708 (nu = 1)
  * and 743 (nu = 30) with two tiles, 696..702 with one, exp -> normal 690 and
  * 675, hyperbolic 705 and 710, quantiles 705 and 701.
