@@ -65,15 +65,14 @@ static uint64_t batch_flag_chunks()
 }
 
 /* Requests per batch that get a completion flag (a batch with more relies
-   on its event alone); one host-coherent array of this many words per
-   serving stream, and one of counts per staging slot. */
+   on its event alone); one host-coherent array of this many words and one of
+   chunk counts in device memory per serving stream. */
 constexpr size_t SERVE_FLAGS = 4096;
 
 struct Staging {
     void* host = nullptr;
     void* dev = nullptr;
     size_t cap = 0;
-    uint32_t* count = nullptr; /* per-request chunk counts: SERVE_FLAGS words, all 0 between launches */
     hipEvent_t ev = nullptr;
     bool busy = false;         /* held by a caller between acquire and event record */
 };
@@ -102,16 +101,15 @@ void runner_free(qm_ctx* ctx)
         }
         if (s->host) (void)hipHostFree(s->host);
         if (s->dev) (void)hipFree(s->dev);
-        if (s->count) (void)hipFree(s->count);
         delete s;
     }
     delete r;
     ctx->runner = nullptr;
 }
 
-/* A staging slot with at least `bytes` of pinned host and device memory, and
-   with zeroed chunk counts if asked for, whose previous use has completed. */
-static qm_status acquire_slot(BatchRunner* br, size_t bytes, bool counts, Staging** out)
+/* A staging slot with at least `bytes` of pinned host and device memory,
+   whose previous use has completed. */
+static qm_status acquire_slot(BatchRunner* br, size_t bytes, Staging** out)
 {
     std::unique_lock<std::mutex> lk(br->mu);
     Staging* slot = nullptr;
@@ -164,17 +162,6 @@ static qm_status acquire_slot(BatchRunner* br, size_t bytes, bool counts, Stagin
             return set_error(QM_E_NOMEM, "staging allocation failed");
         }
         slot->cap = cap;
-    }
-    if (counts && !slot->count) {
-        static const uint32_t zero[SERVE_FLAGS] = {};
-        if (hipMalloc((void**)&slot->count, sizeof zero) != hipSuccess ||
-            hipMemcpy(slot->count, zero, sizeof zero, hipMemcpyHostToDevice) != hipSuccess) {
-            if (slot->count) (void)hipFree(slot->count);
-            slot->count = nullptr;
-            std::lock_guard<std::mutex> g(br->mu);
-            slot->busy = false;
-            return set_error(QM_E_NOMEM, "staging allocation failed");
-        }
     }
     *out = slot;
     return QM_OK;
@@ -325,7 +312,7 @@ static hipError_t launch_in_args(const BatchHeader& h, const BatchReq* reqs, siz
  * into it (the caller owns the event).
  */
 qm_status enqueue_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count, hipStream_t s, hipEvent_t done,
-                        uint32_t* flags)
+                        uint32_t* flags, uint32_t* counts)
 {
     qm_status st = validate_batch(ctx, reqs, count);
     if (st != QM_OK) return st;
@@ -365,10 +352,10 @@ qm_status enqueue_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count, hip
         return QM_OK;
     }
     Staging* slot = nullptr;
-    st = acquire_slot(runner_of(ctx), in_args ? 0 : bytes, flags != nullptr, &slot);
+    st = acquire_slot(runner_of(ctx), in_args ? 0 : bytes, &slot);
     if (st != QM_OK) return st;
     if (flags) {
-        h.count = slot->count;
+        h.count = counts;
         h.done = flags;
     }
     hipError_t e;
@@ -506,6 +493,7 @@ struct Server {
     hipStream_t streams[SERVE_STREAMS] = {};
     bool stream_busy[SERVE_STREAMS] = {};
     uint32_t* flags[SERVE_STREAMS] = {};  /* host-coherent, device-visible; NULL: events only */
+    uint32_t* counts[SERVE_STREAMS] = {}; /* chunk counts beside them, all 0 between launches */
     std::vector<InFlight> inflight;
     std::vector<hipEvent_t> free_events;
 };
@@ -663,7 +651,7 @@ static void server_loop(Server* S)
         hipStream_t st = S->streams[idle];
         S->stream_busy[idle] = true;
         if (!ev) (void)hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-        qm_status rc = enqueue_batch(S->ctx, reqs.data(), reqs.size(), st, ev, flags);
+        qm_status rc = enqueue_batch(S->ctx, reqs.data(), reqs.size(), st, ev, flags, S->counts[idle]);
         if (rc != QM_OK) {
             std::lock_guard<std::mutex> lk(S->mu);
             for (uint64_t t : admit) {
@@ -681,6 +669,44 @@ static void server_loop(Server* S)
     }
 }
 
+/*
+ * Completion flags of serving stream i, in pinned host memory that the GPU
+ * writes through to while a batch runs, and the chunk counts beside them.  A
+ * stream carries one batch at a time and every launch leaves the counts 0, so
+ * they are cleared here once, by a copy kernel on that stream: the scheduler
+ * allocates nothing for them, and nothing waits for the caller's own streams
+ * (a synchronous copy is ordered after all work on the default one).
+ * Without them (an allocation failed) every request completes with its
+ * batch's event.
+ */
+static void make_flags(Server* S, int i)
+{
+    const size_t bytes = SERVE_FLAGS * sizeof(uint32_t);
+    void *flags = nullptr, *counts = nullptr;
+    bool ok = hipHostMalloc(&flags, bytes, hipHostMallocCoherent) == hipSuccess &&
+              hipMalloc(&counts, bytes) == hipSuccess;
+    if (ok) {
+        memset(flags, 0, bytes);
+        ok = launch_upload(flags, counts, bytes, S->streams[i]) == hipSuccess;
+    }
+    if (!ok) {
+        if (counts) (void)hipFree(counts);
+        if (flags) (void)hipHostFree(flags);
+        (void)hipGetLastError();
+        return;
+    }
+    S->flags[i] = static_cast<uint32_t*>(flags);
+    S->counts[i] = static_cast<uint32_t*>(counts);
+}
+
+static void free_flags(Server* S)
+{
+    for (int i = 0; i < SERVE_STREAMS; ++i) {
+        if (S->flags[i]) (void)hipHostFree(S->flags[i]);
+        if (S->counts[i]) (void)hipFree(S->counts[i]);
+    }
+}
+
 static Server* server_of(qm_ctx* ctx, qm_status* st)
 {
     std::lock_guard<std::mutex> lk(ctx->server_mu);
@@ -691,19 +717,15 @@ static Server* server_of(qm_ctx* ctx, qm_status* st)
     for (int i = 0; i < SERVE_STREAMS; ++i) {
         if (hipStreamCreateWithFlags(&S->streams[i], hipStreamNonBlocking) != hipSuccess) {
             for (int j = 0; j < i; ++j) {
+                (void)hipStreamSynchronize(S->streams[j]);
                 (void)hipStreamDestroy(S->streams[j]);
-                if (S->flags[j]) (void)hipHostFree(S->flags[j]);
             }
+            free_flags(S);
             delete S;
             *st = set_error(QM_E_HIP, "hipStreamCreate failed");
             return nullptr;
         }
-        /* completion flags in pinned host memory that the GPU writes
-           through to while a batch runs; without them (allocation failed)
-           every request completes with its batch's event */
-        void* p = nullptr;
-        if (hipHostMalloc(&p, SERVE_FLAGS * sizeof(uint32_t), hipHostMallocCoherent) == hipSuccess)
-            S->flags[i] = static_cast<uint32_t*>(p);
+        make_flags(S, i);
     }
     S->th = std::thread(server_loop, S);
     ctx->server = S;
@@ -729,8 +751,7 @@ void server_stop(Server* S)
             (void)hipStreamSynchronize(S->streams[i]);
             (void)hipStreamDestroy(S->streams[i]);
         }
-    for (int i = 0; i < SERVE_STREAMS; ++i)
-        if (S->flags[i]) (void)hipHostFree(S->flags[i]);
+    free_flags(S);
     delete S;
 }
 

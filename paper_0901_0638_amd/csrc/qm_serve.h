@@ -36,10 +36,11 @@ qm_status set_error(qm_status s, const char* msg);
 
 /* Validate and enqueue requests as one launch (done: optional
    event recorded after it).  flags, if not NULL, is a host-coherent array
-   with a zero word for each request with n > 0, in request order: the
-   launch sets a request's word to 1 once its output is complete. */
+   with a zero word for each request with n > 0, in request order, and counts
+   a device array of as many zero words: the launch sets a request's word to 1
+   once its output is complete, and leaves its count 0. */
 qm_status enqueue_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count, hipStream_t s, hipEvent_t done,
-                        uint32_t* flags = nullptr);
+                        uint32_t* flags = nullptr, uint32_t* counts = nullptr);
 void runner_free(qm_ctx* ctx);
 void server_stop(Server* s);
 
