@@ -211,12 +211,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 }
 
 /* The batch in the kernel's arguments: read from the argument segment, which
-   starts with them (indexing the parameter would copy it to scratch). */
+   starts with them (indexing the parameter would copy it to scratch).  Such a
+   batch has no completion flags. */
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_batch_args(BatchArgs)
 {
     typedef const __attribute__((address_space(4))) BatchArgs* ArgsPtr;
     const ArgsPtr a = (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
-    batch_chunks(a->h.total_chunks, a->h.nreq, a->r, a->h.count, a->h.done);
+    batch_chunks(a->h.total_chunks, a->h.nreq, a->r, nullptr, nullptr);
 }
 
 /*

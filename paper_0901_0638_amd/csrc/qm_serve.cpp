@@ -47,12 +47,19 @@ namespace qm {
    write-back and a count, 64 ns each beside the streams and one after the
    other (MI355X: 1100 flagged chunks took 80 us where the batch's work takes
    14).  So only requests of at most sixteen chunks are flagged, and as many
-   of a batch's, in order, as add two hundredths to its time at about 350 G
-   elements/s: one chunk for each 2^20 elements (with one for each 2^18 the
-   p99 at 50k requests/s was 0.35 ms, 0.26 with few).  The others complete with the
-   batch's event; so does a whole batch of under 2^24 elements, which is over
-   some tens of microseconds after its first request. */
-constexpr uint64_t FLAG_MIN_ELEMENTS = 1 << 24, FLAG_ELEMENTS_PER_CHUNK = 1 << 20;
+   of a batch's, in order, as cost it a third of its time at about 350 G
+   elements/s: one chunk for each 2^16 elements.  That covers the small
+   requests beside large ones, which gain by it (median until a request is
+   observed complete: 200 of 2^15 elements before one of 2^26 117 us, 240 with
+   one chunk for each 2^20 elements, 100 of 2^17 before 2^26 138 and 255; 8 of
+   2^12 in a batch of under 2^24 22, 82 with such batches unflagged), and
+   leaves a batch of nothing but small ones mostly to its event, which is then
+   the earlier of the two (512 of 2^15: 90 us, 445 with every request flagged).
+   2000 requests of 2^12..2^24 elements at once run at 330 G elements/s with
+   this, 345 with the smaller budget.  A batch of under 2^22 elements is over
+   within some 20 us and has no flags (8 requests of 2^10..2^18: 42 us, 47 with
+   them). */
+constexpr uint64_t FLAG_MIN_ELEMENTS = 1 << 22, FLAG_ELEMENTS_PER_CHUNK = 1 << 16;
 static uint64_t batch_flag_chunks()
 {
     /* tuning: QM_SERVE_FLAG_CHUNKS overrides the limit (0: completion by
@@ -329,46 +336,35 @@ qm_status enqueue_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count, hip
         if (done && hipEventRecord(done, s) != hipSuccess) return set_error(QM_E_HIP, "hipEventRecord failed");
         return QM_OK;
     }
-    const bool in_args = fits_args(ctx, h);
-    if (flags) {
-        uint64_t total = 0, budget = 0;
-        for (const BatchReq& r : d) total += r.n;
-        budget = total < FLAG_MIN_ELEMENTS ? 0 : total / FLAG_ELEMENTS_PER_CHUNK;
-        bool any = false;
-        for (BatchReq& r : d) {
-            const uint64_t c = (r.n + h.chunk - 1) / h.chunk;
-            if (c > batch_flag_chunks() || c > budget) continue;
-            budget -= c;
-            r.flagged = (uint32_t)c;
-            any = true;
-        }
-        if (!any) flags = nullptr;
-    }
-    const size_t bytes = sizeof(BatchHeader) + d.size() * sizeof(BatchReq);
-    if (in_args && !flags) {
+    if (fits_args(ctx, h)) {        /* over within some 20 us: its event completes it */
         hipError_t e = launch_in_args(h, d.data(), lds, s);
         if (e != hipSuccess) return set_error(QM_E_HIP, hipGetErrorString(e));
         if (done && hipEventRecord(done, s) != hipSuccess) return set_error(QM_E_HIP, "hipEventRecord failed");
         return QM_OK;
     }
-    Staging* slot = nullptr;
-    st = acquire_slot(runner_of(ctx), in_args ? 0 : bytes, &slot);
-    if (st != QM_OK) return st;
     if (flags) {
-        h.count = counts;
-        h.done = flags;
+        uint64_t total = 0, budget = 0;
+        for (const BatchReq& r : d) total += r.n;
+        budget = total < FLAG_MIN_ELEMENTS ? 0 : total / FLAG_ELEMENTS_PER_CHUNK;
+        for (BatchReq& r : d) {
+            const uint64_t c = (r.n + h.chunk - 1) / h.chunk;
+            if (c > batch_flag_chunks() || c > budget) continue;
+            budget -= c;
+            r.flagged = (uint32_t)c;
+            h.count = counts;
+            h.done = flags;
+        }
     }
-    hipError_t e;
-    if (in_args) {
-        e = launch_in_args(h, d.data(), lds, s);
-    } else {
-        memcpy(slot->host, &h, sizeof h);
-        memcpy((char*)slot->host + sizeof h, d.data(), d.size() * sizeof(BatchReq));
-        e = launch_upload(slot->host, slot->dev, bytes, s);
-        if (e == hipSuccess)
-            e = launch_batch((const BatchHeader*)slot->dev, (const BatchReq*)((char*)slot->dev + sizeof h), lds,
-                             batch_blocks(ctx, h.total_chunks), s);
-    }
+    const size_t bytes = sizeof(BatchHeader) + d.size() * sizeof(BatchReq);
+    Staging* slot = nullptr;
+    st = acquire_slot(runner_of(ctx), bytes, &slot);
+    if (st != QM_OK) return st;
+    memcpy(slot->host, &h, sizeof h);
+    memcpy((char*)slot->host + sizeof h, d.data(), d.size() * sizeof(BatchReq));
+    hipError_t e = launch_upload(slot->host, slot->dev, bytes, s);
+    if (e == hipSuccess)
+        e = launch_batch((const BatchHeader*)slot->dev, (const BatchReq*)((char*)slot->dev + sizeof h), lds,
+                         batch_blocks(ctx, h.total_chunks), s);
     hipError_t e2 = hipEventRecord(slot->ev, s);
     {
         std::lock_guard<std::mutex> g(runner_of(ctx)->mu);

@@ -31,10 +31,9 @@ def submit_group(ctx, x, y, smalls):
     """Tickets of a request of the whole budget, then of `smalls` (outputs, in
     order) and one request of the rest of the budget, admitted together."""
     used = sum(s.numel() for s in smalls)
-    block = qm.qm_submit(ctx, quantile(x, y[0]))
-    small = [qm.qm_submit(ctx, quantile(x[:s.numel()], s)) for s in smalls]
-    big = qm.qm_submit(ctx, quantile(x[used:], y[1][used:]))
-    return block, small, big
+    reqs = [quantile(x, y[0])] + [quantile(x[:s.numel()], s) for s in smalls] + [quantile(x[used:], y[1][used:])]
+    tickets = [qm.qm_submit(ctx, r) for r in reqs]     # well within the first one's time
+    return tickets[0], tickets[1:-1], tickets[-1]
 
 
 def test_flags_do_not_wait_for_the_callers_streams(gpu):
@@ -82,5 +81,43 @@ def test_flags_do_not_wait_for_the_callers_streams(gpu):
         assert all(torch.equal(s, want[:4096]) for s in smalls)
         used = 8 * 4096
         assert torch.equal(y[0], want) and torch.equal(y[1][used:], want[used:])
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("total,sizes", [
+    ((1 << 24) - (1 << 16), [4096] * 8),
+    (1 << 26, [1 << 15] * 40),
+    (1 << 26, [1, 8192, 8193, 50001, 1 << 17]),       # 1, 1, 2, 7 and 16 chunks of 8192
+])
+def test_small_requests_complete_before_their_batch(gpu, total, sizes):
+    """Small requests beside a large one, however few elements the batch has
+    and however late they are in it: each is seen complete before the large one
+    (in one of five batches at least: the scheduler may look late), batch after
+    batch on the same counts, with its output whole when it is reported."""
+    x = torch.rand(total, device="cuda", dtype=torch.float64).clamp_(1e-6, 1 - 1e-6)
+    want = torch.empty_like(x)
+    y = [torch.empty_like(x) for _ in range(2)]
+    smalls = [torch.zeros(n, device="cuda", dtype=torch.float64) for n in sizes]
+    used = sum(sizes)
+    ctx = qm.Context(0, hbm_budget_bytes=16 * total)
+    try:
+        qm.qm_normal_quantile(ctx, x, want)
+        torch.cuda.synchronize()
+        early = [0] * len(sizes)
+        for turn in range(6):
+            for s in smalls:
+                s.zero_()
+            torch.cuda.synchronize()
+            block, small, big = submit_group(ctx, x, y, smalls)
+            for s, t in zip(smalls, small):
+                wait(ctx, [t])
+                assert torch.equal(s, want[:s.numel()])
+            wait(ctx, [block, big])
+            end = qm.qm_poll_times(ctx, big)[2]
+            if turn:
+                early = [e + (qm.qm_poll_times(ctx, t)[2] < end) for e, t in zip(early, small)]
+            assert torch.equal(y[1][used:], want[used:])
+        assert min(early) > 0, early
     finally:
         ctx.close()
