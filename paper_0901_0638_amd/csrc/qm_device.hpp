@@ -411,10 +411,13 @@ __device__ __forceinline__ double div_pos_fast(double a, double b)
  * rational fitted to the accuracy that the rounding leaves room for takes
  * fewer than an FP32 seed with an FP64 correction step against erf or erfc,
  * which evaluates two or three functions for one: 21 issue slots against 28
- * for the central piece, 42 against 71 for the outer one, 33 against 69 for
- * exponential -> normal.  It is also closer to the exact value before the
- * rounding: 2.8e-9, 3.2e-9 and 1e-11 relative, against 2.5e-8, 1.5e-8 and
- * 1e-11 absolute.  MI355X, per pass: 2^24 exponential -> normal 39.4 -> 29.0
+ * for the central piece, 42 against 71 for the outer one, 37 against 69 for
+ * exponential -> normal.  Before the rounding the central and the outer piece
+ * are off by 2.8e-9 and 3.2e-9 relative at most (2.5e-8 and 1.5e-8 with the
+ * seeds), exponential -> normal by 6e-14, which is nowhere more than its seed
+ * and correction step were (1.5e-13 between 5 and 10, more elsewhere); a
+ * rational of degree 10 was (9.5e-12).  MI355X, per pass, without the later
+ * steps: 2^24 exponential -> normal 39.4 -> 29.0
  * us, 2^26 mixture quantiles 106 -> 102, 2^26 fused quantiles 98.3 -> 94.4
  * (all bound by vector instructions before).
  */
@@ -482,7 +485,7 @@ __device__ __forceinline__ float normal_quantile_f32_plain(float u)
     return (float)normal_quantile_f64<false>((double)u);
 }
 
-/* Exponential -> normal for FP32 x: Q(v) = v P10(v)/Q10(v), v = |x| <= 103;
+/* Exponential -> normal for FP32 x: Q(v) = v P12(v)/Q12(v), v = |x| <= 103;
    beyond (also inf and NaN) the plain FP64 map, rounded. */
 __device__ __forceinline__ float exp_to_normal_f32_main(float x, bool* rare)
 {
