@@ -39,8 +39,9 @@ These approximations are fitted here, the rest are the paper's constants:
     the pieces above (an FP32 seed and one FP64 correction step), whose
     constants remain as the form they describe is still checked.  Central:
     q P4(r)/Q4(r) for |q| <= 0.45, r = 0.2025 - q^2.  Outer: v = -log 2p with
-    log m a degree-9 polynomial on [1/2, 1], then z = P7(v)/Q6(v) down to the
-    smallest FP32 p.  Exponential -> normal: z = v P12(v)/Q12(v), v <= 103
+    log m a degree-10 polynomial on [1/2, 1], then z = P7(v)/Q7(v) down to the
+    smallest FP32 p (degrees 9 and (7, 6) were further off than a seed and
+    correction step between |z| = 1.64 and 6).  Exponential -> normal: z = v P12(v)/Q12(v), v <= 103
     (degree 12 and not 10, 9.5e-12, because the seed and correction step were
     as close as 1e-13 between 5 and 10).
   * The FP64 logarithm of the change of variable v = -log(2 min(u,1-u)):
@@ -219,17 +220,18 @@ def fit_direct(g, r_lo, X):
     out.append(carr("QM_D32_CP", p, "Phi^{-1}(1/2 + q)/q numerator in r = 0.2025 - q^2, FP32 form; rel err %.2e" % e))
     out.append(carr("QM_D32_CQ", q, "its denominator (constant term 1)"))
 
-    coef, e = fit_log_abs(mp.mpf("0.5"), mp.mpf(1), 9)
-    print("FP32 log (9): max abs %.3e" % e, file=sys.stderr)
+    coef, e = fit_log_abs(mp.mpf("0.5"), mp.mpf(1), 10)
+    print("FP32 log (10): max abs %.3e" % e, file=sys.stderr)
     out.append(carr("QM_D32_LOG", coef, "log m in m - 3/4, 1/2 <= m <= 1; abs err %.2e" % e))
 
     lo, hi = mp.log(-mp.log(2 * mp.mpf("0.0501"))), mp.log(mp.mpf("103.3"))
     span = lambda n: [mp.exp(t) for t in cheb_nodes(lo, hi, n)]
     xs = span(160)
-    _, p, q = fit_rational(xs, [q_exp(v) for v in xs], 7, 6)
+    with mp.workdps(50):
+        _, p, q = fit_rational(xs, [q_exp(v) for v in xs], 7, 7)
     dense = span(1501)
     e = rounded_error(p, q, dense, [q_exp(v) for v in dense])
-    print("FP32 outer (7,6): max rel %.3e" % e, file=sys.stderr)
+    print("FP32 outer (7,7): max rel %.3e" % e, file=sys.stderr)
     out.append(carr("QM_D32_OP", p, "Q(v) numerator in v, 2.3 <= v <= 103.3, FP32 form; rel err %.2e" % e))
     out.append(carr("QM_D32_OQ", q, "its denominator (constant term 1)"))
 

@@ -43,7 +43,7 @@ __device__ __forceinline__ double horner(double x, const double (&c)[N])
  */
 struct OuterCoeffs {
     double p13[14], q13[14], tail_p[8], tail_q[8], log_r[7];   /* FP64 */
-    double log32[10], p32[8], q32[7];                          /* FP32 */
+    double log32[11], p32[8], q32[8];                          /* FP32 */
 };
 template <int N>
 constexpr void copy_coeffs(double (&to)[N], const double (&from)[N])
@@ -411,19 +411,21 @@ __device__ __forceinline__ double div_pos_fast(double a, double b)
  * rational fitted to the accuracy that the rounding leaves room for takes
  * fewer than an FP32 seed with an FP64 correction step against erf or erfc,
  * which evaluates two or three functions for one: 21 issue slots against 28
- * for the central piece, 42 against 71 for the outer one, 37 against 69 for
- * exponential -> normal.  Before the rounding the central and the outer piece
- * are off by 2.8e-9 and 3.2e-9 relative at most (2.5e-8 and 1.5e-8 with the
- * seeds), exponential -> normal by 6e-14, which is nowhere more than its seed
- * and correction step were (1.5e-13 between 5 and 10, more elsewhere); a
- * rational of degree 10 was (9.5e-12).  MI355X, per pass, without the later
+ * for the central piece, 44 against 71 for the outer one, 37 against 69 for
+ * exponential -> normal.  Before the rounding the central piece is off by
+ * 2.8e-9 relative at most, the outer one by 6e-10 and exponential -> normal
+ * by 6e-14, nowhere more than a seed and correction step were in the same
+ * range: those had 4.8e-9 to 2.3e-8, 1.0e-9 (|z| between 4 and 5) to 1.0e-8,
+ * and 1.5e-13 (between 5 and 10) or more; rationals of one or two degrees
+ * less, outer 3e-9, exponential -> normal 9.5e-12, were further off in parts
+ * of their ranges.  MI355X, per pass, without the later
  * steps: 2^24 exponential -> normal 39.4 -> 29.0
  * us, 2^26 mixture quantiles 106 -> 102, 2^26 fused quantiles 98.3 -> 94.4
  * (all bound by vector instructions before).
  */
 
 /* Phi^{-1}(u) for FP32 u outside the centre: p = min(u, 1-u) (exact), v =
-   -log 2p from p = m 2^e (4.5e-9, a third of that in z), Q(v) = P7/Q6. */
+   -log 2p from p = m 2^e (7.1e-10, a third of that in z), Q(v) = P7/Q7. */
 __device__ __forceinline__ float outer_quantile_f32(float u)
 {
     const double LN2 = 0.69314718055994530942;

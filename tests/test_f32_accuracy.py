@@ -4,7 +4,8 @@ correction step is there, which is what the stored rationals stand in for."""
 import mpmath as mp
 import numpy as np
 
-from tests.test_coefficients import arrays
+import oracle
+from tests.test_coefficients import arrays, exp_refine7
 
 
 def horner(c, x):
@@ -69,3 +70,39 @@ def test_exp_to_normal():
     old = x0 + t * (1 + 0.5 * x0 * t)
     new = v * horner(c["QM_E32_P"], v) / horner(c["QM_E32_Q"], v)
     no_further_off(v, [1e-4, 1e-3, 1e-2, 0.1, 0.5, 1, 2, 5, 10, 20, 42, 104], (new - hi - lo) / hi, (old - hi - lo) / hi)
+
+
+def test_outer_quantile():
+    """|z| > 1.64: seed v S4/S5 and one Newton step with the Mills ratio."""
+    c = arrays()
+    p32 = np.unique(np.geomspace(1.4e-45, 0.05, 40001).astype(np.float32))
+    p32 = p32[p32 > 0]
+    p = p32.astype(np.float64)
+    ref = -oracle.norm_quantile(p)
+    v32 = (-np.log(2 * p)).astype(np.float32)
+    x0 = seed(c, v32)
+    tail = p * 2.5066282746310005024 * exp_refine7(0.5 * (x0 * x0))
+    old = x0 + (horner(c["QM_MILLS32_P"], x0) / horner(c["QM_MILLS32_Q"], x0) - tail)
+    m, e = np.frexp(p)
+    v = -(e + 1) * np.log(2.0) - horner(c["QM_D32_LOG"], m - 0.75)
+    new = horner(c["QM_D32_OP"], v) / horner(c["QM_D32_OQ"], v)
+    no_further_off(ref, [1.64, 1.8, 2, 2.5, 3, 4, 5, 6, 8, 10, 12, 15], new / ref - 1, old / ref - 1)
+
+
+def test_central_quantile():
+    """|u - 1/2| <= 0.45: seed and one Newton step on Phi(z) = u."""
+    c = arrays()
+    u32 = np.linspace(0.05, 0.95, 100001).astype(np.float32)
+    u = u32.astype(np.float64)
+    q = u - 0.5
+    at = (np.abs(q) <= 0.45) & (q != 0)
+    u, q = u[at], q[at]
+    ref = oracle.norm_quantile(u)
+    qf = q.astype(np.float32)
+    rf = (np.float32(0.2025) - qf * qf).astype(np.float32)
+    z0 = (qf * horner32(c["QM_C32_SP"], rf) * (np.float32(1) / horner32(c["QM_C32_SQ"], rf))).astype(np.float64)
+    y = z0 * z0
+    old = z0 - (z0 * horner(c["QM_C32_E"], y) - q) * horner(c["QM_C32_G"], y)
+    r = 0.2025 - q * q
+    new = q * horner(c["QM_D32_CP"], r) / horner(c["QM_D32_CQ"], r)
+    no_further_off(np.abs(q), [0, 0.01, 0.05, 0.1, 0.2, 0.3, 0.35, 0.4, 0.4501], new / ref - 1, old / ref - 1)
