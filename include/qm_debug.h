@@ -1,8 +1,8 @@
 /*
  * qm_debug.h -- host-only diagnostic entry points of libqm (no device work).
  * They expose the table builders' intermediate results (Student t, and the
- * exponential -> hyperbolic map) so that their accuracy can be checked on a
- * machine without a GPU.
+ * exponential -> hyperbolic map) and what the host prepares or shares of the
+ * kernels, so that these can be checked on a machine without a GPU.
  */
 #ifndef QM_DEBUG_H
 #define QM_DEBUG_H
@@ -59,6 +59,13 @@ int qm_debug_hyperbolic_table(double alpha, double beta, double delta, void* hea
 /* The same for the variance-gamma table of (lambda, alpha, beta), real
    lambda in [1, 8] (the header's delta field holds lambda). */
 int qm_debug_vg_table(double lambda, double alpha, double beta, void* header_out, double* coef_out, int coef_cap);
+
+/*
+ * w[i] = a[i]^rho for 0 < a[i] <= 1, as the kernels form it for the origin
+ * series of a variance-gamma table, in the same steps on the host.  Host
+ * arrays of n doubles.  Returns 0.
+ */
+int qm_debug_pow_small(const double* a, double rho, double* w, int n);
 
 #ifdef __cplusplus
 }

@@ -371,28 +371,6 @@ __device__ __forceinline__ float neg_log_f32(float x)
     return __builtin_fmaf(-l2, LN2F, sub ? 32.0f * LN2F : 0.0f);
 }
 
-/* e^a for a <= 700: a = k ln2 + r, |r| <= ln2/2, the degree-DEG Taylor
-   polynomial in r, then scale by 2^k.  Relative error below the remainder
-   (ln2/2)^(DEG+1)/(DEG+1)!: 2e-16 for degree 12. */
-template <int DEG>
-__device__ __forceinline__ double exp_taylor(double a)
-{
-    const double LOG2E = 1.4426950408889634074, LN2_HI = 0.69314718055994528623, LN2_LO = 2.3190468138462996154e-17;
-    double k = __builtin_rint(a * LOG2E);
-    double r = __builtin_fma(-k, LN2_HI, a);
-    r = __builtin_fma(-k, LN2_LO, r);
-    double f = 1.0;
-#pragma unroll
-    for (int i = 2; i <= DEG; ++i) f *= i;           /* DEG!, folded at compile time */
-    double p = 1.0 / f;
-#pragma unroll
-    for (int i = DEG; i >= 1; --i) {
-        f /= i;                                       /* (i-1)! */
-        p = __builtin_fma(p, r, 1.0 / f);
-    }
-    return __builtin_ldexp(p, (int)k);
-}
-
 /* a / b to ~3e-15 for positive b of moderate size: hardware reciprocal and
    one Newton step, no residual correction (enough before a rounding to
    FP32). */

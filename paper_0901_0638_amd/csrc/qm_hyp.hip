@@ -133,3 +133,11 @@ hipError_t launch_hyperbolic(int dtype, int mode, const void* in, void* out, uin
 }
 
 }  // namespace qm
+
+/* Host evaluation of the origin series' power (include/qm_debug.h): the
+   reciprocal's float rounding stands in for the hardware's 5e-8. */
+extern "C" int qm_debug_pow_small(const double* a, double rho, double* w, int n)
+{
+    for (int i = 0; i < n; ++i) w[i] = qm::pow_small(a[i], rho, [](double x) { return (double)(float)(1.0 / x); });
+    return 0;
+}

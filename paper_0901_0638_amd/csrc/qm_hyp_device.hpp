@@ -130,13 +130,59 @@ __device__ __forceinline__ double hyp_near(double v, const double* __restrict__ 
     return a * hyp_cell<DEG>(lds, row, d);
 }
 
+/*
+ * a^rho for 0 < a <= 1, rho > 0, within 3e-16 relative.  log a = hi + lo to
+ * about 1e-18 absolute: a = m 2^e with m in [sqrt(1/2), sqrt(2)), log m =
+ * 2 atanh f as in neg_log_unit, with the remainders of f, of m + 1 and of the
+ * sum with e log 2 carried; an absolute error of rho log a is a relative one
+ * of the power, and |rho log a| reaches hundreds.  Then e^(hi + lo) = 2^k e^r,
+ * e^r by its Taylor polynomial of degree 13 (remainder 4e-18).  rcp: a
+ * reciprocal good to 5e-8.  a = 0 gives some finite value.  A logarithm and
+ * an exponential with no remainders were up to 1.2e-14 off in the power at
+ * rho = 7.5 for a not far below v0, 5.8e-14 at a^rho = 1e-300.  Variance-gamma
+ * (4.25, 1, 0.3), 2^24 samples on MI355X: FP64 50.7 us without the remainders,
+ * 51.2 with them, 56.5 with the library pow; FP32 32.7, 33.8 and 43.
+ */
+template <class Rcp>
+__host__ __device__ __forceinline__ double pow_small(double a, double rho, Rcp rcp)
+{
+    const double SQRT_HALF = 0.70710678118654752440, LOG2E = 1.4426950408889634074;
+    const double LN2_HI = 6.93147180369123816490e-01, LN2_LO = 1.90821492927058770002e-10;     /* e LN2_HI is exact */
+    const double LN2_D = 0.69314718055994528623, LN2_E = 2.3190468138462996154e-17;            /* ln 2 as two doubles */
+    int e;
+    double m = __builtin_frexp(a, &e);
+    const int up = m < SQRT_HALF;
+    m = __builtin_ldexp(m, up);
+    const double de = (double)(e - up);
+    const double n1 = m + 1.0, n2 = m - (n1 - 1.0);                 /* m + 1 = n1 + n2 */
+    double y = rcp(n1);
+    y = __builtin_fma(__builtin_fma(-n1, y, 1.0), y, y);
+    const double f0 = (m - 1.0) * y;
+    const double df = __builtin_fma(-f0, n2, __builtin_fma(-f0, n1, m - 1.0)) * y;
+    const double f = f0 + df, f_lo = df - (f - f0);                 /* (m - 1) / (m + 1) = f + f_lo */
+    double p = QM_LOG_R[0];
+    const double s = f * f, t = f + f, eh = de * LN2_HI;
+#pragma unroll
+    for (int i = 1; i < 7; ++i) p = __builtin_fma(p, s, QM_LOG_R[i]);
+    const double hi = eh + t;                                       /* |eh| >= |t|, or eh = 0 */
+    const double lo = (t - (hi - eh)) + __builtin_fma(de, LN2_LO, __builtin_fma(f * s, p, f_lo + f_lo));
+    const double x = rho * hi, x_lo = __builtin_fma(rho, lo, __builtin_fma(rho, hi, -x));
+    const double k = __builtin_rint(x * LOG2E);
+    const double r = __builtin_fma(-k, LN2_D, x) + __builtin_fma(-k, LN2_E, x_lo);
+    double fact = 6227020800.0;                                     /* 13!, folded with the loop */
+    double w = 1.0 / fact;
+#pragma unroll
+    for (int i = 13; i >= 1; --i) {
+        fact /= i;
+        w = __builtin_fma(w, r, 1.0 / fact);
+    }
+    return __builtin_ldexp(w, (int)k);
+}
+
 /* |Q(a)| in the first octave of a side with the origin series (row 0 of its
    cells, layout in qm_hyp_table.h; here in LDS): a R, R = P0(a) + w (P1(a) +
-   w (P2(a) + w P3(a))), w = a^rho = e^(rho log a); FP32-output cells have no
-   P3.  The terms in w are a small part of R near 0 (w <= v0^rho), so the
-   short logarithm and exponential (a few 1e-15 where w matters) are ample;
-   the library pow took three times their instructions.  Out of line: a
-   kernel's loop would hold its constants otherwise. */
+   w (P2(a) + w P3(a))), w = a^rho; FP32-output cells have no P3.  Out of line:
+   a kernel's loop would hold its constants otherwise. */
 typedef const __attribute__((address_space(3))) double* LdsRow;
 template <int DEG>
 static __device__ __noinline__ double hyp_origin(LdsRow row, double a)
@@ -145,7 +191,7 @@ static __device__ __noinline__ double hyp_origin(LdsRow row, double a)
        their degrees in v */
     constexpr int NFAM = DEG == HYP_DEGREE ? 4 : 3;
     constexpr int DG64[4] = {0, 1, 2, 4}, DG32[4] = {0, 1, 3, 0};
-    const double w = exp_taylor<12>(-row[0] * neg_log_unit(a));
+    const double w = pow_small(a, row[0], [](double x) { return __builtin_amdgcn_rcp(x); });
     double R = 0;
     int k = 1;
 #pragma unroll
@@ -267,7 +313,7 @@ __device__ __forceinline__ void one_per_lane(const double (&v)[K], double (&q)[K
  * pass serves it.  A vote for each of the K slots entered the far code once
  * per slot that held any, with the series' row from device memory and a
  * library pow each (2^24 FP64 samples of variance-gamma (4.25, 1, 0.3): 67.2
- * us on MI355X; 52.5 with the passes and the short power, 49.7 with the rows
+ * us on MI355X; 52.5 with the passes and a short power, 49.7 with the rows
  * in LDS).
  */
 template <int DEG, int K>
