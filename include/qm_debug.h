@@ -33,6 +33,14 @@ int qm_debug_student_dense(double nu, const double* z, double* q, int n);
 int qm_debug_student_table(double nu, void* header_out, double* coef_out, int coef_cap);
 
 /*
+ * Cell rows that a launch for nu stages in LDS (0 for the identity, nu =
+ * +inf), for FP64 or, with f32, FP32 outputs: *y_staged gets the z^2 up to
+ * which they reach, *lds_bytes the LDS they take.  Returns the number of rows,
+ * or -1 for an unsupported nu.
+ */
+int qm_debug_student_staging(double nu, int f32, double* y_staged, unsigned long long* lds_bytes);
+
+/*
  * The hyperbolic builder's solution of the exponential-background recycling
  * ODE (Section 8.1), q[i] = Q(v[i]) for |v[i]| <= 1e12: the Taylor-series
  * legs of each side within its anchor, the direct solution of the tail

@@ -94,6 +94,7 @@ SIGNATURES = {
 DEBUG_SIGNATURES = {
     "qm_debug_student_dense": (ctypes.c_int, [_d, ctypes.POINTER(_d), ctypes.POINTER(_d), ctypes.c_int]),
     "qm_debug_student_table": (ctypes.c_int, [_d, _vp, ctypes.POINTER(_d), ctypes.c_int]),
+    "qm_debug_student_staging": (ctypes.c_int, [_d, _i, ctypes.POINTER(_d), ctypes.POINTER(ctypes.c_ulonglong)]),
     "qm_debug_hyperbolic_dense": (ctypes.c_int, [_d, _d, _d, ctypes.POINTER(_d), ctypes.POINTER(_d), ctypes.c_int]),
     "qm_debug_hyperbolic_table": (ctypes.c_int, [_d, _d, _d, _vp, ctypes.POINTER(_d), ctypes.c_int]),
     "qm_debug_vg_table": (ctypes.c_int, [_d, _d, _d, _vp, ctypes.POINTER(_d), ctypes.c_int]),

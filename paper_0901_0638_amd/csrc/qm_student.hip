@@ -98,7 +98,8 @@ StudentParams make_params(const TTableHeader& h, const TCells& c, const double* 
     P.inv_nu = 1.0 / h.nu;
     P.nu = h.nu;
     P.ncell = c.ncell;
-    P.nlds = std::min(c.nlds, (int)std::ceil(T_Y_STAGED / c.h));
+    /* nu = +inf has no cells (h = 0) */
+    P.nlds = h.identity ? 0 : std::min(c.nlds, (int)std::ceil(T_Y_STAGED / c.h));
     P.y_lds = P.nlds * c.h;
     P.identity = h.identity;
     P.row_shift = c.stride == 16 ? 4 : 3;
@@ -150,3 +151,16 @@ hipError_t launch_student(int dtype, int mode, const void* in, void* out, uint64
 }
 
 }  // namespace qm
+
+/* What a launch stages of the table for nu (include/qm_debug.h). */
+extern "C" int qm_debug_student_staging(double nu, int f32, double* y_staged, unsigned long long* lds_bytes)
+{
+    qm::HostTTable t{};
+    char err[256] = {0};
+    if (qm::build_student_table(nu, &t, err, sizeof err) != 0) return -1;
+    const qm::StudentParams P = qm::make_params(t.hdr, f32 ? t.hdr.f32 : t.hdr.f64, nullptr);
+    qm::free_student_table(&t);
+    *y_staged = P.y_lds;
+    *lds_bytes = P.identity ? 0 : qm::student_lds_bytes(P);
+    return P.nlds;
+}
