@@ -17,9 +17,6 @@
 #include <stdint.h>
 #include <stdlib.h>
 
-#include <algorithm>
-#include <cmath>
-
 #include "qm_device.hpp"
 #include "qm_internal.h"
 #include "qm_stream.hpp"
@@ -78,12 +75,11 @@ static bool cells_valid(const TCells& c, int degree)
     return c.degree == degree && c.stride == degree + 1 && c.nlds >= 1 && c.ncell >= c.nlds;
 }
 
-/* The staged cells reach |z| = 7, which a normal draw passes with probability
-   2.6e-12 (the table's LDS range goes to 10, for twice the rows to stage and
-   to keep); the cells beyond are read from device memory by the far path, to
-   the same bits. */
-constexpr double T_Y_STAGED = 49.0;
-
+/* Every row of the table's LDS range (|z| <= 10) is staged.  Half of it (|z| <=
+   7, all but 2.6e-12 of normal draws) is 0 to 2% faster on normal draws (MI355X,
+   2^26 FP64, nu = 1: 170.7 us against 174.4; nu = 30 169.3 and 169.0), but
+   inputs that do reach 7 < |z| <= 10 then go one element of each lane at a
+   time through the far path (uniform on +-10, nu = 4: 284 against 179). */
 StudentParams make_params(const TTableHeader& h, const TCells& c, const double* d_rows)
 {
     StudentParams P;
@@ -98,9 +94,8 @@ StudentParams make_params(const TTableHeader& h, const TCells& c, const double* 
     P.inv_nu = 1.0 / h.nu;
     P.nu = h.nu;
     P.ncell = c.ncell;
-    /* nu = +inf has no cells (h = 0) */
-    P.nlds = h.identity ? 0 : std::min(c.nlds, (int)std::ceil(T_Y_STAGED / c.h));
-    P.y_lds = P.nlds * c.h;
+    P.nlds = c.nlds;              /* 0 for nu = +inf, which has no cells */
+    P.y_lds = c.y_lds;
     P.identity = h.identity;
     P.row_shift = c.stride == 16 ? 4 : 3;
     P.lds_stride = student_lds_stride(c.stride, P.nlds);
