@@ -108,11 +108,11 @@ typedef struct qm_ctx qm_ctx;
  * hyperbolic or variance-gamma 3 x 2 and 4 x 2; fused generation of uniforms
  * one vector per lane and workgroup, quantiles 64 x 4 (FP64) and 32 x 4 (FP32),
  * Student t 16 x 4, hyperbolic 16 x 4 and 16 x 2); a launch too small to give
- * every compute unit two workgroups takes fewer vectors per lane, and a map
- * of 2^25 elements or so and more one workgroup for every tile or two.
- * The environment
+ * every compute unit two workgroups takes fewer vectors per lane, and a large
+ * map (from 2^25 to 2^28 elements on, by family) one workgroup for every tile
+ * or two.  The environment
  * variables QM_BLOCKS_PER_CU (1..64) and QM_UNROLL (1, 2 or 4), read here,
- * override every family, and QM_SHAPE_STREAM, QM_SHAPE_STREAM32,
+ * override every family, for launches of every size, and QM_SHAPE_STREAM, QM_SHAPE_STREAM32,
  * QM_SHAPE_NQ64, QM_SHAPE_NQ32, QM_SHAPE_GU64, QM_SHAPE_GU32,
  * QM_SHAPE_GEN64, QM_SHAPE_GEN32, QM_SHAPE_GT64, QM_SHAPE_GT32,
  * QM_SHAPE_GH64, QM_SHAPE_GH32, QM_SHAPE_T64, QM_SHAPE_T32, QM_SHAPE_H64,

@@ -69,6 +69,14 @@ int qm_debug_hyperbolic_table(double alpha, double beta, double delta, void* hea
 int qm_debug_vg_table(double lambda, double alpha, double beta, void* header_out, double* coef_out, int coef_cap);
 
 /*
+ * The launch of a kernel of one family, named by its variable ("QM_SHAPE_T64"
+ * and so on, qm_init), over nvec 16-byte vectors on a device of `cus` compute
+ * units, with the environment as it is now: *blocks gets the workgroups.
+ * Returns the vectors per lane, or -1 for an unknown family.
+ */
+int qm_debug_launch(const char* family, int cus, unsigned long long nvec, unsigned long long* blocks);
+
+/*
  * w[i] = a[i]^rho for 0 < a[i] <= 1, as the kernels form it for the origin
  * series of a variance-gamma table, in the same steps on the host.  Host
  * arrays of n doubles.  Returns 0.

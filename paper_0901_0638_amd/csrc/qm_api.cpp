@@ -17,6 +17,7 @@
 #include "qm_batch.h"
 #include "qm_context.h"
 #include "qm_serve.h"
+#include "qm_stream.hpp"
 
 namespace {
 
@@ -52,6 +53,90 @@ bool mode_known(uint32_t m) { return m == QM_PLAIN || m == QM_F32_REFINE || m ==
 bool hyp_params_ok(double alpha, double beta, double delta)
 {
     return std::isfinite(alpha) && std::isfinite(beta) && std::isfinite(delta) && delta > 0 && alpha > std::fabs(beta);
+}
+
+/* Launch shapes for a device of `cus` compute units, and the family's whose
+   variable is named (NULL: none). */
+static const qm::KernelShape* default_shapes(int cus, qm::LaunchShape* shape, const char* family = nullptr)
+{
+    /* launch shapes per kernel family (workgroups of 256 per CU x vectors
+       per lane), the best of measured sweeps over 1..1024 x 1..4 on MI355X;
+       QM_BLOCKS_PER_CU / QM_UNROLL override every family (tuning) */
+    const uint64_t ncu = (uint64_t)cus;
+    shape->cus = cus;
+    /* (big, big_unroll): the two tiles to a workgroup of launch_blocks from
+       `big` tiles of big_unroll vectors per unit on */
+    struct { qm::KernelShape* ks; const char* env; long bpc, unroll, big, big_unroll; } fam[] = {
+        /* light FP64 maps: with no table to stage, many workgroups (2^26
+           exp -> normal: 166 us at 64 x 4, 175 at 2 x 4; 2^22 13.0, 14.0); 2^27
+           337 us with two tiles each, 350 at 64 x 4 */
+        {&shape->stream, "QM_SHAPE_STREAM", 64, 4, 128, 4},
+        /* FP32 maps: exp -> normal 2^24 25 us at 32 x 4, 28.6 at 32 x 2; 2^26
+           90 and 100; two tiles each 2^27 180 us, 177 at 32 x 4, 2^28 359 and
+           368 */
+        {&shape->stream32, "QM_SHAPE_STREAM32", 32, 4, 256, 4},
+        /* quantiles: FP32+refine 2^26 93 us at 32 x 4, 98 at 16 x 4; two tiles
+           each 2^27 188, 183 at 32 x 4, 2^28 368 and 376; FP64 2^25 84 at
+           64 x 4, 2^26 173, 187 at 16 x 4; two tiles of 2 vectors each 2^26 170,
+           2^27 347 (of 4: 351), 362 at 64 x 4 */
+        {&shape->hybrid[0], "QM_SHAPE_NQ32", 32, 4, 256, 4},
+        {&shape->hybrid[1], "QM_SHAPE_NQ64", 64, 4, 256, 2},
+        /* fused generation, write only.  Uniforms: the stores alone, and those
+           are fastest as one 4 KB row to a workgroup, all of them written in
+           order (FP64 2^26 76 us, 83 with four rows, 89 at 64 x 4, 2^28 329, 365
+           and 392; FP32 2^26 40, 43 and 42, 2^28 156, 179 and 190: 6.9 TB/s;
+           2^24 12.6, 12.0 and 12.0).  Quantiles: 2^26 FP32 89 us at 32 x 4, 92
+           at 32 x 2, FP64 152 at 64 x 4, 158 at 8 x 4 */
+        {&shape->uniform[0], "QM_SHAPE_GU32", 16384, 1, 0, 1},
+        {&shape->uniform[1], "QM_SHAPE_GU64", 16384, 1, 0, 1},
+        {&shape->generate[0], "QM_SHAPE_GEN32", 32, 4, 0, 4},
+        {&shape->generate[1], "QM_SHAPE_GEN64", 64, 4, 0, 4},
+        /* kernels that stage a table per workgroup: the grid stays within a
+           few workgroups per unit, so that each stages once for many tiles.
+           Fused Student t, 2^24 FP64: 55 us at 16 x 4, 58 at 32 x 4 (one tile
+           for each staging), 2^28 780, 771 at 64 x 4 and 781 at 128 x 4; FP32
+           2^26 133, 138 at 32 x 4.  Fused hyperbolic, 2^24 FP64: 61 us at
+           8..16 x 4, 63 at 32 x 4, 2^28 805, 820 at 64 x 4; FP32 47 at
+           8..16 x 2, 48 at 32 x 2 */
+        {&shape->generate_t[0], "QM_SHAPE_GT32", 16, 4, 0, 4},
+        {&shape->generate_t[1], "QM_SHAPE_GT64", 16, 4, 0, 4},
+        {&shape->generate_h[0], "QM_SHAPE_GH32", 16, 2, 0, 2},
+        {&shape->generate_h[1], "QM_SHAPE_GH64", 16, 4, 0, 4},
+        /* Student t: 2^24 FP64 44.4 us at 2 x 4, 45.8 at 2 x 2; FP32 2^26 91 at
+           4 x 2, 2^22 8.5 against 10.2 at 2 x 4; two tiles each 2^27 FP64 337,
+           354 at 2 x 4, FP32 166, 183 at 4 x 2 */
+        {&shape->student[0], "QM_SHAPE_T32", 4, 2, 128, 2},
+        {&shape->student[1], "QM_SHAPE_T64", 2, 4, 128, 2},
+        /* exp -> hyperbolic and variance-gamma: 2^22 FP64 14 us at 3 x 2, 17 at
+           16 x 4, 2^24 46 and 54, 2^26 184 and 182; FP32 2^24 25.6 at 4 x 2,
+           26.7 at 16 x 2; two tiles each 2^27 FP64 345, 374 at 3 x 2, FP32 169,
+           185 at 4 x 2 */
+        {&shape->hyperbolic[0], "QM_SHAPE_H32", 4, 2, 128, 2},
+        {&shape->hyperbolic[1], "QM_SHAPE_H64", 3, 2, 128, 2},
+    };
+    long env_bpc = 0, env_unroll = 0;
+    if (const char* ev = getenv("QM_BLOCKS_PER_CU")) env_bpc = strtol(ev, nullptr, 10);
+    if (const char* ev = getenv("QM_UNROLL")) env_unroll = strtol(ev, nullptr, 10);
+    const qm::KernelShape* found = nullptr;
+    for (auto& f : fam) {
+        if (family && !strcmp(family, f.env)) found = f.ks;
+        long bpc = f.bpc, unroll = f.unroll, eb = env_bpc, eu = env_unroll;
+        if (const char* ev = getenv(f.env)) {       /* "bpc,unroll" for this family alone */
+            char* end = nullptr;
+            eb = strtol(ev, &end, 10);
+            eu = (end && *end == ',') ? strtol(end + 1, nullptr, 10) : 0;
+        }
+        f.ks->big_vecs = ncu * (uint64_t)f.big * 256 * (uint64_t)f.big_unroll;
+        f.ks->huge_vecs = f.big ? ncu << 19 : 0;
+        f.ks->big_blocks = 4096 * ncu;
+        f.ks->big_unroll = (int)f.big_unroll;
+        if (eb >= 1 && eb <= 64) { bpc = eb; f.ks->big_vecs = f.ks->huge_vecs = 0; }
+        f.ks->fixed_unroll = eu == 1 || eu == 2 || eu == 4;
+        if (f.ks->fixed_unroll) unroll = eu;
+        f.ks->max_blocks = ncu * (uint64_t)bpc;
+        f.ks->unroll = (int)unroll;
+    }
+    return found;
 }
 
 }  // namespace
@@ -276,80 +361,7 @@ qm_status qm_init(int hip_device, uint64_t hbm_budget_bytes, qm_ctx** out)
     c->device = hip_device;
     c->budget = hbm_budget_bytes;
     c->cus = cus > 0 ? cus : 256;
-    c->shape.cus = c->cus;
-    /* launch shapes per kernel family (workgroups of 256 per CU x vectors
-       per lane), the best of measured sweeps over 1..64 x 1..4 on MI355X;
-       QM_BLOCKS_PER_CU / QM_UNROLL override every family (tuning) */
-    const uint64_t ncu = (uint64_t)(cus > 0 ? cus : 256);
-    /* (big, big_unroll): the two tiles to a workgroup of launch_blocks from
-       `big` tiles of big_unroll vectors per unit on */
-    struct { qm::KernelShape* ks; const char* env; long bpc, unroll, big, big_unroll; } fam[] = {
-        /* light FP64 maps: with no table to stage, many workgroups (2^26
-           exp -> normal: 166 us at 64 x 4, 175 at 2 x 4; 2^22 13.0, 14.0); 2^27
-           337 us with two tiles each, 350 at 64 x 4 */
-        {&c->shape.stream, "QM_SHAPE_STREAM", 64, 4, 128, 4},
-        /* FP32 maps: exp -> normal 2^24 25 us at 32 x 4, 28.6 at 32 x 2; 2^26
-           90 and 100; two tiles each 2^27 180 us, 177 at 32 x 4, 2^28 359 and
-           368 */
-        {&c->shape.stream32, "QM_SHAPE_STREAM32", 32, 4, 256, 4},
-        /* quantiles: FP32+refine 2^26 93 us at 32 x 4, 98 at 16 x 4; two tiles
-           each 2^27 188, 183 at 32 x 4, 2^28 368 and 376; FP64 2^25 84 at
-           64 x 4, 2^26 173, 187 at 16 x 4; two tiles of 2 vectors each 2^26 170,
-           2^27 347 (of 4: 351), 362 at 64 x 4 */
-        {&c->shape.hybrid[0], "QM_SHAPE_NQ32", 32, 4, 256, 4},
-        {&c->shape.hybrid[1], "QM_SHAPE_NQ64", 64, 4, 256, 2},
-        /* fused generation, write only.  Uniforms: the stores alone, and those
-           are fastest as one 4 KB row to a workgroup, all of them written in
-           order (FP64 2^26 76 us, 83 with four rows, 89 at 64 x 4, 2^28 329, 365
-           and 392; FP32 2^26 40, 43 and 42, 2^28 156, 179 and 190: 6.9 TB/s;
-           2^24 12.6, 12.0 and 12.0).  Quantiles: 2^26 FP32 89 us at 32 x 4, 92
-           at 32 x 2, FP64 152 at 64 x 4, 158 at 8 x 4 */
-        {&c->shape.uniform[0], "QM_SHAPE_GU32", 16384, 1, 0, 1},
-        {&c->shape.uniform[1], "QM_SHAPE_GU64", 16384, 1, 0, 1},
-        {&c->shape.generate[0], "QM_SHAPE_GEN32", 32, 4, 0, 4},
-        {&c->shape.generate[1], "QM_SHAPE_GEN64", 64, 4, 0, 4},
-        /* kernels that stage a table per workgroup: the grid stays within a
-           few workgroups per unit, so that each stages once for many tiles.
-           Fused Student t, 2^24 FP64: 55 us at 16 x 4, 58 at 32 x 4 (one tile
-           for each staging), 2^28 780, 771 at 64 x 4 and 781 at 128 x 4; FP32
-           2^26 133, 138 at 32 x 4.  Fused hyperbolic, 2^24 FP64: 61 us at
-           8..16 x 4, 63 at 32 x 4, 2^28 805, 820 at 64 x 4; FP32 47 at
-           8..16 x 2, 48 at 32 x 2 */
-        {&c->shape.generate_t[0], "QM_SHAPE_GT32", 16, 4, 0, 4},
-        {&c->shape.generate_t[1], "QM_SHAPE_GT64", 16, 4, 0, 4},
-        {&c->shape.generate_h[0], "QM_SHAPE_GH32", 16, 2, 0, 2},
-        {&c->shape.generate_h[1], "QM_SHAPE_GH64", 16, 4, 0, 4},
-        /* Student t: 2^24 FP64 44.4 us at 2 x 4, 45.8 at 2 x 2; FP32 2^26 91 at
-           4 x 2, 2^22 8.5 against 10.2 at 2 x 4; two tiles each 2^27 FP64 337,
-           354 at 2 x 4, FP32 166, 183 at 4 x 2 */
-        {&c->shape.student[0], "QM_SHAPE_T32", 4, 2, 128, 2},
-        {&c->shape.student[1], "QM_SHAPE_T64", 2, 4, 128, 2},
-        /* exp -> hyperbolic and variance-gamma: 2^22 FP64 14 us at 3 x 2, 17 at
-           16 x 4, 2^24 46 and 54, 2^26 184 and 182; FP32 2^24 25.6 at 4 x 2,
-           26.7 at 16 x 2; two tiles each 2^27 FP64 345, 374 at 3 x 2, FP32 169,
-           185 at 4 x 2 */
-        {&c->shape.hyperbolic[0], "QM_SHAPE_H32", 4, 2, 128, 2},
-        {&c->shape.hyperbolic[1], "QM_SHAPE_H64", 3, 2, 128, 2},
-    };
-    long env_bpc = 0, env_unroll = 0;
-    if (const char* ev = getenv("QM_BLOCKS_PER_CU")) env_bpc = strtol(ev, nullptr, 10);
-    if (const char* ev = getenv("QM_UNROLL")) env_unroll = strtol(ev, nullptr, 10);
-    for (auto& f : fam) {
-        long bpc = f.bpc, unroll = f.unroll, eb = env_bpc, eu = env_unroll;
-        if (const char* ev = getenv(f.env)) {       /* "bpc,unroll" for this family alone */
-            char* end = nullptr;
-            eb = strtol(ev, &end, 10);
-            eu = (end && *end == ',') ? strtol(end + 1, nullptr, 10) : 0;
-        }
-        f.ks->big_vecs = ncu * (uint64_t)f.big * 256 * (uint64_t)f.big_unroll;
-        f.ks->huge_vecs = f.big ? ncu << 19 : 0;
-        f.ks->big_blocks = 4096 * ncu;
-        f.ks->big_unroll = (int)f.big_unroll;
-        if (eb >= 1 && eb <= 64) { bpc = eb; f.ks->big_vecs = f.ks->huge_vecs = 0; }
-        if (eu == 1 || eu == 2 || eu == 4) unroll = eu;
-        f.ks->max_blocks = ncu * (uint64_t)bpc;
-        f.ks->unroll = (int)unroll;
-    }
+    default_shapes(c->cus, &c->shape);
     const char* ec = getenv("QM_COMPACT");
     c->shape.compact = ec ? (int)strtol(ec, nullptr, 10) != 0 : 1;
     /* set-up of the allocation-free batch entry point (this device is
@@ -623,6 +635,18 @@ const char* qm_status_string(qm_status s)
 }
 
 const char* qm_last_error(void) { return g_last_error.c_str(); }
+
+/* The launch of nvec vectors (include/qm_debug.h). */
+int qm_debug_launch(const char* family, int cus, unsigned long long nvec, unsigned long long* blocks)
+{
+    qm::LaunchShape shape{};
+    if (!family || !blocks || cus < 1) return -1;
+    const qm::KernelShape* ks = default_shapes(cus, &shape, family);
+    if (!ks) return -1;
+    const int u = qm::launch_unroll(nvec, *ks, cus);
+    *blocks = qm::launch_blocks(nvec, u, *ks);
+    return u;
+}
 
 }  /* extern "C" */
 

@@ -16,10 +16,12 @@ namespace qm {
    256, each lane keeping `unroll` 16-byte vectors in flight (1, 2 or 4).
    Launches of big_vecs vectors and more keep big_unroll in flight, with two
    tiles to a workgroup, those of huge_vecs and more four, with one tile (0:
-   never); both have at most big_blocks workgroups. */
+   never); both have at most big_blocks workgroups.  fixed_unroll: `unroll`
+   holds for launches of every size. */
 struct KernelShape {
     uint64_t max_blocks;
     int unroll, big_unroll;
+    bool fixed_unroll;
     uint64_t big_vecs, huge_vecs, big_blocks;
 };
 

@@ -178,6 +178,8 @@ inline bool launch_huge(uint64_t nvec, const KernelShape& ks) { return ks.huge_v
  */
 inline int launch_unroll(uint64_t nvec, const KernelShape& ks, int cus)
 {
+
+    if (ks.fixed_unroll) return ks.unroll;
     if (launch_huge(nvec, ks)) return 4;
     if (launch_big(nvec, ks)) return ks.big_unroll;
     int u = ks.unroll;

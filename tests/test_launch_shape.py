@@ -1,0 +1,43 @@
+"""CPU: the rules that give a launch its workgroups and vectors per lane."""
+import ctypes
+
+import pytest
+
+import paper_0901_0638_amd as qm
+
+FAMILIES = ["QM_SHAPE_" + f for f in ("STREAM", "STREAM32", "NQ32", "NQ64", "GU32", "GU64", "GEN32", "GEN64", "GT32",
+                                      "GT64", "GH32", "GH64", "T32", "T64", "H32", "H64")]
+CUS = 256
+
+
+@pytest.fixture(autouse=True)
+def no_overrides(monkeypatch):
+    for name in FAMILIES + ["QM_UNROLL", "QM_BLOCKS_PER_CU"]:
+        monkeypatch.delenv(name, raising=False)
+
+
+def launch(family, nvec):
+    blocks = ctypes.c_ulonglong()
+    u = qm.load().qm_debug_launch(family.encode(), CUS, nvec, ctypes.byref(blocks))
+    assert u in (1, 2, 4) and 1 <= blocks.value < 1 << 23
+    return u, blocks.value
+
+
+def test_unknown_family():
+    assert qm.load().qm_debug_launch(b"QM_SHAPE_X", CUS, 1, ctypes.byref(ctypes.c_ulonglong())) == -1
+
+
+@pytest.mark.parametrize("family", FAMILIES)
+def test_overrides_hold_for_every_size(family, monkeypatch):
+    """QM_UNROLL, or "0,u" for one family: that many vectors per lane, from the
+    smallest launch to the largest; a number of workgroups caps them all."""
+    sizes = [0, 1, 1 << 16, 1 << 22, 1 << 25, 1 << 27, 1 << 29]
+    for u in (1, 2, 4):
+        monkeypatch.setenv("QM_UNROLL", str(u))
+        assert [launch(family, n)[0] for n in sizes] == [u] * len(sizes)
+        monkeypatch.delenv("QM_UNROLL")
+        monkeypatch.setenv(family, "0,%d" % u)
+        assert [launch(family, n)[0] for n in sizes] == [u] * len(sizes)
+        monkeypatch.setenv(family, "3,%d" % u)
+        assert max(launch(family, n)[1] for n in sizes) == 3 * CUS
+        monkeypatch.delenv(family)
