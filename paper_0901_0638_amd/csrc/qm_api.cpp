@@ -65,32 +65,33 @@ static const qm::KernelShape* default_shapes(int cus, qm::LaunchShape* shape, co
     const uint64_t ncu = (uint64_t)cus;
     shape->cus = cus;
     /* (big, big_unroll): the two tiles to a workgroup of launch_blocks from
-       `big` tiles of big_unroll vectors per unit on */
-    struct { qm::KernelShape* ks; const char* env; long bpc, unroll, big, big_unroll; } fam[] = {
+       `big` tiles of big_unroll vectors per unit on; huge: its one tile from
+       2 GB on */
+    struct { qm::KernelShape* ks; const char* env; long bpc, unroll, big, big_unroll; bool huge; } fam[] = {
         /* light FP64 maps: with no table to stage, many workgroups (2^26
            exp -> normal: 166 us at 64 x 4, 175 at 2 x 4; 2^22 13.0, 14.0); 2^27
            337 us with two tiles each, 350 at 64 x 4 */
-        {&shape->stream, "QM_SHAPE_STREAM", 64, 4, 128, 4},
+        {&shape->stream, "QM_SHAPE_STREAM", 64, 4, 128, 4, true},
         /* FP32 maps: exp -> normal 2^24 25 us at 32 x 4, 28.6 at 32 x 2; 2^26
            90 and 100; two tiles each 2^27 180 us, 177 at 32 x 4, 2^28 359 and
            368 */
-        {&shape->stream32, "QM_SHAPE_STREAM32", 32, 4, 256, 4},
+        {&shape->stream32, "QM_SHAPE_STREAM32", 32, 4, 256, 4, false},
         /* quantiles: FP32+refine 2^26 93 us at 32 x 4, 98 at 16 x 4; two tiles
            each 2^27 188, 183 at 32 x 4, 2^28 368 and 376; FP64 2^25 84 at
            64 x 4, 2^26 173, 187 at 16 x 4; two tiles of 2 vectors each 2^26 170,
            2^27 347 (of 4: 351), 362 at 64 x 4 */
-        {&shape->hybrid[0], "QM_SHAPE_NQ32", 32, 4, 256, 4},
-        {&shape->hybrid[1], "QM_SHAPE_NQ64", 64, 4, 256, 2},
+        {&shape->hybrid[0], "QM_SHAPE_NQ32", 32, 4, 256, 4, false},
+        {&shape->hybrid[1], "QM_SHAPE_NQ64", 64, 4, 256, 2, true},
         /* fused generation, write only.  Uniforms: the stores alone, and those
            are fastest as one 4 KB row to a workgroup, all of them written in
            order (FP64 2^26 76 us, 83 with four rows, 89 at 64 x 4, 2^28 329, 365
            and 392; FP32 2^26 40, 43 and 42, 2^28 156, 179 and 190: 6.9 TB/s;
            2^24 12.6, 12.0 and 12.0).  Quantiles: 2^26 FP32 89 us at 32 x 4, 92
            at 32 x 2, FP64 152 at 64 x 4, 158 at 8 x 4 */
-        {&shape->uniform[0], "QM_SHAPE_GU32", 16384, 1, 0, 1},
-        {&shape->uniform[1], "QM_SHAPE_GU64", 16384, 1, 0, 1},
-        {&shape->generate[0], "QM_SHAPE_GEN32", 32, 4, 0, 4},
-        {&shape->generate[1], "QM_SHAPE_GEN64", 64, 4, 0, 4},
+        {&shape->uniform[0], "QM_SHAPE_GU32", 16384, 1, 0, 1, false},
+        {&shape->uniform[1], "QM_SHAPE_GU64", 16384, 1, 0, 1, false},
+        {&shape->generate[0], "QM_SHAPE_GEN32", 32, 4, 0, 4, false},
+        {&shape->generate[1], "QM_SHAPE_GEN64", 64, 4, 0, 4, false},
         /* kernels that stage a table per workgroup: the grid stays within a
            few workgroups per unit, so that each stages once for many tiles.
            Fused Student t, 2^24 FP64: 55 us at 16 x 4, 58 at 32 x 4 (one tile
@@ -98,21 +99,21 @@ static const qm::KernelShape* default_shapes(int cus, qm::LaunchShape* shape, co
            2^26 133, 138 at 32 x 4.  Fused hyperbolic, 2^24 FP64: 61 us at
            8..16 x 4, 63 at 32 x 4, 2^28 805, 820 at 64 x 4; FP32 47 at
            8..16 x 2, 48 at 32 x 2 */
-        {&shape->generate_t[0], "QM_SHAPE_GT32", 16, 4, 0, 4},
-        {&shape->generate_t[1], "QM_SHAPE_GT64", 16, 4, 0, 4},
-        {&shape->generate_h[0], "QM_SHAPE_GH32", 16, 2, 0, 2},
-        {&shape->generate_h[1], "QM_SHAPE_GH64", 16, 4, 0, 4},
+        {&shape->generate_t[0], "QM_SHAPE_GT32", 16, 4, 0, 4, false},
+        {&shape->generate_t[1], "QM_SHAPE_GT64", 16, 4, 0, 4, false},
+        {&shape->generate_h[0], "QM_SHAPE_GH32", 16, 2, 0, 2, false},
+        {&shape->generate_h[1], "QM_SHAPE_GH64", 16, 4, 0, 4, false},
         /* Student t: 2^24 FP64 44.4 us at 2 x 4, 45.8 at 2 x 2; FP32 2^26 91 at
            4 x 2, 2^22 8.5 against 10.2 at 2 x 4; two tiles each 2^27 FP64 337,
            354 at 2 x 4, FP32 166, 183 at 4 x 2 */
-        {&shape->student[0], "QM_SHAPE_T32", 4, 2, 128, 2},
-        {&shape->student[1], "QM_SHAPE_T64", 2, 4, 128, 2},
+        {&shape->student[0], "QM_SHAPE_T32", 4, 2, 128, 2, true},
+        {&shape->student[1], "QM_SHAPE_T64", 2, 4, 128, 2, true},
         /* exp -> hyperbolic and variance-gamma: 2^22 FP64 14 us at 3 x 2, 17 at
            16 x 4, 2^24 46 and 54, 2^26 184 and 182; FP32 2^24 25.6 at 4 x 2,
            26.7 at 16 x 2; two tiles each 2^27 FP64 345, 374 at 3 x 2, FP32 169,
            185 at 4 x 2 */
-        {&shape->hyperbolic[0], "QM_SHAPE_H32", 4, 2, 128, 2},
-        {&shape->hyperbolic[1], "QM_SHAPE_H64", 3, 2, 128, 2},
+        {&shape->hyperbolic[0], "QM_SHAPE_H32", 4, 2, 128, 2, true},
+        {&shape->hyperbolic[1], "QM_SHAPE_H64", 3, 2, 128, 2, false},
     };
     long env_bpc = 0, env_unroll = 0;
     if (const char* ev = getenv("QM_BLOCKS_PER_CU")) env_bpc = strtol(ev, nullptr, 10);
@@ -127,7 +128,7 @@ static const qm::KernelShape* default_shapes(int cus, qm::LaunchShape* shape, co
             eu = (end && *end == ',') ? strtol(end + 1, nullptr, 10) : 0;
         }
         f.ks->big_vecs = ncu * (uint64_t)f.big * 256 * (uint64_t)f.big_unroll;
-        f.ks->huge_vecs = f.big ? ncu << 19 : 0;
+        f.ks->huge_vecs = f.huge ? ncu << 19 : 0;
         f.ks->big_blocks = 4096 * ncu;
         f.ks->big_unroll = (int)f.big_unroll;
         if (eb >= 1 && eb <= 64) { bpc = eb; f.ks->big_vecs = f.ks->huge_vecs = 0; }

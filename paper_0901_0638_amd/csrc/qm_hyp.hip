@@ -108,7 +108,7 @@ static hipError_t launch_h(const void* in, void* out, uint64_t n, const HypParam
     const Span<T> a = make_span(static_cast<const T*>(in), static_cast<T*>(out), n);
     /* targets with the origin series: a tile's passes over it are a latency
        that two tiles do not hide and more do (variance-gamma 4.25, 2^26 FP64:
-       196 us at 64 workgroups per unit, 219 with two tiles each; 2^28 763 and
+       196 us at 64 workgroups per unit, 219 with two tiles each; 2^28 765 and
        853) */
     if (P.jlo) shape.big_blocks = 64 * (uint64_t)cus;
     const int u = launch_unroll(a.nvec, shape, cus);

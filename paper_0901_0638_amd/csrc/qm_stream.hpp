@@ -178,7 +178,6 @@ inline bool launch_huge(uint64_t nvec, const KernelShape& ks) { return ks.huge_v
  */
 inline int launch_unroll(uint64_t nvec, const KernelShape& ks, int cus)
 {
-
     if (ks.fixed_unroll) return ks.unroll;
     if (launch_huge(nvec, ks)) return 4;
     if (launch_big(nvec, ks)) return ks.big_unroll;
@@ -201,12 +200,16 @@ inline int launch_unroll(uint64_t nvec, const KernelShape& ks, int cus)
  * 732 for 2^28); FP64 Student t 2^26 174.5 -> 167.5, 2^27 354 -> 340; FP64
  * hyperbolic 2^27 363 -> 346; FP32 Student t 2^28 362 -> 340.  One tile each
  * is slower there (Student t 2^26 187, quantiles 182 against 172), and two
- * neighbouring tiles are too at some sizes (quantiles 2^28 741).  From two
- * tiles for each of 64 workgroups per unit on (FP32 maps, which are closer to
- * their arithmetic: 128), 256 MB or so.  From 2 GB on one tile of four vectors
- * each does as well or better: FP64 2^28, Student t 687 (nu = 4), 708 (nu = 1)
- * and 743 (nu = 30) with two tiles, 696..702 with one, exp -> normal 690 and
- * 675, hyperbolic 705 and 710, quantiles 705 and 701.
+ * neighbouring tiles are too at some sizes (quantiles 2^28 741).  Each family
+ * changes over where the two tiles have overtaken its fixed grid, at 256 MB to
+ * 1 GB of one array.  From 2 GB on one tile of four vectors each does better
+ * for some (us, two tiles -> one; FP64 2^28): quantiles 771 -> 755 on the
+ * mixture and 751 -> 683 on uniforms, exp -> normal 688 -> 677, Student t nu =
+ * 30 742 -> 705 and nu = 4 706 -> 708; FP32 2^29: Student t 718 -> 690 (nu = 1
+ * 725 -> 726), hyperbolic 729 -> 715, variance-gamma 740 -> 727.  It costs
+ * where more is staged for the one tile (FP64 hyperbolic 703 -> 739, Student t
+ * with rows of 16, nu = 1, 706 -> 771) and gives nothing to the FP32 quantiles
+ * (783 -> 794, 724 -> 724) and exp -> normal (821 -> 822): those keep two.
  */
 inline unsigned launch_blocks(uint64_t nvec, int unroll, const KernelShape& ks)
 {

@@ -106,7 +106,8 @@ template <typename T, int DEG>
 static hipError_t launch_t(const void* in, void* out, uint64_t n, const double* d_block, const TTableHeader& h,
                            hipStream_t s, const LaunchShape& shape_all)
 {
-    const KernelShape shape = shape_all.student[sizeof(T) == 8];
+    KernelShape shape = shape_all.student[sizeof(T) == 8];
+    if (DEG == T_DEGREE_HIGH) shape.huge_vecs = 0;   /* 25 KB and more to stage: two tiles a workgroup */
     if (h.identity) {
         uint64_t blocks = (n + 255) / 256;
         if (blocks > shape.max_blocks) blocks = shape.max_blocks;

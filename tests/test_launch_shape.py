@@ -41,3 +41,16 @@ def test_overrides_hold_for_every_size(family, monkeypatch):
         monkeypatch.setenv(family, "3,%d" % u)
         assert max(launch(family, n)[1] for n in sizes) == 3 * CUS
         monkeypatch.delenv(family)
+
+
+@pytest.mark.parametrize("family", FAMILIES)
+def test_large_launches(family):
+    """From 2 GB of one array on (2^27 vectors): one tile of four vectors to a
+    workgroup for the families that gain by it; two tiles of their own else."""
+    u, blocks = launch(family, 1 << 27)
+    if family[9:] in ("STREAM", "NQ64", "T32", "T64", "H32"):
+        assert (u, blocks) == (4, 1 << 17)
+    elif family[9:] in ("STREAM32", "NQ32"):
+        assert (u, blocks) == (4, 1 << 16)
+    elif family == "QM_SHAPE_H64":
+        assert (u, blocks) == (2, 1 << 17)
