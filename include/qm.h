@@ -103,23 +103,24 @@ typedef struct qm_ctx qm_ctx;
  * The context owns the per-nu Student t tables and the serving state.
  * Each kernel family has its own launch shape (most workgroups of 256 per
  * compute unit x 16-byte vectors in flight per lane, from measured sweeps:
- * FP64 maps 64 x 4, FP32 maps 32 x 4, FP64 quantile 64 x 4, FP32+refine
- * quantile 32 x 4, Student t 2 x 4 (FP64) and 4 x 2 (FP32), exp ->
- * hyperbolic or variance-gamma 3 x 2 and 4 x 2; fused generation of uniforms
- * one vector per lane and workgroup, quantiles 64 x 4 (FP64) and 32 x 4 (FP32),
- * Student t 16 x 4, hyperbolic 16 x 4 and 16 x 2); a launch too small to give
- * every compute unit two workgroups takes fewer vectors per lane, and a large
- * map (from 2^25 to 2^28 elements on, by family) one workgroup for every tile
- * or two.  The environment
- * variables QM_BLOCKS_PER_CU (1..64) and QM_UNROLL (1, 2 or 4), read here,
- * override every family, for launches of every size, and QM_SHAPE_STREAM, QM_SHAPE_STREAM32,
- * QM_SHAPE_NQ64, QM_SHAPE_NQ32, QM_SHAPE_GU64, QM_SHAPE_GU32,
- * QM_SHAPE_GEN64, QM_SHAPE_GEN32, QM_SHAPE_GT64, QM_SHAPE_GT32,
- * QM_SHAPE_GH64, QM_SHAPE_GH32, QM_SHAPE_T64, QM_SHAPE_T32, QM_SHAPE_H64,
- * QM_SHAPE_H32 ("blocks,unroll")
- * one family each.  QM_COMPACT=0 turns off the quantiles' gathering of
- * non-central lanes across the wave (the results are bitwise the same
- * either way).
+ * FP64 maps 64 x 4, FP32 maps 32 x 4 (both 64 x 2 for the paper's exp ->
+ * normal in FP64 and the paper and plain quantiles in FP32), FP64 quantile
+ * 64 x 4, FP32+refine quantile 32 x 4, Student t 2 x 4 (FP64) and 4 x 2
+ * (FP32), exp -> hyperbolic or variance-gamma 3 x 2 and 4 x 2; fused
+ * generation of uniforms one vector per lane and workgroup, quantiles 64 x 4
+ * (FP64) and 32 x 4 (FP32), Student t 16 x 4, hyperbolic 16 x 4 and 16 x 2);
+ * a launch too small to give every compute unit two workgroups takes fewer
+ * vectors per lane, and a large map (from 2^25 to 2^28 elements on, by
+ * family) one workgroup for every tile or two.  The environment variables
+ * QM_BLOCKS_PER_CU (1..64) and QM_UNROLL (1, 2 or 4), read here, override
+ * every family, for launches of every size, and QM_SHAPE_STREAM,
+ * QM_SHAPE_STREAM32, QM_SHAPE_LIGHT64, QM_SHAPE_LIGHT32, QM_SHAPE_NQ64,
+ * QM_SHAPE_NQ32, QM_SHAPE_GU64, QM_SHAPE_GU32, QM_SHAPE_GEN64,
+ * QM_SHAPE_GEN32, QM_SHAPE_GT64, QM_SHAPE_GT32, QM_SHAPE_GH64,
+ * QM_SHAPE_GH32, QM_SHAPE_T64, QM_SHAPE_T32, QM_SHAPE_H64, QM_SHAPE_H32
+ * ("blocks,unroll") one family each.  QM_COMPACT=0 turns off the quantiles'
+ * gathering of non-central lanes across the wave (the results are bitwise
+ * the same either way).
  * Errors: QM_E_INVAL (out == NULL or no such device), QM_E_HIP, QM_E_NOMEM.
  */
 qm_status qm_init(int hip_device, uint64_t hbm_budget_bytes, qm_ctx** out);

@@ -76,6 +76,15 @@ static const qm::KernelShape* default_shapes(int cus, qm::LaunchShape* shape, co
            90 and 100; two tiles each 2^27 180 us, 177 at 32 x 4, 2^28 359 and
            368 */
         {&shape->stream32, "QM_SHAPE_STREAM32", 32, 4, 256, 4, false},
+        /* the same without a vote: the paper's FP32 quantile and FP64 exp ->
+           normal, and the FP32 plain quantile.  With four vectors in flight
+           their time depends on the card and the buffers: exp -> normal FP64 at 64
+           x 4 2^22 13.0..15.2 us, 2^23 23.1..28.0, 2^24 43.2..52.3, at 64 x 2 13.0..13.3,
+           23.0..23.3, 43.3..44.0; paper quantile FP32 at 32 x 4 2^24 24.3..26.4,
+           2^26 88.3..88.9, at 64 x 2 23.2..23.4, 85.9..86.3; plain 2^21 12.7..12.9,
+           11.6..12.1 */
+        {&shape->light[0], "QM_SHAPE_LIGHT32", 64, 2, 256, 4, false},
+        {&shape->light[1], "QM_SHAPE_LIGHT64", 64, 2, 128, 4, true},
         /* quantiles: FP32+refine 2^26 93 us at 32 x 4, 98 at 16 x 4; two tiles
            each 2^27 188, 183 at 32 x 4, 2^28 368 and 376; FP64 2^25 84 at
            64 x 4, 2^26 173, 187 at 16 x 4; two tiles of 2 vectors each 2^26 170,

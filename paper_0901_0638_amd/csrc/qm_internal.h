@@ -30,8 +30,9 @@ struct KernelShape {
    stage a table run best from few workgroups, the others from many; arrays
    beyond the last-level cache from one for every tile or two. */
 struct LaunchShape {
-    KernelShape stream;      /* k_map, FP64: exp -> normal, paper mode */
-    KernelShape stream32;    /* k_map, FP32: exp -> normal, paper and plain quantiles */
+    KernelShape stream;      /* k_map, FP64: exp -> normal, the paper's quantiles */
+    KernelShape stream32;    /* k_map, FP32: exp -> normal */
+    KernelShape light[2];    /* k_map, [0] FP32: paper and plain quantiles, [1] FP64: the paper's exp -> normal */
     KernelShape hybrid[2];   /* [0] FP32+refine, [1] FP64 quantile: k_hybrid */
     KernelShape uniform[2];  /* [0] FP32, [1] FP64 outputs: k_generate of the uniforms */
     KernelShape generate[2]; /* ... of quantiles */

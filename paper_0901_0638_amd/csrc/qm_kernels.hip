@@ -47,7 +47,10 @@ static hipError_t launch_op(const void* in, void* out, uint64_t n, hipStream_t s
 {
     typedef typename HybridOf<Op>::type H;
     const bool gather = shape.compact && !std::is_void<H>::value;
-    const KernelShape ks = gather ? shape.hybrid[sizeof(T) == 8] : (sizeof(T) == 8 ? shape.stream : shape.stream32);
+    constexpr bool light = std::is_same<Op, OpE64Paper>::value || std::is_same<Op, OpNQ32Paper>::value ||
+                           std::is_same<Op, OpNQ32Plain>::value;
+    const bool f64 = sizeof(T) == 8;
+    const KernelShape ks = gather ? shape.hybrid[f64] : light ? shape.light[f64] : f64 ? shape.stream : shape.stream32;
     const Span<T> a = make_span(static_cast<const T*>(in), static_cast<T*>(out), n);
     const int u = launch_unroll(a.nvec, ks, shape.cus);
     const dim3 grid(launch_blocks(a.nvec, u, ks)), block(256);

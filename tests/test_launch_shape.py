@@ -5,8 +5,8 @@ import pytest
 
 import paper_0901_0638_amd as qm
 
-FAMILIES = ["QM_SHAPE_" + f for f in ("STREAM", "STREAM32", "NQ32", "NQ64", "GU32", "GU64", "GEN32", "GEN64", "GT32",
-                                      "GT64", "GH32", "GH64", "T32", "T64", "H32", "H64")]
+FAMILIES = ["QM_SHAPE_" + f for f in ("STREAM", "STREAM32", "LIGHT32", "LIGHT64", "NQ32", "NQ64", "GU32", "GU64",
+                                      "GEN32", "GEN64", "GT32", "GT64", "GH32", "GH64", "T32", "T64", "H32", "H64")]
 CUS = 256
 
 
@@ -48,9 +48,17 @@ def test_large_launches(family):
     """From 2 GB of one array on (2^27 vectors): one tile of four vectors to a
     workgroup for the families that gain by it; two tiles of their own else."""
     u, blocks = launch(family, 1 << 27)
-    if family[9:] in ("STREAM", "NQ64", "T32", "T64", "H32"):
+    if family[9:] in ("STREAM", "LIGHT64", "NQ64", "T32", "T64", "H32"):
         assert (u, blocks) == (4, 1 << 17)
-    elif family[9:] in ("STREAM32", "NQ32"):
+    elif family[9:] in ("STREAM32", "LIGHT32", "NQ32"):
         assert (u, blocks) == (4, 1 << 16)
     elif family == "QM_SHAPE_H64":
         assert (u, blocks) == (2, 1 << 17)
+
+
+@pytest.mark.parametrize("family", ["QM_SHAPE_LIGHT32", "QM_SHAPE_LIGHT64"])
+def test_light_maps_take_two_vectors(family):
+    """Arrays of 32 to 256 MB: with four vectors in flight these lost up to a
+    sixth to a fixed grid."""
+    for lg in (21, 22, 23):
+        assert launch(family, 1 << lg) == (2, min(64 * CUS, (1 << lg) // 512))
