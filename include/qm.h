@@ -348,7 +348,7 @@ qm_status qm_run_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count, void
  * the call itself allocates nothing, on the device or the host.
  *
  * Memory: the batch header and descriptors go to a fixed device array
- * (QM_BATCH_NOALLOC_MAX_REQUESTS records, about 768 KiB) that the library
+ * (QM_BATCH_NOALLOC_MAX_REQUESTS records, about 736 KiB) that the library
  * holds once per GPU until the process ends, its address looked up by
  * qm_init; they are staged through the context's pinned host buffer, also
  * set up by qm_init.

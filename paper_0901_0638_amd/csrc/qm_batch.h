@@ -31,7 +31,6 @@ struct BatchHeader {
     uint64_t total_chunks;
     uint32_t nreq;
     uint32_t reserved;
-    uint64_t chunk;         /* elements of a request per chunk: a request of n has ceil(n / chunk) */
     /* per-request completion (the serving loop), or both NULL: for a
        request with `flagged` chunks, count[i] in device memory, 0 at launch,
        counts its finished ones; the workgroup finishing the last sets the
@@ -48,9 +47,8 @@ struct BatchReq {
     void* out;
     uint64_t n;
     uint64_t chunk_base;    /* global index of the request's first chunk */
-    const double* coef;     /* Student t: device cell rows of the request's dtype */
     union {
-        StudentParams P;    /* Student t: table parameters */
+        StudentParams P;    /* Student t: table parameters (cells of the request's dtype) */
         HypParams H;        /* exp -> hyperbolic: table parameters (cells of the request's dtype) */
     };
 };
@@ -67,7 +65,7 @@ static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments");
 static_assert(sizeof(BatchHeader) % 8 == 0 && sizeof(BatchReq) % 8 == 0, "uploaded in 8-byte words");
 
 /* The allocation-free entry point's device array: one header and
-   QM_BATCH_NOALLOC_MAX_REQUESTS records (768 KiB) per GPU. */
+   QM_BATCH_NOALLOC_MAX_REQUESTS records (736 KiB) per GPU. */
 constexpr size_t BATCH_SCRATCH_BYTES = sizeof(BatchHeader) + QM_BATCH_NOALLOC_MAX_REQUESTS * sizeof(BatchReq);
 constexpr int BATCH_SCRATCH_MAX_DEVICES = 64;
 

@@ -258,8 +258,7 @@ static qm_status plan_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count,
             qm_status st = build_tables ? get_table(ctx, r.nu, &t) : find_table(ctx, r.nu, &t);
             if (st != QM_OK) return st;
             const TCells& c = r.dtype == QM_F64 ? t->hdr.f64 : t->hdr.f32;
-            b.coef = table_block(t->d_table) + c.coef_offset;
-            b.P = make_params(t->hdr, c, b.coef);
+            b.P = make_params(t->hdr, c, table_block(t->d_table) + c.coef_offset);
             if (!t->hdr.identity) lds = std::max(lds, student_lds_bytes(b.P));
         } else if (r.kind == QM_EXP_TO_HYPERBOLIC || r.kind == QM_EXP_TO_VG) {
             const bool vg = r.kind == QM_EXP_TO_VG;
@@ -282,7 +281,6 @@ static qm_status plan_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count,
     memset(h, 0, sizeof *h);
     h->total_chunks = chunks;
     h->nreq = nreq;
-    h->chunk = chunk;
     *lds_out = lds;
     return QM_OK;
 }
@@ -346,8 +344,9 @@ qm_status enqueue_batch(qm_ctx* ctx, const qm_request* reqs, uint64_t count, hip
         uint64_t total = 0, budget = 0;
         for (const BatchReq& r : d) total += r.n;
         budget = total < FLAG_MIN_ELEMENTS ? 0 : total / FLAG_ELEMENTS_PER_CHUNK;
-        for (BatchReq& r : d) {
-            const uint64_t c = (r.n + h.chunk - 1) / h.chunk;
+        for (size_t i = 0; i < d.size(); ++i) {
+            BatchReq& r = d[i];
+            const uint64_t c = (i + 1 < d.size() ? d[i + 1].chunk_base : h.total_chunks) - r.chunk_base;
             if (c > batch_flag_chunks() || c > budget) continue;
             budget -= c;
             r.flagged = (uint32_t)c;

@@ -91,7 +91,6 @@ StudentParams make_params(const TTableHeader& h, const TCells& c, const double* 
     P.log_K = h.log_K;
     P.tail_a = h.tail_a[0];
     P.sqrt_nu = __builtin_sqrt(h.nu);
-    P.inv_nu = 1.0 / h.nu;
     P.nu = h.nu;
     P.ncell = c.ncell;
     P.nlds = c.nlds;              /* 0 for nu = +inf, which has no cells */

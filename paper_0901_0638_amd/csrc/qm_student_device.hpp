@@ -14,7 +14,7 @@ namespace qm {
 /* Uniform per-launch parameters: the tail constants of the table header and
    the layout of the cell approximation in use. */
 struct StudentParams {
-    double h, inv_h, centre_offset, y_lds, y_max, log_K, tail_a, sqrt_nu, inv_nu, nu;
+    double h, inv_h, centre_offset, y_lds, y_max, log_K, tail_a, sqrt_nu, nu;
     const double* gcoef;  /* all ncell rows in global memory (the rare path reads them) */
     int ncell;        /* rows covering y <= y_max */
     int nlds;         /* rows staged in LDS, covering y <= y_lds */
