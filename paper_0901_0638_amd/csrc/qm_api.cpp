@@ -72,8 +72,8 @@ static const qm::KernelShape* default_shapes(int cus, qm::LaunchShape* shape, co
            exp -> normal: 166 us at 64 x 4, 175 at 2 x 4; 2^22 13.0, 14.0); 2^27
            337 us with two tiles each, 350 at 64 x 4 */
         {&shape->stream, "QM_SHAPE_STREAM", 64, 4, 128, 4, true},
-        /* FP32 maps: exp -> normal 2^24 25 us at 32 x 4, 28.6 at 32 x 2; 2^26
-           90 and 100; two tiles each 2^27 180 us, 177 at 32 x 4, 2^28 359 and
+        /* FP32 maps: exp -> normal 2^24 27 us at 32 x 4, 29 at 32 x 2; 2^26
+           102 and 105; two tiles each 2^27 180 us, 177 at 32 x 4, 2^28 359 and
            368 */
         {&shape->stream32, "QM_SHAPE_STREAM32", 32, 4, 256, 4, false},
         /* the same without a vote: the paper's FP32 quantile and FP64 exp ->

@@ -2,16 +2,17 @@
  * qm_batch.hip -- one launch over many requests of mixed kind,
  * dtype, mode and nu.
  *
- * Every request is cut into chunks of hdr->chunk elements; chunks are numbered
- * globally in request order (chunk_base = prefix sum).  Each workgroup starts
- * with the chunk of its own index and goes on in steps of the grid, finds
- * each chunk's request by its chunk_base, and evaluates it with the same walk
- * and per-element functions as the single-request kernels, so every output is
- * bitwise identical to the single call's.  A chunk
- * belongs to one request, so the kind switch and the wave votes inside the
- * maps are uniform across the workgroup.  A Student t or hyperbolic chunk
- * stages its table in LDS unless the workgroup's previous chunk already did.
- * Every workgroup reaches the end of its loop without waiting on another.
+ * Every request is cut into chunks of a number of elements that its batch
+ * sets (batch_chunk in qm_serve.cpp); chunks are numbered globally in
+ * request order (chunk_base = prefix sum).  Each workgroup starts with the
+ * chunk of its own index and goes on in steps of the grid, finds each
+ * chunk's request by its chunk_base, and evaluates it with the same walk and
+ * per-element functions as the single-request kernels, so every output is
+ * bitwise identical to the single call's.  A chunk belongs to one request,
+ * so the kind switch and the wave votes inside the maps are uniform across
+ * the workgroup.  A Student t or hyperbolic chunk stages its table in LDS
+ * unless the workgroup's previous chunk already did.  Every workgroup reaches
+ * the end of its loop without waiting on another.
  */
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -89,7 +89,7 @@ __device__ __forceinline__ float open_u23(uint32_t word)
     return __uint_as_float(__builtin_amdgcn_alignbit(0x7fu, word, 9u)) - (1.0f - 0x1p-24f);
 }
 
-/* element e of the stream, one at a time (heads, tails, unaligned outputs) */
+/* element e of the stream, one at a time (heads and tails) */
 template <typename T> __device__ T stream_uniform(uint64_t e, uint32_t k0, uint32_t k1);
 template <> __device__ __forceinline__ double stream_uniform<double>(uint64_t e, uint32_t k0, uint32_t k1)
 {

@@ -1,6 +1,7 @@
 /*
- * qm_stream.hpp -- how every elementwise kernel walks its arrays: wave tiles
- * of 16-byte vectors (shared by the streaming, generating and batch kernels).
+ * qm_stream.hpp -- how the kernels that read an array walk it: wave tiles of
+ * 16-byte vectors (streaming and batch kernels; the generating ones, which
+ * have no input, share the vector types and the launch rules).
  */
 #pragma once
 #include <hip/hip_runtime.h>

@@ -8,8 +8,9 @@
  * y = s^2 by one multiply, the offset d = s^2 - y_c by one fused
  * multiply-add (so the full input precision reaches the polynomial: log R
  * grows like y/(2 nu)), the cell's coefficients from LDS, Horner in d, one
- * multiply by z.  FP64 outputs use degree-15 cells, FP32 outputs degree-7
- * cells.  Elements beyond (|z| > 10, probability below 1e-23 for a normal
+ * multiply by z.  FP64 outputs use degree-7 cells where at most 200 of them
+ * cover y <= 100 (nu >= 3 or so) and degree-15 cells else, FP32 outputs their
+ * own degree-7 cells.  Elements beyond (|z| > 10, probability below 1e-23 for a normal
  * sample) are entered by a wave vote: the table's further cells from global
  * memory, then the two-term tail formula of Section 3.5 in log space.
  */
