@@ -69,6 +69,12 @@ int qm_debug_hyperbolic_table(double alpha, double beta, double delta, void* hea
 int qm_debug_vg_table(double lambda, double alpha, double beta, void* header_out, double* coef_out, int coef_cap);
 
 /*
+ * Staging slots (pinned and device memory for the descriptors of one batch)
+ * that a context (qm_ctx*) has made so far, or -1 for NULL.
+ */
+int qm_debug_staging_slots(void* ctx);
+
+/*
  * The launch of a kernel of one family, named by its variable ("QM_SHAPE_T64"
  * and so on, qm_init), over nvec 16-byte vectors on a device of `cus` compute
  * units, with the environment as it is now: *blocks gets the workgroups.

@@ -121,3 +121,25 @@ def test_small_requests_complete_before_their_batch(gpu, total, sizes):
         assert min(early) > 0, early
     finally:
         ctx.close()
+
+
+def test_staging_is_made_before_traffic(gpu):
+    """The serving loop has its staging slots when the first request is
+    admitted, and makes none while batches that need them run."""
+    total = 1 << 24
+    x = torch.rand(total, device="cuda", dtype=torch.float64).clamp_(1e-6, 1 - 1e-6)
+    y = [torch.empty_like(x) for _ in range(2)]
+    smalls = [torch.zeros(4096, device="cuda", dtype=torch.float64) for _ in range(40)]
+    ctx = qm.Context(0, hbm_budget_bytes=16 * total)
+    try:
+        slots = lambda: qm.load().qm_debug_staging_slots(ctx.handle)  # noqa: E731
+        assert slots() == 0
+        wait(ctx, [qm.qm_submit(ctx, quantile(x[:4096], smalls[0]))])
+        made = slots()
+        assert made >= 4
+        for _ in range(6):
+            block, small, big = submit_group(ctx, x, y, smalls)
+            wait(ctx, [block, *small, big])
+        assert slots() == made
+    finally:
+        ctx.close()
