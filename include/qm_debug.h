@@ -77,10 +77,12 @@ int qm_debug_staging_slots(void* ctx);
 /*
  * The launch of a kernel of one family, named by its variable ("QM_SHAPE_T64"
  * and so on, qm_init), over nvec 16-byte vectors on a device of `cus` compute
- * units, with the environment as it is now: *blocks gets the workgroups.
- * Returns the vectors per lane, or -1 for an unknown family.
+ * units, with the environment as it is now; table_bytes: what a Student t or
+ * hyperbolic launch stages, or 0.  *blocks gets the workgroups.  Returns the
+ * vectors per lane, or -1 for an unknown family.
  */
-int qm_debug_launch(const char* family, int cus, unsigned long long nvec, unsigned long long* blocks);
+int qm_debug_launch(const char* family, int cus, unsigned long long nvec, unsigned long long table_bytes,
+                    unsigned long long* blocks);
 
 /*
  * w[i] = a[i]^rho for 0 < a[i] <= 1, as the kernels form it for the origin

@@ -99,7 +99,8 @@ DEBUG_SIGNATURES = {
     "qm_debug_hyperbolic_table": (ctypes.c_int, [_d, _d, _d, _vp, ctypes.POINTER(_d), ctypes.c_int]),
     "qm_debug_vg_table": (ctypes.c_int, [_d, _d, _d, _vp, ctypes.POINTER(_d), ctypes.c_int]),
     "qm_debug_staging_slots": (ctypes.c_int, [_vp]),
-    "qm_debug_launch": (ctypes.c_int, [ctypes.c_char_p, _i, ctypes.c_ulonglong, ctypes.POINTER(ctypes.c_ulonglong)]),
+    "qm_debug_launch": (ctypes.c_int, [ctypes.c_char_p, _i, ctypes.c_ulonglong, ctypes.c_ulonglong,
+                                       ctypes.POINTER(ctypes.c_ulonglong)]),
     "qm_debug_pow_small": (ctypes.c_int, [ctypes.POINTER(_d), _d, ctypes.POINTER(_d), ctypes.c_int]),
 }
 

@@ -647,14 +647,18 @@ const char* qm_status_string(qm_status s)
 const char* qm_last_error(void) { return g_last_error.c_str(); }
 
 /* The launch of nvec vectors (include/qm_debug.h). */
-int qm_debug_launch(const char* family, int cus, unsigned long long nvec, unsigned long long* blocks)
+int qm_debug_launch(const char* family, int cus, unsigned long long nvec, unsigned long long table_bytes,
+                    unsigned long long* blocks)
 {
     qm::LaunchShape shape{};
     if (!family || !blocks || cus < 1) return -1;
-    const qm::KernelShape* ks = default_shapes(cus, &shape, family);
-    if (!ks) return -1;
-    const int u = qm::launch_unroll(nvec, *ks, cus);
-    *blocks = qm::launch_blocks(nvec, u, *ks);
+    const qm::KernelShape* found = default_shapes(cus, &shape, family);
+    if (!found) return -1;
+    qm::KernelShape ks = *found;
+    const bool student = found >= shape.student && found < shape.student + 2;
+    if (table_bytes) qm::fit_to_table(ks, table_bytes, student ? qm::T_TABLE_BLOCKS : qm::H_TABLE_BLOCKS, cus);
+    const int u = qm::launch_unroll(nvec, ks, cus);
+    *blocks = qm::launch_blocks(nvec, u, ks);
     return u;
 }
 

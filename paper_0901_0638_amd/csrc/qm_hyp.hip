@@ -111,6 +111,7 @@ static hipError_t launch_h(const void* in, void* out, uint64_t n, const HypParam
        196 us at 64 workgroups per unit, 219 with two tiles each; 2^28 765 and
        853) */
     if (P.jlo) shape.big_blocks = 64 * (uint64_t)cus;
+    else fit_to_table(shape, lds, H_TABLE_BLOCKS, cus);
     const int u = launch_unroll(a.nvec, shape, cus);
     const dim3 grid(launch_blocks(a.nvec, u, shape)), block(256);
     with_unroll(u, [&](auto U) {

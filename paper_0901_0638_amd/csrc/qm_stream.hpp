@@ -164,6 +164,24 @@ __device__ __forceinline__ void run_edges(const Span<T>& s, const Map& map)
     }
 }
 
+/*
+ * A large launch over a table of more than 24 KB in LDS: a workgroup for every
+ * tile or two would stage more than the 16 KB that it reads, so such a launch
+ * keeps a grid of a few workgroups per unit, with four vectors per lane.
+ * MI355X, us, two tiles each -> fixed grid: FP64 hyperbolic (1, 0, 1e-6), 41
+ * KB, 2^27 517 -> 374 at 16 per unit, (1, 0.9, 5), 27 KB, 412 -> 380; FP64
+ * Student t nu = 0.3, 51 KB, 713 -> 523 at 2 per unit, nu = 0.4, 29 KB, 2^25 99
+ * -> 92, 2^27 387 -> 388; FP32 nu = 0.3, 32 KB, 207 -> 185.
+ */
+constexpr int T_TABLE_BLOCKS = 2, H_TABLE_BLOCKS = 16;
+inline void fit_to_table(KernelShape& ks, size_t lds_bytes, int blocks_per_cu, int cus)
+{
+    if (lds_bytes <= 24 * 1024) return;
+    ks.big_unroll = 4;
+    ks.big_blocks = (uint64_t)blocks_per_cu * cus;
+    ks.huge_vecs = 0;
+}
+
 /* launches of the last two kinds of KernelShape */
 inline bool launch_big(uint64_t nvec, const KernelShape& ks) { return ks.big_vecs && nvec >= ks.big_vecs; }
 inline bool launch_huge(uint64_t nvec, const KernelShape& ks) { return ks.huge_vecs && nvec >= ks.huge_vecs; }

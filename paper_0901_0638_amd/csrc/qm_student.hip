@@ -107,7 +107,6 @@ static hipError_t launch_t(const void* in, void* out, uint64_t n, const double* 
                            hipStream_t s, const LaunchShape& shape_all)
 {
     KernelShape shape = shape_all.student[sizeof(T) == 8];
-    if (DEG == T_DEGREE_HIGH) shape.huge_vecs = 0;   /* 25 KB and more to stage: two tiles a workgroup */
     if (h.identity) {
         uint64_t blocks = (n + 255) / 256;
         if (blocks > shape.max_blocks) blocks = shape.max_blocks;
@@ -119,6 +118,15 @@ static hipError_t launch_t(const void* in, void* out, uint64_t n, const double* 
     const StudentParams P = make_params(h, c, d_block + c.coef_offset);
     const size_t lds = student_lds_bytes(P);
     if (lds > 65536) return hipErrorInvalidValue;   /* beyond the dynamic LDS a launch may ask for */
+    fit_to_table(shape, lds, T_TABLE_BLOCKS, shape_all.cus);
+    if (DEG == T_DEGREE_HIGH) {
+        /* rows of 16: two tiles from 2^26 elements on (2^25, nu = 1: 91 to 98 us
+           on two cards, 89 to 92 on the fixed grid; 2^26 174, 179 to 191), one
+           only where a thread stages one piece (2^28: 694 us with 32 rows, 761
+           with 33) */
+        shape.big_vecs *= 2;
+        if (P.nlds > 32) shape.huge_vecs = 0;
+    }
     const Span<T> a = make_span(static_cast<const T*>(in), static_cast<T*>(out), n);
     const int u = launch_unroll(a.nvec, shape, shape_all.cus);
     const dim3 grid(launch_blocks(a.nvec, u, shape)), block(256);

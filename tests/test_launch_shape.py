@@ -16,15 +16,15 @@ def no_overrides(monkeypatch):
         monkeypatch.delenv(name, raising=False)
 
 
-def launch(family, nvec):
+def launch(family, nvec, table=0):
     blocks = ctypes.c_ulonglong()
-    u = qm.load().qm_debug_launch(family.encode(), CUS, nvec, ctypes.byref(blocks))
+    u = qm.load().qm_debug_launch(family.encode(), CUS, nvec, table, ctypes.byref(blocks))
     assert u in (1, 2, 4) and 1 <= blocks.value < 1 << 23
     return u, blocks.value
 
 
 def test_unknown_family():
-    assert qm.load().qm_debug_launch(b"QM_SHAPE_X", CUS, 1, ctypes.byref(ctypes.c_ulonglong())) == -1
+    assert qm.load().qm_debug_launch(b"QM_SHAPE_X", CUS, 1, 0, ctypes.byref(ctypes.c_ulonglong())) == -1
 
 
 @pytest.mark.parametrize("family", FAMILIES)
@@ -62,3 +62,14 @@ def test_light_maps_take_two_vectors(family):
     sixth to a fixed grid."""
     for lg in (21, 22, 23):
         assert launch(family, 1 << lg) == (2, min(64 * CUS, (1 << lg) // 512))
+
+
+@pytest.mark.parametrize("family,per_unit", [("T32", 2), ("T64", 2), ("H32", 16), ("H64", 16)])
+def test_large_tables_are_staged_by_few_workgroups(family, per_unit):
+    """More than 24 KB to stage: large launches keep a fixed grid."""
+    family = "QM_SHAPE_" + family
+    for nvec in (1 << 24, 1 << 26, 1 << 28):
+        assert launch(family, nvec, 24 * 1024) == launch(family, nvec)
+        assert launch(family, nvec)[1] > 64 * CUS - 1
+        assert launch(family, nvec, 28 * 1024) == (4, per_unit * CUS)
+    assert launch(family, 1 << 21, 50 * 1024) == launch(family, 1 << 21)
