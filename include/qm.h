@@ -105,7 +105,7 @@ typedef struct qm_ctx qm_ctx;
  * compute unit x 16-byte vectors in flight per lane, from measured sweeps:
  * FP64 maps 64 x 4, FP32 maps 32 x 4 (both 64 x 2 for the paper's exp ->
  * normal in FP64 and the paper and plain quantiles in FP32), FP64 quantile
- * 64 x 4, FP32+refine quantile 32 x 4, Student t 2 x 4 (FP64) and 4 x 2
+ * 64 x 2, FP32+refine quantile 32 x 4, Student t 2 x 4 (FP64) and 4 x 2
  * (FP32), exp -> hyperbolic or variance-gamma 3 x 2 and 4 x 2; fused
  * generation of uniforms one vector per lane and workgroup, quantiles 64 x 4
  * (FP64) and 32 x 4 (FP32), Student t 16 x 4, hyperbolic 16 x 4 and 16 x 2);

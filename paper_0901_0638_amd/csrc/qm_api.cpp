@@ -86,11 +86,14 @@ static const qm::KernelShape* default_shapes(int cus, qm::LaunchShape* shape, co
         {&shape->light[0], "QM_SHAPE_LIGHT32", 64, 2, 256, 4, false},
         {&shape->light[1], "QM_SHAPE_LIGHT64", 64, 2, 128, 4, true},
         /* quantiles: FP32+refine 2^26 93 us at 32 x 4, 98 at 16 x 4; two tiles
-           each 2^27 188, 183 at 32 x 4, 2^28 368 and 376; FP64 2^25 84 at
-           64 x 4, 2^26 173, 187 at 16 x 4; two tiles of 2 vectors each 2^26 170,
-           2^27 347 (of 4: 351), 362 at 64 x 4 */
+           each 2^27 188, 183 at 32 x 4, 2^28 368 and 376; FP64 2^25 86 at
+           64 x 2, 2^26 175, 185 at 32 x 2; two tiles of 2 vectors each 2^26 171,
+           2^27 347 (of 4: 351), 362 at 64 x 4.  With 4 vectors in flight the FP64
+           time on uniforms depends on the card and the buffers: 2^22 15.7..17.7 at
+           64 x 4, 13.8..14.2 at 64 x 2, 2^23 26..30 and 24, 2^24 45..56 and 45..46;
+           on the mixture 4 gain 2% from 2^24 to 2^25, 2 lose 10% on 2^21 */
         {&shape->hybrid[0], "QM_SHAPE_NQ32", 32, 4, 256, 4, false},
-        {&shape->hybrid[1], "QM_SHAPE_NQ64", 64, 4, 256, 2, true},
+        {&shape->hybrid[1], "QM_SHAPE_NQ64", 64, 2, 256, 2, true},
         /* fused generation, write only.  Uniforms: the stores alone, and those
            are fastest as one 4 KB row to a workgroup, all of them written in
            order (FP64 2^26 76 us, 83 with four rows, 89 at 64 x 4, 2^28 329, 365
