@@ -68,7 +68,7 @@ static const qm::KernelShape* default_shapes(int cus, qm::LaunchShape* shape, co
        `big` tiles of big_unroll vectors per unit on; huge: its one tile from
        2 GB on */
     struct { qm::KernelShape* ks; const char* env; long bpc, unroll, big, big_unroll; bool huge; } fam[] = {
-        /* light FP64 maps: with no table to stage, many workgroups (2^26
+        /* FP64 maps with no table to stage: many workgroups (2^26
            exp -> normal: 166 us at 64 x 4, 175 at 2 x 4; 2^22 13.0, 14.0); 2^27
            337 us with two tiles each, 350 at 64 x 4 */
         {&shape->stream, "QM_SHAPE_STREAM", 64, 4, 128, 4, true},
